@@ -29,6 +29,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 namespace ldu {
 
@@ -1128,54 +1129,63 @@ k_vc_rrestrict_cmp(SellView<T> R, const T *__restrict__ r, T *__restrict__ rc,
     });
 }
 
-// r_c = R r, and the coarse level's first Jacobi sweep from zero
-// e_c = omega r_c / D_c when ec_first is given.  G lanes share a row: lane g
+// the sum over row c of R of value times x(column), shared by G lanes: lane g
 // of the group sums the row's entries g, g + G, g + 2G, ... in order, then
 // the group adds its G partial sums by a fixed butterfly (every lane ends
-// with the same total).  A wave covers 64 / G consecutive rows.  The order
-// is fixed, so results are reproducible; it is not the row's column order,
-// which R's results never had to follow (R's rows are sums the oracle forms
-// in two steps, residual then restriction).
-template <int G, typename T>
+// with the same total).  The order is fixed, so results are reproducible; it
+// is not the row's column order.  Every lane of the wave calls this (lanes
+// without a row: c >= R.n).
+template <int G, bool NT, typename T, class XA>
+__device__ __forceinline__ T csr_row_sum(const CsrView<T> &R, int64_t c, int g, const XA &x) {
+    constexpr int U = kCsrBatch;
+    T acc = T(0);
+    if (c < R.n) {
+        const int64_t e1 = R.rptr[c + 1];
+        for (int64_t k0 = R.rptr[c] + g; k0 < e1; k0 += (int64_t)G * U) {
+            int32_t cc[U];
+            T vv[U], xv[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int64_t k = k0 + (int64_t)u * G;
+                if (k < e1) {
+                    cc[u] = vld<NT>(R.col + k);
+                    vv[u] = vld<NT>(R.val + k);
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (k0 + (int64_t)u * G < e1) xv[u] = x(cc[u]);
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (k0 + (int64_t)u * G < e1) acc = acc + vv[u] * xv[u];
+        }
+    }
+#pragma unroll
+    for (int off = G / 2; off > 0; off >>= 1) acc = acc + __shfl_xor(acc, off);
+    return acc;
+}
+
+// r_c = R r, and the coarse level's first Jacobi sweep from zero
+// e_c = omega r_c / D_c when ec_first is given.  G lanes share a row, so a
+// wave covers 64 / G consecutive rows.  R's results never had to follow the
+// row's column order (R's rows are sums the oracle forms in two steps,
+// residual then restriction).
+template <int G, bool NT, typename T>
 __global__ void __launch_bounds__(kBlock)
 k_vc_rrestrict_csr(CsrView<T> R, const T *__restrict__ r, T *__restrict__ rc,
                T *__restrict__ ec_first, const T *__restrict__ Dc, T omega,
                const DevScalars *ds) {
     if (vc_skip(ds)) return;
     constexpr int RPW = kWave / G;
-    constexpr int U = kCsrBatch;
     const int lane = threadIdx.x & 63;
     const int g = lane % G;
     const int64_t chunks = (R.n + RPW - 1) / RPW;
     for_each_slice(chunks, [&](int64_t s) {
         const int64_t c = s * RPW + lane / G;
-        T acc = T(0), dc = T(1);
-        if (c < R.n) {
-            // the coarse diagonal is loaded before the row, so its round
-            // trip overlaps the row's gathers
-            if (ec_first && g == 0) dc = Dc[c];
-            const int64_t e1 = R.rptr[c + 1];
-            for (int64_t k0 = R.rptr[c] + g; k0 < e1; k0 += (int64_t)G * U) {
-                int32_t cc[U];
-                T vv[U], xv[U];
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    const int64_t k = k0 + (int64_t)u * G;
-                    if (k < e1) {
-                        cc[u] = __builtin_nontemporal_load(R.col + k);
-                        vv[u] = __builtin_nontemporal_load(R.val + k);
-                    }
-                }
-#pragma unroll
-                for (int u = 0; u < U; ++u)
-                    if (k0 + (int64_t)u * G < e1) xv[u] = r[cc[u]];
-#pragma unroll
-                for (int u = 0; u < U; ++u)
-                    if (k0 + (int64_t)u * G < e1) acc = acc + vv[u] * xv[u];
-            }
-        }
-#pragma unroll
-        for (int off = G / 2; off > 0; off >>= 1) acc = acc + __shfl_xor(acc, off);
+        // the coarse diagonal is loaded before the row, so its round trip
+        // overlaps the row's gathers
+        const T dc = (ec_first && g == 0 && c < R.n) ? Dc[c] : T(1);
+        const T acc = csr_row_sum<G, NT>(R, c, g, Direct<T>{r});
         if (c < R.n && g == 0) {
             rc[c] = acc;
             if (ec_first) ec_first[c] = omega * acc / dc;
@@ -1183,18 +1193,164 @@ k_vc_rrestrict_csr(CsrView<T> R, const T *__restrict__ r, T *__restrict__ rc,
     });
 }
 
+// ---------------------------------------------------------------- up-leg operator
+// The up leg of the same cycles on a small level: the first sweep from zero,
+// the coarse correction and the first post-sweep are together one linear map
+// of the level's right-hand side and the coarse result,
+//   e0 = omega D^-1 r + P e_c,  e = e0 + omega D^-1 (r - A e0)
+//      = S r + Q e_c = U (r, e_c),
+//   S = omega D^-1 (2 I - omega A D^-1),  Q = (I - omega D^-1 A) P.
+// As separate steps the coarse level scattered its result through the member
+// lists and the sweep then ran a lane per row: eight dependent round trips to
+// memory (slice start, row header, entries, gathers, a second batch, members,
+// their values), about 8 us a level, on levels whose data takes under 1 us.
+// U's rows are shared by G lanes like R's, which leaves row bounds, entries
+// and gathers.  Levels of 600 to 50,000 cells (100^3 box, pairwise): 8.0-12.1
+// -> 4.0-7.5 us; 102,000 cells: 12.9 -> 15.2 us, so larger levels keep the
+// separate steps (kUpRows).  CG + V-cycle on that box 18.5 -> 17.0 ms.
+// Columns: j < n for r_j, n + c for e_c's entry c; a row holds its S entries
+// in column order (diagonal in place), then its Q entries by aggregate.
+template <typename T>
+struct Stacked {
+    const T *r, *ec;
+    int32_t n;
+    __device__ __forceinline__ T operator()(int32_t j) const {
+        const T *p = j < n ? r + j : ec + (j - n);
+        return *p;
+    }
+};
+
+template <int G, bool DOT, typename T>
+__global__ void __launch_bounds__(kBlock)
+k_vc_up_csr(CsrView<T> U, const T *__restrict__ r, const T *__restrict__ ec, T *__restrict__ e,
+            const T *__restrict__ rdot, double *partials, const DevScalars *ds) {
+    if (vc_skip(ds)) return;
+    constexpr int RPW = kWave / G;
+    const int lane = threadIdx.x & 63;
+    const int g = lane % G;
+    const int64_t chunks = (U.n + RPW - 1) / RPW;
+    double acc[1] = {0.0};
+    for_each_slice(chunks, [&](int64_t s) {
+        const int64_t i = s * RPW + lane / G;
+        const T z = csr_row_sum<G, false>(U, i, g, Stacked<T>{r, ec, U.n});
+        if (i < U.n && g == 0) {
+            e[i] = z;
+            if constexpr (DOT) acc[0] += (double)rdot[i] * (double)z;
+        }
+    });
+    if constexpr (DOT) block_partials<1>(acc, partials);
+}
+
+// row i's entries in column order with the diagonal in place: f(column,
+// position in A's slices, or -1 for the diagonal); padding is skipped
+template <class F>
+__device__ __forceinline__ void for_row_entries(const Sell &A, int32_t i, F &&f) {
+    const int64_t ps = A.iperm ? (int64_t)A.iperm[i] : (int64_t)i;
+    const int w = row_len(A, ps);
+    bool diag = false;
+    for (int k = 0; k < w; ++k) {
+        const int64_t e = entry_at(A, ps, k);
+        const int32_t j = A.col[e];
+        if (j == i) continue;
+        if (!diag && j > i) {
+            f(i, (int64_t)-1);
+            diag = true;
+        }
+        f(j, e);
+    }
+    if (!diag) f(i, (int64_t)-1);
+}
+
+// U's row lengths: the S entries and the distinct aggregates they lie in
+__global__ void k_up_count(Sell A, const int32_t *__restrict__ agg, int64_t *cnt) {
+    GRID_STRIDE(i, A.n) {
+        int64_t m = 0;
+        for_row_entries(A, (int32_t)i, [&](int32_t j, int64_t) {
+            const int32_t c = agg[j];
+            bool seen = false;  // an earlier entry of the row in the same aggregate
+            for_row_entries(A, (int32_t)i, [&](int32_t q, int64_t) {
+                seen = seen || (q < j && agg[q] == c);
+            });
+            m += seen ? 1 : 2;
+        });
+        cnt[i] = m;
+    }
+}
+
+// U's columns and values (val: A, valT: A^T) for this omega
+__global__ void k_up_fill(Sell A, Csr U, const int32_t *__restrict__ agg, double omega) {
+    GRID_STRIDE(i, A.n) {
+        const int64_t e0 = U.rptr[i], e1 = U.rptr[i + 1];
+        const double w = omega / A.diag[i];
+        int64_t s = e0, q0 = e0;
+        for_row_entries(A, (int32_t)i, [&](int32_t, int64_t) { ++q0; });
+        int64_t q = q0;  // end of the aggregates found so far
+        for_row_entries(A, (int32_t)i, [&](int32_t j, int64_t e) {
+            const double dj = A.diag[j];
+            const double a = e < 0 ? dj : A.val[e], at = e < 0 ? dj : A.valT[e];
+            U.col[s] = j;
+            U.val[s] = e < 0 ? w * (2.0 - omega) : w * ((-omega * a) / dj);
+            U.valT[s] = e < 0 ? w * (2.0 - omega) : w * ((-omega * at) / dj);
+            ++s;
+            const int32_t c = A.n + agg[j];
+            int64_t k = q0;
+            while (k < q && U.col[k] != c) ++k;
+            if (k == q) {
+                U.col[k] = c;
+                U.val[k] = U.valT[k] = 0.0;
+                ++q;
+            }
+            U.val[k] = U.val[k] + a;
+            U.valT[k] = U.valT[k] + at;
+        });
+        const int32_t own = A.n + agg[i];
+        for (int64_t k = q0; k < e1; ++k) {
+            const double p = U.col[k] == own ? 1.0 : 0.0;
+            U.val[k] = p - w * U.val[k];
+            U.valT[k] = p - w * U.valT[k];
+        }
+    }
+}
+
+// f(std::integral_constant<int, lanes per row>)
+template <class F>
+static void with_group(int group, F &&f) {
+    switch (group) {
+    case 1: f(std::integral_constant<int, 1>{}); break;
+    case 2: f(std::integral_constant<int, 2>{}); break;
+    case 4: f(std::integral_constant<int, 4>{}); break;
+    case 8: f(std::integral_constant<int, 8>{}); break;
+    default: f(std::integral_constant<int, 16>{});
+    }
+}
+
+// the number of blocks launched (of partials, with rdot)
+template <typename T>
+static int launch_up_csr(const CsrView<T> &U, const T *r, const T *ec, T *e, const T *rdot,
+                         double *partials, const DevScalars *ds, hipStream_t st) {
+    const int64_t chunks = (U.n + kWave / U.group - 1) / (kWave / U.group);
+    const int G = stream_grid_slices(chunks);
+    with_group(U.group, [&](auto lanes) {
+        constexpr int L = decltype(lanes)::value;
+        if (rdot) k_vc_up_csr<L, true, T><<<G, kBlock, 0, st>>>(U, r, ec, e, rdot, partials, ds);
+        else k_vc_up_csr<L, false, T><<<G, kBlock, 0, st>>>(U, r, ec, e, rdot, partials, ds);
+    });
+    return G;
+}
+
 template <typename T>
 static void launch_rrestrict_csr(const CsrView<T> &R, const T *r, T *rc, T *ec_first, const T *Dc,
                              T omega, const DevScalars *ds, hipStream_t st) {
     const int64_t chunks = (R.n + kWave / R.group - 1) / (kWave / R.group);
     const int G = stream_grid_slices(chunks);
-    switch (R.group) {
-    case 1: k_vc_rrestrict_csr<1, T><<<G, kBlock, 0, st>>>(R, r, rc, ec_first, Dc, omega, ds); break;
-    case 2: k_vc_rrestrict_csr<2, T><<<G, kBlock, 0, st>>>(R, r, rc, ec_first, Dc, omega, ds); break;
-    case 4: k_vc_rrestrict_csr<4, T><<<G, kBlock, 0, st>>>(R, r, rc, ec_first, Dc, omega, ds); break;
-    case 8: k_vc_rrestrict_csr<8, T><<<G, kBlock, 0, st>>>(R, r, rc, ec_first, Dc, omega, ds); break;
-    default: k_vc_rrestrict_csr<16, T><<<G, kBlock, 0, st>>>(R, r, rc, ec_first, Dc, omega, ds);
-    }
+    const bool nt = R.nnz * (int64_t)(sizeof(int32_t) + sizeof(T)) > kCsrCachedBytes;
+    with_group(R.group, [&](auto lanes) {
+        constexpr int L = decltype(lanes)::value;
+        if (nt)
+            k_vc_rrestrict_csr<L, true, T><<<G, kBlock, 0, st>>>(R, r, rc, ec_first, Dc, omega, ds);
+        else
+            k_vc_rrestrict_csr<L, false, T><<<G, kBlock, 0, st>>>(R, r, rc, ec_first, Dc, omega, ds);
+    });
 }
 
 // c = P e_c; s = (c . t) / (c . A c), or 1 when c.Ac is ~0
@@ -1752,6 +1908,12 @@ template <>
 CsrView<double> rcview<double>(const Level &L, bool tr) { return L.Rc.view(tr); }
 template <>
 CsrView<float> rcview<float>(const Level &L, bool tr) { return L.Rc.view32(tr); }
+template <typename T>
+static CsrView<T> upview(const Level &L, bool tr);
+template <>
+CsrView<double> upview<double>(const Level &L, bool tr) { return L.Uc.view(tr); }
+template <>
+CsrView<float> upview<float>(const Level &L, bool tr) { return L.Uc.view32(tr); }
 // R's values of this precision exist (either layout)
 template <typename T>
 static const T *ahval(const Level &L, bool tr);
@@ -1778,20 +1940,46 @@ float *lvec<float>(Level &L, int which) {
 }
 
 constexpr int kFuseCorrRows = 1 << 17;
+// levels of at most this many cells run their up leg as the operator U (limits
+// of 2^14, 2^16, 2^17 and 400,000 cells: 17.7, 17.0, 17.2 and 17.7 ms for CG +
+// V-cycle at 100^3, 127.1, 126.2, 126.6 and 129.7 ms at 200^3)
+#ifndef LDU_UP_ROWS
+#define LDU_UP_ROWS (1 << 16)
+#endif
+constexpr int kUpRows = LDU_UP_ROWS;
 
+// level l's down leg runs in one pass (R, or the scaled slices)
+template <typename T>
+static bool rop_level(const VCtx &c, size_t l) {
+    const Level &L = c.h->levels[l];
+    return rop_cycle(*c.o) && L.r_ready && L.r_omega == c.o->omega && has_rop<T>(L, c.tr);
+}
+// level l's up leg runs through U
+template <typename T>
+static bool up_level(const VCtx &c, size_t l) {
+    return rop_level<T>(c, l) && c.o->n_post > 0 && upview<T>(c.h->levels[l], c.tr).val;
+}
+// level l's unscaled correction is applied by the coarse level's last kernel
+// (a coarse level that runs through U leaves it to level l)
+template <typename T>
+static bool takes_correction(const VCtx &c, size_t l) {
+    const bool coarse_up = l + 2 < c.h->levels.size() && up_level<T>(c, l + 1);
+    return !c.o->scale_correction && c.h->levels[l].n <= kFuseCorrRows && !up_level<T>(c, l) &&
+           !coarse_up;
+}
 
 // One V-cycle e = V(l, r); returns the buffer holding e.  With rdot, the
-// last level-l kernel also leaves the block partials of rdot . e in
-// h->partials and *dotted is set (only when that kernel is a Jacobi sweep).
+// last level-l kernel also leaves its block partials of rdot . e in
+// h->partials and their number in *dotted (0: that kernel took no dot).
 // e_ready: the caller's restriction already stored the first Jacobi sweep
 // e = omega r / D in this level's e.  fc: the finer level's unscaled
 // correction e_f += P e, applied here by the kernel that produces e when it
 // can (*corrected tells the caller).
 template <typename T>
 static T *vcycle(const VCtx &c, size_t l, const T *r, const T *rdot = nullptr,
-                 bool *dotted = nullptr, bool e_ready = false, FineCorr<T> fc = {},
+                 int *dotted = nullptr, bool e_ready = false, FineCorr<T> fc = {},
                  bool *corrected = nullptr) {
-    if (dotted) *dotted = false;
+    if (dotted) *dotted = 0;
     if (corrected) *corrected = false;
     ldu_t *h = c.h;
     Level &L = h->levels[l];
@@ -1825,13 +2013,14 @@ static T *vcycle(const VCtx &c, size_t l, const T *r, const T *rdot = nullptr,
     const T omega = (T)c.o->omega;
     const bool gs = c.o->smoother == LDU_SMOOTH_GS2;
     T *w1 = lvec<T>(L, 4);
-    const bool rop = rop_cycle(*c.o) && L.r_ready && L.r_omega == c.o->omega &&
-                     has_rop<T>(L, c.tr);
+    const bool rop = rop_level<T>(c, l);
+    // small levels: first sweep, correction and first post-sweep as U (r, e_c)
+    const bool up = up_level<T>(c, l);
     // without correction scaling, on levels small enough to be bound by launch
     // latency, the coarse level applies e += P e_c itself (a scatter through
     // the member lists: on large levels the gather form of k_vc_correct moves
     // fewer bytes)
-    const bool fuse_corr = !c.o->scale_correction && L.n <= kFuseCorrRows;
+    const bool fuse_corr = takes_correction<T>(c, l);
     // with the one-pass down leg nothing reads the first sweep before the
     // correction, which then forms it itself
     const bool defer_first = rop && !e_ready && !fuse_corr;
@@ -1841,7 +2030,7 @@ static T *vcycle(const VCtx &c, size_t l, const T *r, const T *rdot = nullptr,
             gs_sweep<T>(A, r, e, t, e2, w1, k == 0, false, c.o->gs_inner, h->dev, G, st);
     } else {
         if (c.o->n_pre == 0) k_vc_zero<T><<<G, kBlock, 0, st>>>(L.n, S, e, h->dev);
-        else if (!e_ready && !defer_first)
+        else if (!e_ready && !defer_first && !up)
             k_vc_first<T><<<G, kBlock, 0, st>>>(L.n, S, r, A.diag, e, omega, h->dev);
         for (int k = 1; k < c.o->n_pre; ++k) {
             launch_jacobi<T>(A, r, e, e2, omega, nullptr, nullptr, {}, h->dev, G, st);
@@ -1853,9 +2042,8 @@ static T *vcycle(const VCtx &c, size_t l, const T *r, const T *rdot = nullptr,
     // the coarse level's first Jacobi sweep rides on the restriction, unless
     // the coarse level will form it in its own correction (a large
     // non-coarsest level whose down leg also runs through R)
-    const bool c_defers = l + 2 < h->levels.size() && rop && C.r_ready &&
-                          C.r_omega == c.o->omega && has_rop<T>(C, c.tr) &&
-                          C.n > kFuseCorrRows;
+    const bool c_defers = l + 2 < h->levels.size() && rop_level<T>(c, l + 1) &&
+                          !takes_correction<T>(c, l + 1);
     const bool c_first = !gs && c.o->n_pre > 0 && l + 2 < h->levels.size() && !c_defers;
     T *ec_first = c_first ? lvec<T>(C, 1) : nullptr;
     if (rop) {
@@ -1893,10 +2081,17 @@ static T *vcycle(const VCtx &c, size_t l, const T *r, const T *rdot = nullptr,
         else k_vc_scale<false, T><<<G, kBlock, 0, st>>>(A, ec, L.agg, t, h->partials, h->dev);
         launch_finalize<2>(h->partials, G, h->dev, EpiScale{}, st);
     }
-    if (!done_corr)
+    int post = 0;  // post-sweeps done
+    if (up) {
+        const bool last = c.o->n_post == 1;
+        const int blocks = launch_up_csr<T>(upview<T>(L, c.tr), r, ec, e, last ? rdot : nullptr,
+                                            h->partials, h->dev, st);
+        if (last && rdot && dotted) *dotted = blocks;
+        post = 1;
+    } else if (!done_corr)
         k_vc_correct<T><<<G, kBlock, 0, st>>>(L.n, S, ec, L.agg, e, c.o->scale_correction,
                                              defer_first ? r : nullptr, A.diag, omega, h->dev);
-    for (int k = 0; k < c.o->n_post; ++k) {
+    for (int k = post; k < c.o->n_post; ++k) {
         const bool last = k + 1 == c.o->n_post;
         if (gs) {  // backward sweeps: the V-cycle stays symmetric
             gs_sweep<T>(A, r, e, t, e2, w1, false, true, c.o->gs_inner, h->dev, G, st);
@@ -1904,7 +2099,7 @@ static T *vcycle(const VCtx &c, size_t l, const T *r, const T *rdot = nullptr,
             launch_jacobi<T>(A, r, e, e2, omega, last ? rdot : nullptr, h->partials,
                              last ? fc : FineCorr<T>{}, h->dev, G, st);
             std::swap(e, e2);
-            if (last && rdot && dotted) *dotted = true;
+            if (last && rdot && dotted) *dotted = G;
             if (last && fc.e && corrected) *corrected = true;
         }
     }
@@ -1927,6 +2122,34 @@ static void ensure_work32(ldu_t *h, hipStream_t st) {
 // buffers and factors a cycle needs beyond the hierarchy: the second
 // ping-pong vector of the two-stage smoother (three or more inner steps) and
 // the DIC pivots of the coarsest level
+// lanes per row of a CSR operator: the power of two nearest mean row length /
+// entries per lane
+static int csr_group(int64_t nnz, int32_t n) {
+    const double per = (double)nnz / std::max<int32_t>(n, 1) / kCsrEntriesPerLane;
+    int g = 1;
+    while (g < 16 && 2.0 * g <= per * 1.41421356) g *= 2;
+    return g;
+}
+
+// U's row bounds and arrays for level l (columns and values: k_up_fill)
+static void up_structure(ldu_t *h, size_t l, hipStream_t st) {
+    Level &L = h->levels[l];
+    Arena tmp;
+    Csr &U = L.Uc;
+    U = Csr{};
+    U.n = L.n;
+    U.rptr = h->gamg_arena.get<int64_t>((size_t)L.n + 1);
+    int64_t *cnt = tmp.get<int64_t>(L.n);
+    k_up_count<<<grid_n(L.n), kBlock, 0, st>>>(L.A, L.agg, cnt);
+    exclusive_scan_i64(cnt, U.rptr, L.n, tmp, st);
+    HIP_CHECK(hipMemcpyAsync(&U.nnz, U.rptr + L.n, sizeof(int64_t), hipMemcpyDeviceToHost, st));
+    HIP_CHECK(hipStreamSynchronize(st));
+    U.col = h->gamg_arena.get<int32_t>(U.nnz);
+    U.val = h->gamg_arena.get<double>(U.nnz);
+    U.valT = h->gamg_arena.get<double>(U.nnz);
+    U.group = csr_group(U.nnz, U.n);
+}
+
 // R's structure for level l (once per hierarchy): its slices and, per
 // entry, the run of sources its value sums
 static void rop_structure(ldu_t *h, size_t l, hipStream_t st) {
@@ -1971,15 +2194,12 @@ static void rop_structure(ldu_t *h, size_t l, hipStream_t st) {
         R.col = h->gamg_arena.get<int32_t>(R.nnz);
         R.val = h->gamg_arena.get<double>(R.nnz);
         R.valT = h->gamg_arena.get<double>(R.nnz);
-        // lanes per row: the power of two nearest mean length / entries per lane
-        const double per = (double)R.nnz / std::max<int32_t>(C.n, 1) / kCsrEntriesPerLane;
-        int g = 1;
-        while (g < 16 && 2.0 * g <= per * 1.41421356) g *= 2;
-        R.group = g;
+        R.group = csr_group(R.nnz, C.n);
         L.r_src0 = h->gamg_arena.get<int64_t>(R.nnz);
         L.r_srcn = h->gamg_arena.get<int32_t>(R.nnz);
         k_rop_link_csr<<<grid_n(C.n), kBlock, 0, st>>>(C.n, R, tstart, tcol, L.r_src0, L.r_srcn);
     }
+    if (L.Rc.rptr && L.n <= kUpRows) up_structure(h, l, st);
     HIP_CHECK(hipGetLastError());
     HIP_CHECK(hipStreamSynchronize(st));  // tmp is released after this point
     L.r_ready = false;
@@ -2010,6 +2230,13 @@ static void rop_values(Level &L, double omega, hipStream_t st) {
     };
     if (L.R.sptr) fill(L.R);
     else fill(L.Rc);
+    if (L.Uc.rptr) {
+        k_up_fill<<<grid_n(L.n), kBlock, 0, st>>>(L.A, L.Uc, L.agg, omega);
+        if (L.Uc.val32) {
+            k_rop_f32<<<grid_n(L.Uc.nnz), kBlock, 0, st>>>(L.Uc.val, L.Uc.val32, L.Uc.nnz);
+            k_rop_f32<<<grid_n(L.Uc.nnz), kBlock, 0, st>>>(L.Uc.valT, L.Uc.valT32, L.Uc.nnz);
+        }
+    }
     HIP_CHECK(hipGetLastError());
     L.r_omega = omega;
     L.r_ready = true;
@@ -2044,6 +2271,7 @@ static void ensure_rop(ldu_t *h, const ldu_gamg_opts &o, hipStream_t st) {
             f32_copies(L.R);
         } else {
             f32_copies(L.Rc);
+            if (L.Uc.rptr) f32_copies(L.Uc);
         }
         HIP_CHECK(hipGetLastError());
     }
@@ -2286,10 +2514,10 @@ int pcg_gamg_fp64(ldu_t *h, const double *b, double *x, const ldu_pcg_opts &o, b
                     k_pg_update<false><<<G, kBlock, 0, st>>>(n, S, h->r, h->q, h->partials,
                                                              h->dev);
                 launch_converge(h, G, false, st);
-                bool dotted = false;
-                z = vcycle<double>(c, 0, h->r, h->r, &dotted);
-                if (!dotted) k_pg_rz<<<G, kBlock, 0, st>>>(n, S, h->r, z, h->partials, h->dev);
-                launch_finalize<1>(h->partials, G, h->dev, EpiBeta{}, st);
+                int blocks = 0;  // the last level-0 kernel may take r.z itself
+                z = vcycle<double>(c, 0, h->r, h->r, &blocks);
+                if (!blocks) k_pg_rz<<<G, kBlock, 0, st>>>(n, S, h->r, z, h->partials, h->dev);
+                launch_finalize<1>(h->partials, blocks ? blocks : G, h->dev, EpiBeta{}, st);
                 k_pg_p<<<G, kBlock, 0, st>>>(n, S, x, z, h->p, h->dev);
             }
             HIP_CHECK(hipGetLastError());
@@ -2454,10 +2682,10 @@ int pcg_gamg_mixed(ldu_t *h, const double *b, double *x, const ldu_pcg_opts &o, 
             for (int k = 0; k < every; ++k) {
                 launch_mx_q(h, A32, G, st);
                 launch_mx_update_plain(h, n, S, G, st);
-                bool dotted = false;  // the last level-0 sweep may take r.z itself
-                z = vcycle<float>(c, 0, h->r32, h->r32, &dotted);
-                if (!dotted) k_mxg_rz<<<G, kBlock, 0, st>>>(n, S, h->r32, z, h->partials, h->dev);
-                launch_finalize<1>(h->partials, G, h->dev, EpiMxBeta{}, st);
+                int blocks = 0;  // the last level-0 kernel may take r.z itself
+                z = vcycle<float>(c, 0, h->r32, h->r32, &blocks);
+                if (!blocks) k_mxg_rz<<<G, kBlock, 0, st>>>(n, S, h->r32, z, h->partials, h->dev);
+                launch_finalize<1>(h->partials, blocks ? blocks : G, h->dev, EpiMxBeta{}, st);
                 k_mxg_p<<<G, kBlock, 0, st>>>(n, S, z, h->p32, h->dev);
             }
             HIP_CHECK(hipGetLastError());
