@@ -2,6 +2,7 @@
 // internal exceptions to status codes; nothing but plain C crosses the ABI.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -24,33 +25,100 @@ void hip_fail(hipError_t e, const char *what, const char *file, int line) {
     throw Error(LDU_ERR_HIP, buf);
 }
 
-Arena::~Arena() { release_all(); }
-
-void *Arena::alloc(size_t bytes) {
+static void *device_alloc(size_t bytes) {
     void *p = nullptr;
-    if (bytes == 0) bytes = 16;
-    hipError_t e = hipMalloc(&p, bytes);
-    if (e != hipSuccess) {
+    if (hipMalloc(&p, bytes) != hipSuccess) {
         (void)hipGetLastError();
         throw Error(LDU_ERR_NOMEM, "hipMalloc of " + std::to_string(bytes) + " bytes failed");
     }
-    ptrs_.push_back(p);
     return p;
 }
 
+// a chunk for a request of `bytes` beside `total` bytes held already: half as
+// much again, at least 1 MiB and at most 512 MiB beyond the request, or just
+// the request when that much is not there
+static Chunk new_chunk(size_t bytes, size_t total) {
+    Chunk c;
+    c.bytes = std::max(bytes, std::min(std::max(total / 2, size_t(1) << 20), size_t(512) << 20));
+    void *p = nullptr;
+    if (c.bytes > bytes && hipMalloc(&p, c.bytes) != hipSuccess) {
+        (void)hipGetLastError();
+        p = nullptr;
+        c.bytes = bytes;
+    }
+    c.p = static_cast<char *>(p ? p : device_alloc(c.bytes));
+    return c;
+}
+
+Chunk ChunkPool::take(size_t bytes) {
+    size_t best = free_.size();
+    for (size_t k = 0; k < free_.size(); ++k)
+        if (free_[k].bytes >= bytes && (best == free_.size() || free_[k].bytes < free_[best].bytes))
+            best = k;
+    if (best < free_.size()) {
+        const Chunk c = free_[best];
+        free_[best] = free_.back();
+        free_.pop_back();
+        return c;
+    }
+    const Chunk c = new_chunk(bytes, total_);
+    total_ += c.bytes;
+    return c;
+}
+
+void ChunkPool::trim() {
+    for (const Chunk &c : free_) (void)hipFree(c.p);
+    free_.clear();
+    total_ = 0;
+}
+
+Arena::~Arena() { release_all(); }
+
+void Arena::add_chunk(size_t bytes) {
+    chunks_.reserve(chunks_.size() + 1);
+    const Chunk c = temporary_ ? pool_->take(bytes) : new_chunk(bytes, total_);
+    chunks_.push_back(c);
+    total_ += c.bytes;
+    used_ = 0;
+}
+
+void Arena::reserve(size_t bytes) {
+    if (chunks_.empty() || chunks_.back().bytes - used_ < bytes) add_chunk(bytes);
+}
+
+void *Arena::alloc(size_t bytes) {
+    bytes = (std::max(bytes, size_t(16)) + 255) & ~size_t(255);
+    reserve(bytes);
+    void *p = chunks_.back().p + used_;
+    used_ += bytes;
+    return p;
+}
+
+void *Arena::alloc_own(size_t bytes) {
+    own_.reserve(own_.size() + 1);
+    own_.push_back(device_alloc(std::max(bytes, size_t(16))));
+    return own_.back();
+}
+
 void Arena::release(void *p) {
-    for (size_t k = 0; k < ptrs_.size(); ++k)
-        if (ptrs_[k] == p) {
+    for (size_t k = 0; k < own_.size(); ++k)
+        if (own_[k] == p) {
             (void)hipFree(p);
-            ptrs_[k] = ptrs_.back();
-            ptrs_.pop_back();
+            own_[k] = own_.back();
+            own_.pop_back();
             return;
         }
 }
 
 void Arena::release_all() {
-    for (void *p : ptrs_) (void)hipFree(p);
-    ptrs_.clear();
+    for (const Chunk &c : chunks_) {
+        if (temporary_) pool_->put(c);
+        else (void)hipFree(c.p);
+    }
+    chunks_.clear();
+    for (void *p : own_) (void)hipFree(p);
+    own_.clear();
+    used_ = total_ = 0;
 }
 
 }  // namespace ldu
@@ -181,6 +249,12 @@ int ldu_create(int32_t nCells, int64_t nFaces, const int32_t *owner, const int32
         hipStream_t st = S(hip_stream);
         HIP_CHECK(hipGetDevice(&h->device));
         noalloc_init(h->device);  // the static scratch's address on this device
+        h->arena.use_pool(&h->pool);
+        h->gamg_arena.use_pool(&h->pool);
+        // level 0's arrays: per cell five FP64 and four FP32 vectors, the row
+        // starts; per face its arrays and slots, and two slice entries of
+        // column, value, transposed value and 16-bit column
+        h->arena.reserve((size_t)nCells * 72 + (size_t)nFaces * 84 + (size_t(1) << 20));
         Level &L = h->L0;
         L.n = nCells;
         L.nf = nFaces;
@@ -210,6 +284,7 @@ int ldu_create(int32_t nCells, int64_t nFaces, const int32_t *owner, const int32
         h->d32 = h->arena.get<float>(nCells);
         build_level_sell(h, h->arena, L, true, st);
         HIP_CHECK(hipStreamSynchronize(st));
+        h->pool.trim();
         return LDU_OK;
     });
     if (rc != LDU_OK) {

@@ -384,7 +384,7 @@ static void coarse_values(ldu_t *h, Level &F, Level &C, hipStream_t st) {
 
 // record the fine faces each coarse value and diagonal sums (count, scan, fill)
 static void coarse_lists(Level &F, const Level &C, Arena &ar, hipStream_t st) {
-    Arena tmp;
+    Arena tmp(&ar);
     int64_t *cnt = tmp.get<int64_t>((size_t)C.nf + 1);
     F.cfStart = ar.get<int64_t>((size_t)C.nf + 1);
     if (C.nf > 0)
@@ -426,7 +426,7 @@ static void detect_singular(ldu_t *h, Level &L, hipStream_t st) {
 // member lists of F's aggregation (F.agg, F.nc): aggStart and aggCells in
 // ascending cell order
 static void agg_lists(Level &F, Arena &ar, hipStream_t st) {
-    Arena tmp;
+    Arena tmp(&ar);
     const int32_t n = F.n, nc = F.nc;
     const unsigned g = grid_n(n);
     int32_t *cnt = tmp.get<int32_t>(nc);
@@ -448,7 +448,7 @@ static void agg_lists(Level &F, Arena &ar, hipStream_t st) {
 static int32_t agglomerate(ldu_t *h, Level &F, int match_rounds, Arena &ar, Arena &lists_ar,
                            hipStream_t st) {
     const int32_t n = F.n;
-    Arena tmp;
+    Arena tmp(&ar);
     int32_t *partner = tmp.get<int32_t>(n);
     int32_t *pick = tmp.get<int32_t>(n);
     int32_t *join = tmp.get<int32_t>(n);
@@ -488,7 +488,7 @@ static void galerkin(ldu_t *h, Level &F, Level &C, Arena &ar, hipStream_t st);
 static int32_t agglomerate_passes(ldu_t *h, Level &F, int match_rounds, int passes, Arena &ar,
                                   hipStream_t st) {
     if (passes <= 1) return agglomerate(h, F, match_rounds, ar, ar, st);
-    Arena tmp;
+    Arena tmp(&ar);
     const int32_t nc = agglomerate(h, F, match_rounds, ar, tmp, st);
     if (nc <= 1) {
         agg_lists(F, ar, st);
@@ -506,7 +506,7 @@ static int32_t agglomerate_passes(ldu_t *h, Level &F, int match_rounds, int pass
 }
 
 static void galerkin(ldu_t *h, Level &F, Level &C, Arena &ar, hipStream_t st) {
-    Arena tmp;
+    Arena tmp(&ar);
     const int32_t nc = F.nc;
     int32_t *cnt = tmp.get<int32_t>(nc);
     int32_t *cptr = tmp.get<int32_t>((size_t)nc + 1);
@@ -585,6 +585,7 @@ void gamg_build(ldu_t *h, const ldu_gamg_opts &o, hipStream_t st) {
         q.scale_correction = 0;
         ensure_rop(h, q, st);
     }
+    h->pool.trim();
 }
 
 // new level-0 values: recompute every coarse matrix on the cached structure
@@ -2134,7 +2135,7 @@ static int csr_group(int64_t nnz, int32_t n) {
 // U's row bounds and arrays for level l (columns and values: k_up_fill)
 static void up_structure(ldu_t *h, size_t l, hipStream_t st) {
     Level &L = h->levels[l];
-    Arena tmp;
+    Arena tmp(&h->pool);
     Csr &U = L.Uc;
     U = Csr{};
     U.n = L.n;
@@ -2161,7 +2162,7 @@ static void rop_structure(ldu_t *h, size_t l, hipStream_t st) {
         L.r_ready = false;
         return;
     }
-    Arena tmp;
+    Arena tmp(&h->pool);
     int64_t *cnt = tmp.get<int64_t>(C.n);
     int64_t *tstart = tmp.get<int64_t>(C.n + 1);
     k_rop_count<<<grid_n(C.n), kBlock, 0, st>>>(C.n, L.aggStart, L.aggCells, L.A, cnt);
@@ -2287,6 +2288,7 @@ static void refresh_rop(ldu_t *h, hipStream_t st) {
 
 static VCtx make_ctx(ldu_t *h, const ldu_gamg_opts &o, bool tr, hipStream_t st) {
     ensure_rop(h, o, st);
+    h->pool.trim();
     if (o.smoother == LDU_SMOOTH_GS2 && o.gs_inner >= 3) {
         for (auto &L : h->levels) {
             if (!L.w) L.w = h->gamg_arena.get<double>(L.n);

@@ -440,7 +440,7 @@ void build_level_sell(ldu_t *h, Arena &ar, Level &L, bool validate, hipStream_t 
     const int32_t n = L.n;
     const int64_t nf = L.nf;
     const int64_t S = slices_of(n);
-    Arena tmp;
+    Arena tmp(&ar);
     if (validate) {
         HIP_CHECK(hipMemsetAsync(h->flag, 0, sizeof(int), st));
         if (nf > 0)
@@ -531,7 +531,7 @@ void build_level_sell(ldu_t *h, Arena &ar, Level &L, bool validate, hipStream_t 
 // lane order, slice starts and offset tables, and uninitialised col, val and
 // valT arrays of the total entry count (no diagonal)
 void build_sliced_rows(Sell &A, int32_t n, const int32_t *deg, Arena &ar, hipStream_t st) {
-    Arena tmp;
+    Arena tmp(&ar);
     const int64_t S = slices_of(n);
     A = Sell{};
     A.n = n;

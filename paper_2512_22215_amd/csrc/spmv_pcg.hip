@@ -79,7 +79,7 @@ void ensure_hist(ldu_t *h, int64_t entries) {
     if (h->hist) h->arena.release(h->hist);
     h->hist = nullptr;
     h->hist_cap = 0;
-    h->hist = h->arena.get<double>((size_t)entries);
+    h->hist = static_cast<double *>(h->arena.alloc_own(sizeof(double) * (size_t)entries));
     h->hist_cap = (int)entries;
 }
 
