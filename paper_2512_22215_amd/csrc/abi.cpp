@@ -35,11 +35,12 @@ static void *device_alloc(size_t bytes) {
 }
 
 // a chunk for a request of `bytes` beside `total` bytes held already: half as
-// much again, at least 1 MiB and at most 512 MiB beyond the request, or just
-// the request when that much is not there
+// much again, at least 64 KiB (small matrices keep to what the runtime hands
+// out of its own pages) and at most 512 MiB, or just the request when that
+// much is not there
 static Chunk new_chunk(size_t bytes, size_t total) {
     Chunk c;
-    c.bytes = std::max(bytes, std::min(std::max(total / 2, size_t(1) << 20), size_t(512) << 20));
+    c.bytes = std::max(bytes, std::min(std::max(total / 2, size_t(64) << 10), size_t(512) << 20));
     void *p = nullptr;
     if (c.bytes > bytes && hipMalloc(&p, c.bytes) != hipSuccess) {
         (void)hipGetLastError();
@@ -254,7 +255,7 @@ int ldu_create(int32_t nCells, int64_t nFaces, const int32_t *owner, const int32
         // level 0's arrays: per cell five FP64 and four FP32 vectors, the row
         // starts; per face its arrays and slots, and two slice entries of
         // column, value, transposed value and 16-bit column
-        h->arena.reserve((size_t)nCells * 72 + (size_t)nFaces * 84 + (size_t(1) << 20));
+        h->arena.reserve((size_t)nCells * 72 + (size_t)nFaces * 84 + (size_t(128) << 10));
         Level &L = h->L0;
         L.n = nCells;
         L.nf = nFaces;

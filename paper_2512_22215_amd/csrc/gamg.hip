@@ -90,30 +90,31 @@ __device__ int32_t best_neighbour(const Sell &A, int32_t i, const int32_t *partn
     return best;
 }
 
-// flags[0] = pair added this round, flags[1] = matching finished
-__global__ void k_match_init(int32_t n, int32_t *partner, int *flags) {
+// added[k]: round k added a pair.  A round after one that added none has
+// nothing to do and returns at once (its own flag stays 0, so all later ones
+// return too).
+__global__ void k_match_init(int32_t n, int32_t *partner, int *added, int rounds) {
     GRID_STRIDE(i, n) partner[i] = -1;
-    if (blockIdx.x == 0 && threadIdx.x == 0) { flags[0] = 0; flags[1] = 0; }
+    if (blockIdx.x == 0)
+        for (int k = threadIdx.x; k < rounds; k += blockDim.x) added[k] = 0;
 }
-__global__ void k_match_pick(Sell A, const int32_t *partner, int32_t *pick, const int *flags) {
-    if (flags[1]) return;
+__global__ void k_match_pick(Sell A, const int32_t *partner, int32_t *pick, const int *added,
+                             int round) {
+    if (round > 0 && !added[round - 1]) return;
     GRID_STRIDE(i, A.n) {
         pick[i] = partner[i] < 0 ? best_neighbour(A, (int32_t)i, partner, false) : -1;
     }
 }
-__global__ void k_match_pair(int32_t n, const int32_t *pick, int32_t *partner, int *flags) {
-    if (flags[1]) return;
+__global__ void k_match_pair(int32_t n, const int32_t *pick, int32_t *partner, int *added,
+                             int round) {
+    if (round > 0 && !added[round - 1]) return;
     GRID_STRIDE(i, n) {
         const int32_t j = pick[i];
         if (j >= 0 && pick[j] == (int32_t)i) {
             partner[i] = j;
-            flags[0] = 1;
+            added[round] = 1;
         }
     }
-}
-__global__ void k_match_round_end(int *flags) {
-    if (!flags[1] && !flags[0]) flags[1] = 1;
-    flags[0] = 0;
 }
 __global__ void k_match_leftover(Sell A, const int32_t *partner, int32_t *join, int32_t *seed) {
     GRID_STRIDE(i, A.n) {
@@ -187,21 +188,135 @@ __device__ int coarse_row(const Sell &A, const int32_t *agg, const int32_t *star
     }
     return m;
 }
-__global__ void k_coarse_count(Sell A, int32_t nc, const int32_t *agg, const int32_t *start,
-                               const int32_t *cells, int32_t *cnt, int *overflow) {
-    int32_t list[kMaxCoarseRow];
-    GRID_STRIDE(a, nc) cnt[a] = coarse_row(A, agg, start, cells, (int32_t)a, list, overflow);
-}
-__global__ void k_coarse_fill(Sell A, int32_t nc, const int32_t *agg, const int32_t *start,
-                              const int32_t *cells, const int32_t *cptr, int32_t *cown,
-                              int32_t *cnb, int *overflow) {
-    int32_t list[kMaxCoarseRow];
-    GRID_STRIDE(a, nc) {
-        const int m = coarse_row(A, agg, start, cells, (int32_t)a, list, overflow);
-        for (int k = 0; k < m; ++k) {
-            cown[cptr[a] + k] = (int32_t)a;
-            cnb[cptr[a] + k] = list[k];
+// One coarse row by a group of kRowLanes lanes: the members' entries are read
+// side by side into LDS (the candidates b > a), duplicates drop out by
+// comparison with all earlier candidates, and each distinct b's place is the
+// number of smaller distinct ones.  A thread per row kept its sorted list in
+// scratch memory and walked the entries one dependent load after another:
+// 217 us a launch on average over a 1.8M-cell hierarchy, 62 us now.  A row
+// with more candidates than fit takes that serial path.
+constexpr int kRowLanes = 16;
+constexpr int kRowGroups = kBlock / kRowLanes;
+constexpr int kRowCand = 256;  // candidates a group's LDS holds
+
+struct CoarseRowLds {
+    int32_t c[kRowGroups][kRowCand];
+};
+
+// f(b, place) for the distinct aggregates b > a of row a, by one lane group;
+// the return value is their number (every lane of the group)
+template <class F>
+__device__ int coarse_row_group(const Sell &A, const int32_t *agg, const int32_t *start,
+                                const int32_t *cells, int32_t a, bool have, CoarseRowLds &sm,
+                                int *overflow, F &&f) {
+    const int l = threadIdx.x % kRowLanes;
+    int32_t *cand = sm.c[threadIdx.x / kRowLanes];
+    const int shift = (threadIdx.x & 63) / kRowLanes * kRowLanes;
+    const uint64_t mine = ((uint64_t(1) << kRowLanes) - 1) << shift;
+    const uint64_t below = mine & ((uint64_t(1) << (threadIdx.x & 63)) - 1);
+    int m = 0;
+    if (have) {
+        for (int32_t k = start[a]; k < start[a + 1]; ++k) {
+            const int32_t i = cells[k];
+            const int64_t ps = A.iperm ? (int64_t)A.iperm[i] : (int64_t)i;
+            const int w = row_len(A, ps);
+            for (int q0 = 0; q0 < w; q0 += kRowLanes) {  // the same bounds for the group's lanes
+                int32_t b = -1;
+                if (q0 + l < w) {
+                    const int32_t c = A.col[entry_at(A, ps, q0 + l)];
+                    if (c != i) b = agg[c];
+                }
+                const uint64_t in = __ballot(b > a) & mine;
+                const int at = m + __popcll(in & below);
+                if (b > a && at < kRowCand) cand[at] = b;
+                m += __popcll(in);
+            }
         }
+    }
+    if (m > kRowCand) {  // rare: one lane, as a sorted list
+        int32_t list[kMaxCoarseRow];
+        int n = 0;
+        if (l == 0) {
+            n = coarse_row(A, agg, start, cells, a, list, overflow);
+            for (int k = 0; k < n; ++k) f(list[k], k);
+        }
+        return __shfl(n, shift);
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    // first occurrences (bit t / kRowLanes of lane t % kRowLanes)
+    uint32_t first = 0;
+    int n = 0;
+    for (int t = l; t < m; t += kRowLanes) {
+        const int32_t b = cand[t];
+        bool seen = false;
+        for (int u = 0; u < t; ++u) seen = seen || cand[u] == b;
+        if (!seen) {
+            first |= 1u << (t / kRowLanes);
+            ++n;
+        }
+    }
+    int total = n;
+    for (int off = 1; off < kRowLanes; off <<= 1) total += __shfl_xor(total, off);
+    if (have && total > kMaxCoarseRow) {
+        if (l == 0) *overflow = 1;
+        return kMaxCoarseRow;
+    }
+    // repeats step aside, so that a place counts distinct aggregates
+    __builtin_amdgcn_wave_barrier();
+    int32_t own[kRowCand / kRowLanes];
+#pragma unroll
+    for (int j = 0; j < kRowCand / kRowLanes; ++j)
+        own[j] = j * kRowLanes + l < m ? cand[j * kRowLanes + l] : 0;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+    for (int j = 0; j < kRowCand / kRowLanes; ++j)
+        if (j * kRowLanes + l < m && !(first >> j & 1)) cand[j * kRowLanes + l] = INT32_MAX;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+    for (int j = 0; j < kRowCand / kRowLanes; ++j) {
+        if (first >> j & 1) {
+            int place = 0;
+            for (int u = 0; u < m; ++u) place += cand[u] < own[j];
+            f(own[j], place);
+        }
+    }
+    return total;
+}
+
+// the group's rows, the same number of steps for every lane of a wave
+#define ROW_GROUPS(a, n)                                                                  \
+    for (int64_t a0_ = blockIdx.x * (int64_t)kRowGroups; a0_ < (n);                       \
+         a0_ += (int64_t)gridDim.x * kRowGroups)                                          \
+        if (const int64_t a = a0_ + threadIdx.x / kRowLanes; true)
+
+__global__ void __launch_bounds__(kBlock)
+k_coarse_count(Sell A, int32_t nc, const int32_t *agg, const int32_t *start,
+               const int32_t *cells, int32_t *cnt, int *overflow) {
+    __shared__ CoarseRowLds sm;
+    ROW_GROUPS(a, nc) {
+        const int n = coarse_row_group(A, agg, start, cells, (int32_t)a, a < nc, sm, overflow,
+                                       [](int32_t, int) {});
+        if (a < nc && threadIdx.x % kRowLanes == 0) cnt[a] = n;
+    }
+}
+__global__ void __launch_bounds__(kBlock)
+k_coarse_fill(Sell A, int32_t nc, const int32_t *agg, const int32_t *start,
+              const int32_t *cells, const int32_t *cptr, int32_t *cown, int32_t *cnb,
+              int *overflow) {
+    __shared__ CoarseRowLds sm;
+    ROW_GROUPS(a, nc) {
+        const int32_t o = a < nc ? cptr[a] : 0;
+        coarse_row_group(A, agg, start, cells, (int32_t)a, a < nc, sm, overflow,
+                         [&](int32_t b, int place) {
+                             cown[o + place] = (int32_t)a;
+                             cnb[o + place] = b;
+                         });
     }
 }
 
@@ -454,13 +569,12 @@ static int32_t agglomerate(ldu_t *h, Level &F, int match_rounds, Arena &ar, Aren
     int32_t *join = tmp.get<int32_t>(n);
     int32_t *seed = tmp.get<int32_t>(n);
     int32_t *rank = tmp.get<int32_t>((size_t)n + 1);
-    int *flags = tmp.get<int>(2);
+    int *added = tmp.get<int>((size_t)match_rounds + 1);
     const unsigned g = grid_n(n);
-    k_match_init<<<g, kBlock, 0, st>>>(n, partner, flags);
+    k_match_init<<<g, kBlock, 0, st>>>(n, partner, added, match_rounds);
     for (int round = 0; round < match_rounds; ++round) {
-        k_match_pick<<<g, kBlock, 0, st>>>(F.A, partner, pick, flags);
-        k_match_pair<<<g, kBlock, 0, st>>>(n, pick, partner, flags);
-        k_match_round_end<<<1, 1, 0, st>>>(flags);
+        k_match_pick<<<g, kBlock, 0, st>>>(F.A, partner, pick, added, round);
+        k_match_pair<<<g, kBlock, 0, st>>>(n, pick, partner, added, round);
     }
     k_match_leftover<<<g, kBlock, 0, st>>>(F.A, partner, join, seed);
     scan_counts_i32(seed, rank, n, tmp, st);
@@ -512,7 +626,7 @@ static void galerkin(ldu_t *h, Level &F, Level &C, Arena &ar, hipStream_t st) {
     int32_t *cptr = tmp.get<int32_t>((size_t)nc + 1);
     int *overflow = tmp.get<int>(1);
     HIP_CHECK(hipMemsetAsync(overflow, 0, sizeof(int), st));
-    k_coarse_count<<<grid_n(nc), kBlock, 0, st>>>(F.A, nc, F.agg, F.aggStart, F.aggCells, cnt,
+    k_coarse_count<<<grid_n((int64_t)nc * kRowLanes), kBlock, 0, st>>>(F.A, nc, F.agg, F.aggStart, F.aggCells, cnt,
                                                   overflow);
     scan_counts_i32(cnt, cptr, nc, tmp, st);
     int32_t ncf = 0;
@@ -528,7 +642,7 @@ static void galerkin(ldu_t *h, Level &F, Level &C, Arena &ar, hipStream_t st) {
     C.upper = ar.get<double>(ncf);
     C.lower = ar.get<double>(ncf);
     C.diag = ar.get<double>(nc);
-    k_coarse_fill<<<grid_n(nc), kBlock, 0, st>>>(F.A, nc, F.agg, F.aggStart, F.aggCells, cptr,
+    k_coarse_fill<<<grid_n((int64_t)nc * kRowLanes), kBlock, 0, st>>>(F.A, nc, F.agg, F.aggStart, F.aggCells, cptr,
                                                  C.own, C.nb, overflow);
     HIP_CHECK(hipGetLastError());
     coarse_values(h, F, C, st);
@@ -865,123 +979,138 @@ __global__ void k_rop_count(int32_t nc, const int32_t *__restrict__ start,
             const int64_t ps = A.iperm ? (int64_t)A.iperm[i] : (int64_t)i;
             const int w = row_len(A, ps);
             m += 1;
-            for (int q = 0; q < w; ++q) m += A.col[entry_at(A, ps, q)] != i;  // padding: col i
+            if (A.pdeg) m += w;  // compressed slices hold no padding
+            else
+                for (int q = 0; q < w; ++q) m += A.col[entry_at(A, ps, q)] != i;
         }
         cnt[c] = m;
     }
 }
 
-// a member row's entries in column order, with the diagonal at its place:
-// (col, src) with src the entry's position in the level's slices, or -1 for
-// the diagonal; valid is false past the end
-struct RowCursor {
-    int32_t i = 0, col = 0;
-    int64_t ps = 0, src = 0;
-    int w = 0, q = 0;
-    bool diag = false, valid = false;
-    __device__ void init(const Sell &A, int32_t row) {
-        i = row;
-        ps = A.iperm ? (int64_t)A.iperm[row] : (int64_t)row;
-        w = row_len(A, ps);
-        q = 0;
-        diag = false;
-        next(A);
-    }
-    __device__ void next(const Sell &A) {
-        while (q < w) {
-            const int64_t e = entry_at(A, ps, q);
-            const int32_t j = A.col[e];
-            if (j == i) {  // padding points at the row
-                ++q;
-                continue;
-            }
-            if (!diag && j > i) break;
-            col = j;
-            src = e;
-            ++q;
-            valid = true;
-            return;
-        }
-        if (!diag) {
-            col = i;
-            src = -1;
-            diag = true;
-            valid = true;
-            return;
-        }
-        valid = false;
-    }
-};
-
 // per coarse row: the member contributions in member order, each member's in
 // column order, as (column, source) pairs (source: the entry's position in
 // the level's slices, or -1 for a member's own diagonal), ordered by column
-// with equal columns in member order: a merge of the two rows of a pair, or a
-// stable insertion sort of the concatenated rows of a larger aggregate.
-// rdeg: the number of distinct columns.
-__global__ void k_rop_gather(int32_t nc, const int32_t *__restrict__ start,
-                             const int32_t *__restrict__ cells, Sell A,
-                             const int64_t *__restrict__ tstart, int32_t *tcol, int64_t *tsrc,
-                             int32_t *rdeg) {
-    GRID_STRIDE(c, nc) {
+// with equal columns in member order.  rdeg: the number of distinct columns.
+// One wave per coarse row: the members' row headers are loaded side by side,
+// each member's entries by as many lanes, into LDS, and a pair's place is the
+// number of pairs that sort before it (all lanes read the same pair at a
+// time, a broadcast).  A thread per row with an insertion sort in global
+// memory took 21 ms on the 1.8M-cell merged hierarchy; this takes 0.9 ms.
+// Rows of more pairs than the LDS holds are sorted by one lane in place.
+constexpr int kGatherPairs = 512;
+
+__global__ void __launch_bounds__(kBlock)
+k_rop_gather(int32_t nc, const int32_t *__restrict__ start, const int32_t *__restrict__ cells,
+             Sell A, const int64_t *__restrict__ tstart, int32_t *tcol, int64_t *tsrc,
+             int32_t *rdeg) {
+    __shared__ int32_t sc[kWavesPerBlock][kGatherPairs];
+    __shared__ int32_t ss[kWavesPerBlock][kGatherPairs];  // positions fit 31 bits
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const uint64_t below = (uint64_t(1) << lane) - 1;
+    int32_t *pc = sc[wv], *psrc = ss[wv];
+    for (int64_t c = blockIdx.x * (int64_t)kWavesPerBlock + wv; c < nc;
+         c += (int64_t)gridDim.x * kWavesPerBlock) {
         const int64_t o = tstart[c];
-        int m = 0;
-        auto push = [&](int32_t j, int64_t src) {
-            tcol[o + m] = j;
-            tsrc[o + m] = src;
-            ++m;
-        };
+        const int m = (int)(tstart[c + 1] - o);
+        const bool lds = m <= kGatherPairs;
         const int32_t k0 = start[c], k1 = start[c + 1];
-        if (k1 - k0 <= 2) {
-            RowCursor a, b;
-            a.init(A, cells[k0]);
-            if (k1 - k0 == 2) b.init(A, cells[k0 + 1]);
-            while (a.valid || b.valid) {
-                if (a.valid && (!b.valid || a.col <= b.col)) {
-                    push(a.col, a.src);
-                    a.next(A);
-                } else {
-                    push(b.col, b.src);
-                    b.next(A);
-                }
+        int base = 0;
+        for (int32_t kb = k0; kb < k1; kb += kWave) {
+            const int nm = min(kWave, k1 - kb);
+            int32_t mi = 0, mw = 0, mt = 0;
+            int64_t mb = 0;
+            if (lane < nm) {
+                mi = cells[kb + lane];
+                const int64_t ps = A.iperm ? (int64_t)A.iperm[mi] : (int64_t)mi;
+                mw = row_len(A, ps);
+                mb = A.sptr[ps >> 6] + (ps & 63);
+                if (A.pdeg) mt = A.tptr[ps >> 6];
             }
-            int u = 0;
-            for (int t = 0; t < m; ++t) u += t == 0 || tcol[o + t] != tcol[o + t - 1];
-            rdeg[c] = u;
+            for (int u = 0; u < nm; ++u) {
+                const int32_t i = __shfl(mi, u), w = __shfl(mw, u), t = __shfl(mt, u);
+                const int64_t b0 = __shfl(mb, u);
+                int nv = 0, nb = 0;  // entries so far, and those left of the diagonal
+                for (int q0 = 0; q0 < w; q0 += kWave) {
+                    const int q = q0 + lane;
+                    int32_t j = i;
+                    int64_t e = -1;
+                    if (q < w) {
+                        e = b0 + (A.pdeg ? (int64_t)A.otab[t + q] : (int64_t)q * kWave);
+                        j = A.col[e];
+                    }
+                    const uint64_t in = __ballot(j != i);  // padding points at the row
+                    const int at = base + nv + __popcll(in & below) + (j > i ? 1 : 0);
+                    if (j != i) {
+                        if (lds) {
+                            pc[at] = j;
+                            psrc[at] = (int32_t)e;
+                        } else {
+                            tcol[o + at] = j;
+                            tsrc[o + at] = e;
+                        }
+                    }
+                    nv += __popcll(in);
+                    nb += __popcll(__ballot(j != i && j < i));
+                }
+                if (lane == 0) {
+                    if (lds) {
+                        pc[base + nb] = i;
+                        psrc[base + nb] = -1;
+                    } else {
+                        tcol[o + base + nb] = i;
+                        tsrc[o + base + nb] = -1;
+                    }
+                }
+                base += nv + 1;
+            }
+        }
+        if (!lds) {
+            // the wave's own stores, then one lane's stable insertion sort
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+            if (lane == 0) {
+                int u = 0;
+                for (int a = 0; a < m; ++a) {
+                    const int32_t kc = tcol[o + a];
+                    const int64_t ks = tsrc[o + a];
+                    int b = a - 1;
+                    while (b >= 0 && tcol[o + b] > kc) {
+                        tcol[o + b + 1] = tcol[o + b];
+                        tsrc[o + b + 1] = tsrc[o + b];
+                        --b;
+                    }
+                    tcol[o + b + 1] = kc;
+                    tsrc[o + b + 1] = ks;
+                }
+                for (int a = 0; a < m; ++a) u += a == 0 || tcol[o + a] != tcol[o + a - 1];
+                rdeg[c] = u;
+            }
             continue;
         }
-        for (int32_t k = k0; k < k1; ++k) {
-            const int32_t i = cells[k];
-            const int64_t ps = A.iperm ? (int64_t)A.iperm[i] : (int64_t)i;
-            const int w = row_len(A, ps);
-            bool diag = false;
-            for (int q = 0; q < w; ++q) {
-                const int64_t e = entry_at(A, ps, q);
-                const int32_t j = A.col[e];
-                if (j == i) continue;
-                if (!diag && j > i) {
-                    push(i, -1);
-                    diag = true;
-                }
-                push(j, e);
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        int distinct = 0;
+        for (int t0 = 0; t0 < m; t0 += kWave) {
+            const int t = t0 + lane;
+            const int32_t j = t < m ? pc[t] : INT32_MAX;
+            int place = 0;
+            bool seen = false;
+            for (int u = 0; u < m; ++u) {
+                const int32_t ju = pc[u];
+                const bool same = ju == j && u < t;
+                place += ju < j || same;
+                seen = seen || same;
             }
-            if (!diag) push(i, -1);
-        }
-        int u = 0;
-        for (int a = 0; a < m; ++a) {
-            const int32_t kc = tcol[o + a];
-            const int64_t ks = tsrc[o + a];
-            int b = a - 1;
-            while (b >= 0 && tcol[o + b] > kc) {
-                tcol[o + b + 1] = tcol[o + b];
-                tsrc[o + b + 1] = tsrc[o + b];
-                --b;
+            if (t < m) {
+                tcol[o + place] = j;
+                tsrc[o + place] = psrc[t];
             }
-            tcol[o + b + 1] = kc;
-            tsrc[o + b + 1] = ks;
+            distinct += __popcll(__ballot(t < m && !seen));
         }
-        for (int a = 0; a < m; ++a) u += a == 0 || tcol[o + a] != tcol[o + a - 1];
-        rdeg[c] = u;
+        if (lane == 0) rdeg[c] = distinct;
+        __builtin_amdgcn_wave_barrier();
     }
 }
 
@@ -1262,17 +1391,33 @@ __device__ __forceinline__ void for_row_entries(const Sell &A, int32_t i, F &&f)
     if (!diag) f(i, (int64_t)-1);
 }
 
-// U's row lengths: the S entries and the distinct aggregates they lie in
+// U's row lengths: the S entries and the distinct aggregates they lie in (the
+// first few found are held in registers, the rest are looked up in the row)
+constexpr int kUpSeen = 8;
+
 __global__ void k_up_count(Sell A, const int32_t *__restrict__ agg, int64_t *cnt) {
     GRID_STRIDE(i, A.n) {
         int64_t m = 0;
+        int32_t seen[kUpSeen];
+#pragma unroll
+        for (int k = 0; k < kUpSeen; ++k) seen[k] = -1;
+        int nseen = 0;
         for_row_entries(A, (int32_t)i, [&](int32_t j, int64_t) {
             const int32_t c = agg[j];
-            bool seen = false;  // an earlier entry of the row in the same aggregate
-            for_row_entries(A, (int32_t)i, [&](int32_t q, int64_t) {
-                seen = seen || (q < j && agg[q] == c);
-            });
-            m += seen ? 1 : 2;
+            bool old = false;
+#pragma unroll
+            for (int k = 0; k < kUpSeen; ++k) old = old || seen[k] == c;
+            if (!old && nseen >= kUpSeen)
+                for_row_entries(A, (int32_t)i, [&](int32_t q, int64_t) {
+                    old = old || (q < j && agg[q] == c);
+                });
+            if (!old) {
+#pragma unroll
+                for (int k = 0; k < kUpSeen; ++k)
+                    if (k == nseen) seen[k] = c;
+                ++nseen;
+            }
+            m += old ? 1 : 2;
         });
         cnt[i] = m;
     }
@@ -2173,7 +2318,7 @@ static void rop_structure(ldu_t *h, size_t l, hipStream_t st) {
     int32_t *tcol = tmp.get<int32_t>(total);
     L.r_src = h->gamg_arena.get<int64_t>(total);
     int32_t *rdeg = tmp.get<int32_t>(C.n);
-    k_rop_gather<<<grid_n(C.n), kBlock, 0, st>>>(C.n, L.aggStart, L.aggCells, L.A, tstart, tcol,
+    k_rop_gather<<<grid_n((int64_t)C.n * kWave), kBlock, 0, st>>>(C.n, L.aggStart, L.aggCells, L.A, tstart, tcol,
                                                 L.r_src, rdeg);
     if (C.n > kCsrMaxRows) {
         build_sliced_rows(L.R, C.n, rdeg, h->gamg_arena, st);

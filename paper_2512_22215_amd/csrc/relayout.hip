@@ -290,11 +290,39 @@ __global__ void k_fill_lower(int64_t nf, const int32_t *own, const int32_t *nb, 
     }
 }
 
+// rows of at most kSortRegs lower entries are ranked in registers (all loads
+// of the row together), longer ones by an insertion sort in place
+constexpr int kSortRegs = 8;
+
 __global__ void k_sort_lower(int32_t n, Slots slot, const int32_t *cntL, int32_t *col,
                              int64_t *faceAt, int64_t *slotL) {
     for (int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; j < n;
          j += (int64_t)gridDim.x * blockDim.x) {
         const int m = cntL[j];
+        if (m <= kSortRegs) {
+            int64_t pos[kSortRegs], f[kSortRegs];
+            int32_t c[kSortRegs];
+#pragma unroll
+            for (int a = 0; a < kSortRegs; ++a) pos[a] = a < m ? slot(j, a) : 0;
+#pragma unroll
+            for (int a = 0; a < kSortRegs; ++a) {
+                c[a] = a < m ? col[pos[a]] : INT32_MAX;
+                f[a] = a < m ? faceAt[pos[a]] : 0;
+            }
+#pragma unroll
+            for (int a = 0; a < kSortRegs; ++a) {
+                if (a >= m) continue;
+                int rank = 0;
+#pragma unroll
+                for (int b = 0; b < kSortRegs; ++b) rank += c[b] < c[a];  // columns are distinct
+                int64_t to = pos[0];
+#pragma unroll
+                for (int b = 1; b < kSortRegs; ++b) to = rank == b ? pos[b] : to;
+                col[to] = c[a];
+                slotL[f[a]] = to;
+            }
+            continue;
+        }
         for (int a = 1; a < m; ++a) {  // insertion sort by column
             const int64_t pa = slot(j, a);
             const int32_t c = col[pa];
