@@ -269,7 +269,7 @@ int ldu_create(int32_t nCells, int64_t nFaces, const int32_t *owner, const int32
         copy_in(L.upper, upper, sizeof(double) * nFaces, st);
         copy_in(L.lower, lower, sizeof(double) * nFaces, st);
         copy_in(L.diag, diag, sizeof(double) * nCells, st);
-        h->dev = h->arena.get<DevScalars>(1);
+        h->dev = h->arena.get<DevScalars>(2);
         h->flag = h->arena.get<int>(1);
         h->partials = h->arena.get<double>(4 * (size_t)kMaxGrid);
         HIP_CHECK(hipHostMalloc((void **)&h->host, sizeof(DevScalars), hipHostMallocDefault));

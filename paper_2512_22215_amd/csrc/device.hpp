@@ -170,6 +170,61 @@ inline void launch_finalize(double *partials, int nblocks, DevScalars *ds, const
     k_finalize<K, M, Epi><<<1, kBlock, 0, st>>>(partials, nblocks, ds, epi);
 }
 
+// The same reduction without a launch of its own: the kernel that uses the
+// result sums the partials itself.  Every wave sums them all by itself when
+// there are few (no barrier; a wave's loads are in flight together), every
+// block when there are many.  The order depends only on the number of
+// partials, so all waves and blocks get the same bits.  A reduction of its
+// own takes about 4.5 us and a launch.
+constexpr int kWavePartials = 256;  // a wave sums up to this many by itself
+
+template <int K>
+__device__ __forceinline__ void sum_partials(const double *__restrict__ partials, int nblocks,
+                                             double (&v)[K]) {
+    if (nblocks <= kWavePartials) {
+        const int lane = threadIdx.x & 63;
+        double t[K][kWavePartials / kWave];
+#pragma unroll
+        for (int j = 0; j < kWavePartials / kWave; ++j)
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                const int b = j * kWave + lane;
+                t[k][j] = b < nblocks ? partials[k * kMaxGrid + b] : 0.0;
+            }
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            v[k] = t[k][0];
+#pragma unroll
+            for (int j = 1; j < kWavePartials / kWave; ++j) v[k] = v[k] + t[k][j];
+            v[k] = wave_sum(v[k]);
+        }
+        return;
+    }
+    __shared__ double total[K];
+    double t[K][kMaxGrid / kBlock];
+#pragma unroll
+    for (int j = 0; j < kMaxGrid / kBlock; ++j)
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const int b = j * kBlock + threadIdx.x;
+            t[k][j] = b < nblocks ? partials[k * kMaxGrid + b] : 0.0;
+        }
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        v[k] = t[k][0];
+#pragma unroll
+        for (int j = 1; j < kMaxGrid / kBlock; ++j) v[k] = v[k] + t[k][j];
+    }
+    block_reduce<K>(v);
+    if (threadIdx.x == 0) {
+#pragma unroll
+        for (int k = 0; k < K; ++k) total[k] = v[k];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < K; ++k) v[k] = total[k];
+}
+
 // Loads and stores of the level-0 vector streams.  NT: nontemporal, for
 // vectors too large to stay in the 256 MB Infinity Cache between kernels
 // (kStreamNtCells); below that the plain forms keep them there.

@@ -2672,7 +2672,7 @@ int pcg_gamg_fp64(ldu_t *h, const double *b, double *x, const ldu_pcg_opts &o, b
             if (hs.done != kRunning) break;
         }
         // the stopping iteration's x += alpha p (none when alpha itself failed)
-        launch_x_pending(h, x, n, S, G, st);
+        launch_x_pending(h, x, h->p, n, S, G, st);
         if (hs.done == kFailed) {
             status = hs.status;
             break;

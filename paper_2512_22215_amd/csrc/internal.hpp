@@ -64,6 +64,23 @@ constexpr int kCmpBatch = LDU_CMP_BATCH;  // compressed-slice row products: entr
 #define LDU_STREAM_NT_CELLS 12000000
 #endif
 constexpr int64_t kStreamNtCells = LDU_STREAM_NT_CELLS;
+// diagonal CG and PBiCG run an iteration as two kernels up to this many cells
+// (the product forms the new direction in its gathers), as three above.  CG,
+// two against three kernels: 32^3 2.87 and 3.50 ms, 48^3 4.79 and 5.73, 64^3
+// 9.03 and 8.72, 100^3 50.6 and 26.3; PBiCG: 32^3 1.33 and 1.37 ms, 64^3 2.68
+// and 2.39
+#ifndef LDU_FUSED_CG_CELLS
+#define LDU_FUSED_CG_CELLS 160000
+#endif
+constexpr int64_t kFusedCgCells = LDU_FUSED_CG_CELLS;
+constexpr int64_t kFusedBicgCells = 1 << 16;
+// blocks of the CG forms' vector updates, whose partials every block of the
+// next kernel reads (512, 1024 and 2048: 28.0, 26.3 and 27.5 ms for diagonal
+// CG at 100^3, 117.0, 108.9 and 109.4 ms at 150^3)
+#ifndef LDU_CG_BLOCKS
+#define LDU_CG_BLOCKS 1024
+#endif
+constexpr int kCgBlocks = LDU_CG_BLOCKS;
 constexpr int kMaxLevels = 64;
 constexpr int kMaxCoarseRow = 128; // widest coarse-level row the setup supports
 constexpr double kCoarsestTol = 1e-10;
@@ -324,11 +341,13 @@ struct ldu_t {
     ldu_gamg_opts gamg_opts{};
     bool f32_ready = false;          // FP32 copies of level values exist
     // solver buffers
-    double *r = nullptr, *p = nullptr, *q = nullptr, *z = nullptr;
+    double *r = nullptr, *p = nullptr, *q = nullptr;
+    double *z = nullptr, *p2 = nullptr;  // z = M^-1 r, and p's second buffer (two-kernel CG)
     double *rt = nullptr, *pt = nullptr, *qt = nullptr;  // PBiCG shadow vectors
+    double *zt = nullptr, *pt2 = nullptr;
     float *r32 = nullptr, *p32 = nullptr, *q32 = nullptr, *d32 = nullptr;
     double *partials = nullptr;      // [4 * kMaxGrid]
-    ldu::DevScalars *dev = nullptr;
+    ldu::DevScalars *dev = nullptr;  // [2]: the second for kernels that pass scalars on
     ldu::DevScalars *host = nullptr; // pinned mirror
     double *hist = nullptr;          // device residual history
     int hist_cap = 0;
@@ -403,8 +422,9 @@ void launch_pcg_q(ldu_t *h, const SellView<double> &A, const double *p, double *
 void set_done(ldu_t *h, int done, hipStream_t st);
 // epilogue after an r update whose partials hold ||r||^2 (and r.z)
 void launch_converge(ldu_t *h, int grid, bool with_beta, hipStream_t st);
-// x += alpha p (p: the handle's direction) if a stopped CG still owes it
-void launch_x_pending(ldu_t *h, double *x, int32_t n, int64_t S, int grid, hipStream_t st);
+// x += alpha p if a stopped CG still owes it
+void launch_x_pending(ldu_t *h, double *x, const double *p, int32_t n, int64_t S, int grid,
+                      hipStream_t st);
 
 // gamg.hip
 void gamg_build(ldu_t *h, const ldu_gamg_opts &o, hipStream_t st);

@@ -6,7 +6,7 @@
 // streams of columns and values, the x gather served from L2, and an
 // atomic-free row ownership (each row is summed by exactly one lane).
 //
-// PCG with the diagonal preconditioner (Appendix A) runs as three fused
+// PCG with the diagonal preconditioner (Appendix A) runs as two or three fused
 // kernels per iteration, with every scalar (rho, alpha, beta, residual) kept in
 // device memory and a device "done" flag that freezes the iteration at the
 // first iterate meeting the tolerance; the host only reads the scalars every
@@ -14,7 +14,9 @@
 // paper's executor does (Sec. 4.3, CUDA API statistics).
 #include "device.hpp"
 
+#include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 namespace ldu {
 
@@ -241,39 +243,18 @@ struct EpiAlpha {
     }
 };
 
-void launch_pcg_q(ldu_t *h, const SellView<double> &A, const double *p, double *q, int grid,
-                  hipStream_t st) {
-    if (A.pdeg) k_pcg_q<true><<<grid, kBlock, 0, st>>>(A, p, q, h->partials, h->dev);
+static void launch_product_dot(ldu_t *h, const SellView<double> &A, const double *p, double *q,
+                               int grid, const DevScalars *ds, hipStream_t st) {
+    if (A.pdeg) k_pcg_q<true><<<grid, kBlock, 0, st>>>(A, p, q, h->partials, ds);
     else if (A.n > kStreamNtCells)
-        k_pcg_q<false, true><<<grid, kBlock, 0, st>>>(A, p, q, h->partials, h->dev);
-    else k_pcg_q<false><<<grid, kBlock, 0, st>>>(A, p, q, h->partials, h->dev);
-    launch_finalize<1>(h->partials, grid, h->dev, EpiAlpha{}, st);
+        k_pcg_q<false, true><<<grid, kBlock, 0, st>>>(A, p, q, h->partials, ds);
+    else k_pcg_q<false><<<grid, kBlock, 0, st>>>(A, p, q, h->partials, ds);
 }
 
-// r -= alpha q; ||r||^2 and r.D^-1 r.  The iteration's x += alpha p waits
-// for the direction update, which reads p anyway (k_pcg_p), or, when the
-// solve stops in between, for k_x_pending: one read of p per iteration
-// instead of two.
-template <bool NT>
-__global__ void __launch_bounds__(kBlock)
-k_pcg_update(int32_t n, int64_t S, const double *__restrict__ D, double *__restrict__ r,
-             const double *__restrict__ q, int precond, double *partials,
-             const DevScalars *ds) {
-    if (ds->done) return;
-    const double alpha = ds->alpha;
-    const int lane = threadIdx.x & 63;
-    double acc[2] = {0.0, 0.0};
-    for_each_slice(S, [&](int64_t s) {
-        const int64_t i = s * kWave + lane;
-        if (i < n) {
-            const double ri = vld<NT>(r + i) - alpha * vld<NT>(q + i);
-            vst<NT>(r + i, ri);
-            const double zi = precond ? ri / vld<NT>(D + i) : ri;
-            acc[0] += ri * ri;
-            acc[1] += ri * zi;
-        }
-    });
-    block_partials<2>(acc, partials);
+void launch_pcg_q(ldu_t *h, const SellView<double> &A, const double *p, double *q, int grid,
+                  hipStream_t st) {
+    launch_product_dot(h, A, p, q, grid, h->dev, st);
+    launch_finalize<1>(h->partials, grid, h->dev, EpiAlpha{}, st);
 }
 
 // iteration count, residual history and convergence test after the x, r
@@ -300,7 +281,7 @@ struct EpiConverge {
         } else if (with_beta) {
             ds->beta = t[1] / ds->rho;
             ds->rho = t[1];
-            ds->x_pending = 0;  // k_pcg_p applies it next
+            ds->x_pending = 0;  // k_pg_p applies it next
         }
     }
 };
@@ -310,19 +291,250 @@ void launch_converge(ldu_t *h, int grid, bool with_beta, hipStream_t st) {
     else launch_finalize<1>(h->partials, grid, h->dev, EpiConverge{h->hist, h->hist_cap, 0}, st);
 }
 
-// x += alpha p (the iteration's solution update, deferred from
-// k_pcg_update); p = D^-1 r + beta p.  p keeps the default cache policy even
-// where the other vectors stream nontemporally (NT): the CG product gathers
-// it next (c4's diagonal PCG: 1.05 -> 1.02 s per right-hand side).
+// An iteration of diagonal CG is two or three kernels.  Scalars travel with
+// them: the direction update takes ||r||^2 and r.z (the
+// convergence test and beta) from the partials of the residual update and
+// passes dev[0] on to dev[1], the residual update takes p.q (alpha) from the
+// product's and passes dev[1] on to dev[0].  As separate one-block reductions
+// these two were 9 us of a 40 us iteration at 1M cells and two of five
+// launches of an 18 us one at 32,768; diagonal CG at 32^3 4.89 -> 2.87 ms, at
+// 100^3 29.5 -> 26.3 ms, at 150^3 115.2 -> 108.9 ms.  The partials of p.q are
+// the first kMaxGrid values, those of ||r||^2 and r.z the next two.
+//
+// Up to kFusedCgCells the product forms the new direction itself, also in its
+// gathers (p_j = z_j + beta p_j, the same bits as the owner stores), and the
+// iteration's x += alpha p rides along: the level's vectors sit in the caches
+// there, so a second gather costs less than a kernel.  Above, the direction
+// update is its own kernel.
+//
+// mode of a direction update: the partials hold the last residual update's
+// sums; the scalars are current (a reduction of its own ran for the host); the
+// first iteration, whose direction is z itself.
+enum { kStepReduce = 0, kStepReady = 1, kStepFirst = 2 };
+
+// what the solve of one handle passes to its step kernels
+struct StepHistory {
+    double *hist;
+    int hist_cap;
+};
+
+struct Step {
+    double alpha, beta;
+    bool go;  // false: the solve has stopped
+};
+
+// The residual update's sums (||r||^2 and r.z; PBiCG: z.rt), taken by every
+// thread of the kernel that follows: iteration count, history, convergence
+// test and beta, the same decisions in every thread.  Block 0's first thread
+// writes the scalars to `out`, which other blocks do not read (in place only
+// for a launch of one block).  Only the fields a thread needs are held in
+// registers: a copy of the struct went to scratch memory and cost every wave
+// several microseconds.
+template <bool BICG>
+__device__ __forceinline__ Step step_converge(int mode, const double *__restrict__ partials,
+                                              int nblocks, const DevScalars *in, DevScalars *out,
+                                              const StepHistory &h) {
+    const bool lead = blockIdx.x == 0 && threadIdx.x == 0;
+    const int done0 = in->done;
+    Step st{in->alpha, in->beta, done0 == 0};
+    if (done0 || mode != kStepReduce) {
+        if (lead && in != out) *out = *in;
+        return st;
+    }
+    const double rho = in->rho, bnorm = in->bnorm, tol = in->tol;
+    const int it = in->iters + 1, max_iter = in->max_iter;
+    double t[2];
+    sum_partials<2>(partials, nblocks, t);
+    const double res = sqrt(t[0]) / bnorm;
+    int done = kRunning, status = 0;
+    if (!isfinite(res)) {
+        done = kFailed;
+        status = LDU_ERR_NAN;
+    } else if (res <= tol) {
+        done = kConverged;
+    } else if (it >= max_iter) {
+        done = kMaxIter;
+    } else if (BICG && (!isfinite(t[1]) || fabs(t[1]) <= 1e-300)) {
+        done = kFailed;
+        status = LDU_ERR_BREAKDOWN;
+    }
+    st.go = done == kRunning;
+    st.beta = t[1] / rho;
+    if (lead) {
+        if (in != out) *out = *in;
+        out->iters = it;
+        out->rr = t[0];
+        out->res = res;
+        if (h.hist && it < h.hist_cap) h.hist[it] = res;
+        if (st.go) {
+            out->beta = st.beta;
+            out->rho = t[1];
+            out->x_pending = 0;  // the direction update applies it now
+        } else {
+            out->done = done;
+            if (done == kFailed) out->status = status;
+        }
+    }
+    return st;
+}
+
+// the product's p.q, taken the same way: alpha, or breakdown
+__device__ __forceinline__ Step step_alpha(const double *__restrict__ partials, int nblocks,
+                                           const DevScalars *in, DevScalars *out) {
+    const bool lead = blockIdx.x == 0 && threadIdx.x == 0;
+    const int done0 = in->done;
+    const double rho = in->rho;
+    if (done0) {
+        if (lead) *out = *in;
+        return {0.0, 0.0, false};
+    }
+    double t[1];
+    sum_partials<1>(partials, nblocks, t);
+    const double pq = t[0];
+    const bool go = isfinite(pq) && fabs(pq) > 1e-300;
+    const double alpha = rho / pq;
+    if (lead) {
+        *out = *in;
+        out->pq = pq;
+        if (go) {
+            out->alpha = alpha;
+            out->x_pending = 1;
+        } else {
+            out->status = LDU_ERR_BREAKDOWN;
+            out->done = kFailed;
+        }
+    }
+    return {alpha, 0.0, go};
+}
+
+// the convergence step for the host, which reads the scalars next
+template <bool BICG>
+__global__ void __launch_bounds__(kBlock)
+k_step_converge(const double *partials, int nblocks, DevScalars *ds, StepHistory h) {
+    step_converge<BICG>(kStepReduce, partials, nblocks, ds, ds, h);
+}
+
+// p_j = z_j + beta p_j
+struct NewDirection {
+    const double *z, *p;
+    double beta;
+    bool first;
+    __device__ __forceinline__ double operator()(int32_t j) const {
+        return first ? z[j] : z[j] + beta * p[j];
+    }
+};
+
+// x += alpha p (the last iteration's); p2 = z + beta p; q = A p2; p2.q
+template <bool CMP>
+__global__ void __launch_bounds__(kBlock)
+k_cg_pq(SellView<double> A, const double *__restrict__ z, const double *__restrict__ p,
+        double *__restrict__ p2, double *__restrict__ x, double *__restrict__ q,
+        double *partials, int nblocks, int mode, const DevScalars *__restrict__ in,
+        DevScalars *__restrict__ out, StepHistory hist) {
+    const int lane = threadIdx.x & 63;
+    const bool first = mode == kStepFirst;
+    Step s{};
+    double acc[1] = {0.0};
+    auto finish = [&](int32_t i, double pi, double pold, double qi) {
+        if (!first) x[i] = x[i] + s.alpha * pold;
+        p2[i] = pi;
+        q[i] = qi;
+        acc[0] += pi * qi;
+    };
+    if constexpr (CMP) {
+        s = step_converge<false>(mode, partials + kMaxGrid, nblocks, in, out, hist);
+        if (!s.go) return;
+        const NewDirection np{z, p, s.beta, first};
+        for_each_slice(A.nslices, [&](int64_t sl) {
+            const int64_t pos = sl * kWave + lane;
+            if (pos < A.n) {
+                const int32_t i = A.perm[pos];
+                const double pi = np(i);
+                double qi = A.diag[i] * pi;
+                cmp_entries<kCmpBatch>(A, sl, lane, np,
+                                       [&](int32_t, double v, double pv) { qi = qi + v * pv; });
+                finish(i, pi, first ? 0.0 : p[i], qi);
+            }
+        });
+    } else {
+        // a wave's slice is loaded, gathers included, before the scalars of
+        // the step are there: of this kernel's chain of round trips at small
+        // sizes (scalars, partials; slice start, entries, gathers) the two
+        // halves overlap
+        constexpr int B = 8;
+        const SliceWalkRange r = slice_walk_range(A.nslices, gridDim.x);
+        int32_t c[B], cb[B];
+        double v[B], zv[B], pv[B], di = 0.0, zi = 0.0, po = 0.0;
+        int w = 0;
+        auto load = [&](auto c16, int64_t sl, int k) {
+            constexpr bool C16 = decltype(c16)::value;
+            const PlainWalk<C16, double> pw(A, sl, lane);
+            w = pw.w;
+#pragma unroll
+            for (int u = 0; u < B; ++u)
+                if (k + u < w) pw.load(k + u, c[u], cb[u], v[u]);
+#pragma unroll
+            for (int u = 0; u < B; ++u)
+                if (k + u < w) {
+                    c[u] = PlainWalk<C16, double>::column(c[u], cb[u]);
+                    zv[u] = z[c[u]];
+                    if (!first) pv[u] = p[c[u]];
+                }
+        };
+        auto load_any = [&](int64_t sl, int k) {
+            if (A.c16) load(std::true_type{}, sl, k);
+            else load(std::false_type{}, sl, k);
+        };
+        auto load_row = [&](int64_t sl) {
+            const int64_t i = sl * kWave + lane;
+            if (i >= A.n) return;
+            di = A.diag[i];
+            zi = z[i];
+            if (!first) po = p[i];
+            load_any(sl, 0);
+        };
+        const int64_t step = r.Gx * kWavesPerBlock;
+        int64_t sl = r.lo + r.j * kWavesPerBlock + r.w;
+        if (sl < r.hi) load_row(sl);
+        s = step_converge<false>(mode, partials + kMaxGrid, nblocks, in, out, hist);
+        if (!s.go) return;
+        const double beta = s.beta;
+        for (; sl < r.hi; sl += step) {
+            const int64_t i = sl * kWave + lane;
+            if (i < A.n) {
+                const double pi = first ? zi : zi + beta * po;
+                double qi = di * pi;
+                for (int k = 0;;) {
+#pragma unroll
+                    for (int u = 0; u < B; ++u)
+                        if (k + u < w) qi = qi + v[u] * (first ? zv[u] : zv[u] + beta * pv[u]);
+                    k += B;
+                    if (k >= w) break;
+                    load_any(sl, k);
+                }
+                finish((int32_t)i, pi, po, qi);
+            }
+            if (sl + step < r.hi) load_row(sl + step);
+        }
+    }
+    block_partials<1>(acc, partials);
+}
+
+// x += alpha p (the last iteration's); p = z + beta p with z = D^-1 r.  p keeps
+// the default cache policy even where the other vectors stream nontemporally
+// (NT): the product gathers it next (c4's diagonal PCG: 1.05 -> 1.02 s per
+// right-hand side).
 template <bool NT>
 __global__ void __launch_bounds__(kBlock)
-k_pcg_p(int32_t n, int64_t S, const double *__restrict__ D, const double *__restrict__ r,
-        double *__restrict__ x, double *__restrict__ p, int precond, const DevScalars *ds) {
-    if (ds->done) return;
-    const double alpha = ds->alpha, beta = ds->beta;
+k_cg_p(int32_t n, int64_t S, const double *__restrict__ D, const double *__restrict__ r,
+       double *__restrict__ x, double *__restrict__ p, int precond, const double *partials,
+       int nblocks, int mode, const DevScalars *in, DevScalars *out, StepHistory hist) {
+    const Step s = step_converge<false>(mode, partials + kMaxGrid, nblocks, in, out, hist);
+    if (!s.go || mode == kStepFirst) return;  // the first direction is z, there already
+    const double alpha = s.alpha, beta = s.beta;
     const int lane = threadIdx.x & 63;
-    for_each_slice(S, [&](int64_t s) {
-        const int64_t i = s * kWave + lane;
+    for_each_slice(S, [&](int64_t sl) {
+        const int64_t i = sl * kWave + lane;
         if (i < n) {
             const double pi = p[i];
             vst<NT>(x + i, vld<NT>(x + i) + alpha * pi);
@@ -331,6 +543,34 @@ k_pcg_p(int32_t n, int64_t S, const double *__restrict__ D, const double *__rest
             p[i] = zi + beta * pi;
         }
     });
+}
+
+// r -= alpha q; ||r||^2 and r.D^-1 r; z = D^-1 r is stored for the two-kernel
+// form (z given).  The iteration's x += alpha p waits for the direction
+// update, which reads p anyway, or, when the solve stops in between, for
+// k_x_pending: one read of p per iteration instead of two.
+template <bool NT>
+__global__ void __launch_bounds__(kBlock)
+k_cg_r(int32_t n, int64_t S, const double *__restrict__ D, double *__restrict__ r,
+       const double *__restrict__ q, double *__restrict__ z, int precond, double *partials,
+       int nblocks, const DevScalars *in, DevScalars *out) {
+    const Step s = step_alpha(partials, nblocks, in, out);
+    if (!s.go) return;
+    const double alpha = s.alpha;
+    const int lane = threadIdx.x & 63;
+    double acc[2] = {0.0, 0.0};
+    for_each_slice(S, [&](int64_t sl) {
+        const int64_t i = sl * kWave + lane;
+        if (i < n) {
+            const double ri = vld<NT>(r + i) - alpha * vld<NT>(q + i);
+            vst<NT>(r + i, ri);
+            const double zi = precond ? ri / vld<NT>(D + i) : ri;
+            if (z) z[i] = zi;
+            acc[0] += ri * ri;
+            acc[1] += ri * zi;
+        }
+    });
+    block_partials<2>(acc, partials + kMaxGrid);
 }
 
 // x += alpha p when the stopped solve's last iteration still owes it: alpha
@@ -348,8 +588,9 @@ k_x_pending(int32_t n, int64_t S, double *__restrict__ x, const double *__restri
     });
 }
 
-void launch_x_pending(ldu_t *h, double *x, int32_t n, int64_t S, int grid, hipStream_t st) {
-    k_x_pending<<<grid, kBlock, 0, st>>>(n, S, x, h->p, h->dev);
+void launch_x_pending(ldu_t *h, double *x, const double *p, int32_t n, int64_t S, int grid,
+                      hipStream_t st) {
+    k_x_pending<<<grid, kBlock, 0, st>>>(n, S, x, p, h->dev);
     HIP_CHECK(hipGetLastError());
 }
 
@@ -384,10 +625,23 @@ int pcg_fp64(ldu_t *h, const double *b, double *x, const ldu_pcg_opts &o, bool t
     const int G = stream_grid_slices(S);
     const int precond = o.precond ? 1 : 0;
     const bool nt = n > kStreamNtCells;
+    // the allocation-free entry point has no room for the two-kernel form's
+    // vectors; the results are the same bit for bit
+    const bool fused = own_hist && n <= kFusedCgCells;
+    if (fused && !h->z) {
+        h->z = h->arena.get<double>(n);
+        h->p2 = h->arena.get<double>(n);
+    }
+    // products on plain slices: blocks past the cap would only add zeros; the
+    // residual update: see kCgBlocks
+    const int Gq = A.pdeg ? G : std::min(G, kPlainF64ProductBlocks);
+    const int Gr = std::min(G, kCgBlocks);
+    double *const p0 = fused ? h->z : h->p;  // where a (re)start's direction goes
+    double *const pbuf[2] = {fused ? h->p2 : h->p, h->p};  // direction after j iterations: j & 1
     if (own_hist) ensure_hist(h, (int64_t)o.max_iter + 2);
     fill_stats_common(stats);
     set_scalars_for_solve(h, o.rel_tol, o.max_iter, st);
-    launch_residual<true, false>(h, A, b, x, h->r, h->p, precond, kResPlain, true, st);
+    launch_residual<true, false>(h, A, b, x, h->r, p0, precond, kResPlain, true, st);
     read_scalars(h, st);
     DevScalars &hs = *h->host;
     if (stats) stats->initial_residual = hs.res;
@@ -406,36 +660,56 @@ int pcg_fp64(ldu_t *h, const double *b, double *x, const ldu_pcg_opts &o, bool t
     double res = hs.res;
     int status = LDU_OK;
     const int every = o.check_every > 0 ? o.check_every : 16;
+    const StepHistory conv{h->hist, h->hist_cap};
     while (res > o.rel_tol) {
+        const int iters0 = hs.iters;
+        int step = 0;  // iterations launched since the (re)start
         for (;;) {
-            for (int k = 0; k < every; ++k) {
-                launch_pcg_q(h, A, h->p, h->q, G, st);
+            for (int k = 0; k < every; ++k, ++step) {
+                const int mode = step == 0 ? kStepFirst : k == 0 ? kStepReady : kStepReduce;
+                if (fused) {
+                    const double *p = pbuf[step & 1];
+                    double *p2 = pbuf[(step + 1) & 1];
+                    if (A.pdeg)
+                        k_cg_pq<true><<<Gq, kBlock, 0, st>>>(A, h->z, p, p2, x, h->q, h->partials,
+                                                             Gr, mode, h->dev, h->dev + 1, conv);
+                    else
+                        k_cg_pq<false><<<Gq, kBlock, 0, st>>>(A, h->z, p, p2, x, h->q, h->partials,
+                                                              Gr, mode, h->dev, h->dev + 1, conv);
+                } else {
+                    const int Gp = mode == kStepFirst ? 1 : Gr;
+                    if (nt)
+                        k_cg_p<true><<<Gp, kBlock, 0, st>>>(n, S, A.diag, h->r, x, h->p, precond,
+                                                            h->partials, Gr, mode, h->dev,
+                                                            h->dev + 1, conv);
+                    else
+                        k_cg_p<false><<<Gp, kBlock, 0, st>>>(n, S, A.diag, h->r, x, h->p, precond,
+                                                             h->partials, Gr, mode, h->dev,
+                                                             h->dev + 1, conv);
+                    launch_product_dot(h, A, h->p, h->q, Gq, h->dev + 1, st);
+                }
+                double *z = fused ? h->z : nullptr;
                 if (nt)
-                    k_pcg_update<true><<<G, kBlock, 0, st>>>(n, S, A.diag, h->r, h->q, precond,
-                                                             h->partials, h->dev);
+                    k_cg_r<true><<<Gr, kBlock, 0, st>>>(n, S, A.diag, h->r, h->q, z, precond,
+                                                       h->partials, Gq, h->dev + 1, h->dev);
                 else
-                    k_pcg_update<false><<<G, kBlock, 0, st>>>(n, S, A.diag, h->r, h->q, precond,
-                                                              h->partials, h->dev);
-                launch_converge(h, G, true, st);
-                if (nt)
-                    k_pcg_p<true><<<G, kBlock, 0, st>>>(n, S, A.diag, h->r, x, h->p, precond,
-                                                        h->dev);
-                else
-                    k_pcg_p<false><<<G, kBlock, 0, st>>>(n, S, A.diag, h->r, x, h->p, precond,
-                                                         h->dev);
+                    k_cg_r<false><<<Gr, kBlock, 0, st>>>(n, S, A.diag, h->r, h->q, z, precond,
+                                                        h->partials, Gq, h->dev + 1, h->dev);
             }
+            // the last iteration's test for the host
+            k_step_converge<false><<<1, kBlock, 0, st>>>(h->partials + kMaxGrid, Gr, h->dev, conv);
             HIP_CHECK(hipGetLastError());
             read_scalars(h, st);
             if (hs.done != kRunning) break;
         }
         // the stopping iteration's x += alpha p (none when alpha itself failed)
-        launch_x_pending(h, x, n, S, G, st);
+        launch_x_pending(h, x, pbuf[(hs.iters - iters0) & 1], n, S, G, st);
         if (hs.done == kFailed) {
             status = hs.status;
             break;
         }
         // true residual; restart from it if the recursive one drifted
-        launch_residual<true, false>(h, A, b, x, h->r, h->p, precond, kResPlain, false, st);
+        launch_residual<true, false>(h, A, b, x, h->r, p0, precond, kResPlain, false, st);
         read_scalars(h, st);
         res = hs.res;
         if (!std::isfinite(res)) { status = LDU_ERR_NAN; break; }
@@ -476,104 +750,198 @@ k_bicg_start(int32_t n, int64_t S, const double *__restrict__ r, const double *_
     });
 }
 
-// q = A p and qt = A^T pt in one pass over the shared column structure
-// (valT holds A^T at the same positions); sigma = pt . q
-template <bool CMP>
+// the entries of one row for A and for A^T together (valT holds A^T at the
+// same positions), so that columns and slot bases are read once: q and qt add
+// v x(c) and vt xt(c) in column order
+template <bool C16, class X, class XT>
+__device__ __forceinline__ void plain_pair(const SellView<double> &A, const double *valT,
+                                           int64_t s, int lane, const X &x, const XT &xt,
+                                           double &q, double &qt) {
+    constexpr int B = 8;
+    const PlainWalk<C16, double> pw(A, s, lane);
+    const double *tp = valT + A.sptr[s] + lane;
+    for (int k = 0; k < pw.w; k += B) {
+        int32_t c[B], cb[B];
+        double v[B], vt[B], xv[B], xtv[B];
+#pragma unroll
+        for (int u = 0; u < B; ++u)
+            if (k + u < pw.w) {
+                pw.load(k + u, c[u], cb[u], v[u]);
+                vt[u] = __builtin_nontemporal_load(tp + (int64_t)(k + u) * kWave);
+            }
+#pragma unroll
+        for (int u = 0; u < B; ++u)
+            if (k + u < pw.w) {
+                c[u] = PlainWalk<C16, double>::column(c[u], cb[u]);
+                xv[u] = x(c[u]);
+                xtv[u] = xt(c[u]);
+            }
+#pragma unroll
+        for (int u = 0; u < B; ++u)
+            if (k + u < pw.w) {
+                q = q + v[u] * xv[u];
+                qt = qt + vt[u] * xtv[u];
+            }
+    }
+}
+
+template <bool CMP, class X, class XT>
+__device__ __forceinline__ void pair_entries(const SellView<double> &A, const double *valT,
+                                             int64_t s, int lane, const X &x, const XT &xt,
+                                             double &q, double &qt) {
+    if constexpr (!CMP) {
+        if (A.c16) plain_pair<true>(A, valT, s, lane, x, xt, q, qt);
+        else plain_pair<false>(A, valT, s, lane, x, xt, q, qt);
+    } else {
+        constexpr int B = 12;
+        const int64_t b0 = A.sptr[s];
+        const int w = A.pdeg[s * kWave + lane];
+        const int32_t *cp = A.col + b0 + lane;
+        const double *vp = A.val + b0 + lane, *tp = valT + b0 + lane;
+        SliceOffsets so;
+        for (int k = 0; k < w; k += B) {
+            int32_t c[B];
+            double v[B], vt[B], xv[B], xtv[B];
+#pragma unroll
+            for (int u = 0; u < B; ++u) {
+                const bool has = k + u < w;
+                const int64_t o = so.next(has);
+                if (has) {
+                    c[u] = __builtin_nontemporal_load(cp + o);
+                    v[u] = __builtin_nontemporal_load(vp + o);
+                    vt[u] = __builtin_nontemporal_load(tp + o);
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < B; ++u)
+                if (k + u < w) {
+                    xv[u] = x(c[u]);
+                    xtv[u] = xt(c[u]);
+                }
+#pragma unroll
+            for (int u = 0; u < B; ++u)
+                if (k + u < w) {
+                    q = q + v[u] * xv[u];
+                    qt = qt + vt[u] * xtv[u];
+                }
+        }
+    }
+}
+
+// An iteration in two or three kernels, as diagonal CG above: scalars from
+// the producers' partials, x += alpha p deferred to the direction update, and
+// up to kFusedBicgCells the product forms both new directions in its gathers.
+// q and qt come from one pass over the columns (two sweeps over the row read
+// them twice).  Convection-diffusion boxes: 32^3 1.92 -> 1.33 ms, 100^3 8.64
+// -> 7.53 ms.
+
+// p2 = z + beta p and pt2 = zt + beta pt (formed here when FUSED, else p2 and
+// pt2 are p and pt); x += alpha p (the last iteration's, FUSED only);
+// q = A p2, qt = A^T pt2; pt2.q
+template <bool CMP, bool FUSED>
 __global__ void __launch_bounds__(kBlock)
-k_bicg_q(SellView<double> A, const double *__restrict__ valT, const double *__restrict__ p,
-         const double *__restrict__ pt, double *__restrict__ q, double *__restrict__ qt,
-         double *partials, const DevScalars *ds) {
-    if (ds->done) return;
-    SellView<double> At = A;
-    At.val = valT;
+k_bicg_pq(SellView<double> A, const double *__restrict__ valT, const double *__restrict__ z,
+          const double *__restrict__ zt, const double *__restrict__ p,
+          const double *__restrict__ pt, double *__restrict__ p2, double *__restrict__ pt2,
+          double *__restrict__ x, double *__restrict__ q, double *__restrict__ qt,
+          double *partials, int nblocks, int mode, const DevScalars *in, DevScalars *out,
+          StepHistory hist) {
+    Step s{};
+    if constexpr (FUSED) {
+        s = step_converge<true>(mode, partials + kMaxGrid, nblocks, in, out, hist);
+        if (!s.go) return;
+    } else {
+        if (in->done) return;
+    }
+    const bool first = mode == kStepFirst;
+    const double alpha = FUSED ? s.alpha : 0.0, beta = FUSED ? s.beta : 0.0;
     const int lane = threadIdx.x & 63;
     double acc[1] = {0.0};
-    for_each_slice<product_cap<CMP, double>()>(A.nslices, [&](int64_t s) {
-        const int64_t pos = s * kWave + lane;
+    for_each_slice<product_cap<CMP, double>()>(A.nslices, [&](int64_t sl) {
+        const int64_t pos = sl * kWave + lane;
         if (pos < A.n) {
             const int32_t i = sv_row<CMP>(A, pos);
-            const double qi = sell_row<CMP>(A, s, lane, i, Direct<double>{p});
-            const double qti = sell_row<CMP>(At, s, lane, i, Direct<double>{pt});
+            const double di = A.diag[i];
+            double pi, pti, qi, qti;
+            if constexpr (FUSED) {
+                const NewDirection np{z, p, beta, first}, npt{zt, pt, beta, first};
+                pi = np(i);
+                pti = npt(i);
+                qi = di * pi;
+                qti = di * pti;
+                pair_entries<CMP>(A, valT, sl, lane, np, npt, qi, qti);
+                if (!first) x[i] = x[i] + alpha * p[i];
+                p2[i] = pi;
+                pt2[i] = pti;
+            } else {
+                pi = p[i];
+                pti = pt[i];
+                qi = di * pi;
+                qti = di * pti;
+                pair_entries<CMP>(A, valT, sl, lane, Direct<double>{p}, Direct<double>{pt}, qi,
+                                  qti);
+            }
             q[i] = qi;
             qt[i] = qti;
-            acc[0] += pt[i] * qi;
+            acc[0] += pti * qi;
         }
     });
     block_partials<1>(acc, partials);
 }
 
-// x += alpha p; r -= alpha q; rt -= alpha qt; ||r||^2 and (M^-1 r) . rt
+// x += alpha p (the last iteration's); p = M^-1 r + beta p; pt = M^-1 rt + beta pt
 __global__ void __launch_bounds__(kBlock)
-k_bicg_update(int32_t n, int64_t S, const double *__restrict__ D, double *__restrict__ x,
-              double *__restrict__ r, double *__restrict__ rt, const double *__restrict__ p,
-              const double *__restrict__ q, const double *__restrict__ qt, int precond,
-              double *partials, const DevScalars *ds) {
-    if (ds->done) return;
-    const double alpha = ds->alpha;
+k_bicg_p(int32_t n, int64_t S, const double *__restrict__ D, const double *__restrict__ r,
+         const double *__restrict__ rt, double *__restrict__ x, double *__restrict__ p,
+         double *__restrict__ pt, int precond, const double *partials, int nblocks, int mode,
+         const DevScalars *in, DevScalars *out, StepHistory hist) {
+    const Step s = step_converge<true>(mode, partials + kMaxGrid, nblocks, in, out, hist);
+    if (!s.go || mode == kStepFirst) return;  // the first directions are there already
+    const double alpha = s.alpha, beta = s.beta;
+    const int lane = threadIdx.x & 63;
+    for_each_slice(S, [&](int64_t sl) {
+        const int64_t i = sl * kWave + lane;
+        if (i < n) {
+            const double di = D[i], pi = p[i];
+            const double zi = precond ? r[i] / di : r[i];
+            const double zti = precond ? rt[i] / di : rt[i];
+            x[i] = x[i] + alpha * pi;
+            p[i] = zi + beta * pi;
+            pt[i] = zti + beta * pt[i];
+        }
+    });
+}
+
+// r -= alpha q; rt -= alpha qt; ||r||^2 and (M^-1 r) . rt; the preconditioned
+// residuals are stored for the two-kernel form (z given)
+__global__ void __launch_bounds__(kBlock)
+k_bicg_r(int32_t n, int64_t S, const double *__restrict__ D, double *__restrict__ r,
+         double *__restrict__ rt, const double *__restrict__ q, const double *__restrict__ qt,
+         double *__restrict__ z, double *__restrict__ zt, int precond, double *partials,
+         int nblocks, const DevScalars *in, DevScalars *out) {
+    const Step s = step_alpha(partials, nblocks, in, out);
+    if (!s.go) return;
+    const double alpha = s.alpha;
     const int lane = threadIdx.x & 63;
     double acc[2] = {0.0, 0.0};
-    for_each_slice(S, [&](int64_t s) {
-        const int64_t i = s * kWave + lane;
+    for_each_slice(S, [&](int64_t sl) {
+        const int64_t i = sl * kWave + lane;
         if (i < n) {
-            x[i] = x[i] + alpha * p[i];
+            const double di = precond ? D[i] : 1.0;
             const double ri = r[i] - alpha * q[i];
             const double rti = rt[i] - alpha * qt[i];
             r[i] = ri;
             rt[i] = rti;
-            const double zi = precond ? ri / D[i] : ri;
+            const double zi = precond ? ri / di : ri;
+            if (z) {
+                z[i] = zi;
+                zt[i] = precond ? rti / di : rti;
+            }
             acc[0] += ri * ri;
             acc[1] += zi * rti;
         }
     });
-    block_partials<2>(acc, partials);
-}
-
-// convergence as for CG, then beta, with breakdown when rho' vanishes
-struct EpiBicg {
-    double *hist;
-    int hist_cap;
-    __device__ bool active(const DevScalars *ds) const { return !ds->done; }
-    __device__ void operator()(const double *t, DevScalars *ds) const {
-        const int it = ds->iters + 1;
-        ds->iters = it;
-        ds->rr = t[0];
-        const double res = sqrt(t[0]) / ds->bnorm;
-        ds->res = res;
-        if (hist && it < hist_cap) hist[it] = res;
-        if (!isfinite(res)) {
-            ds->status = LDU_ERR_NAN;
-            ds->done = kFailed;
-        } else if (res <= ds->tol) {
-            ds->done = kConverged;
-        } else if (it >= ds->max_iter) {
-            ds->done = kMaxIter;
-        } else if (!isfinite(t[1]) || fabs(t[1]) <= 1e-300) {
-            ds->status = LDU_ERR_BREAKDOWN;
-            ds->done = kFailed;
-        } else {
-            ds->beta = t[1] / ds->rho;
-            ds->rho = t[1];
-        }
-    }
-};
-
-// p = M^-1 r + beta p; pt = M^-1 rt + beta pt
-__global__ void __launch_bounds__(kBlock)
-k_bicg_p(int32_t n, int64_t S, const double *__restrict__ D, const double *__restrict__ r,
-         const double *__restrict__ rt, double *__restrict__ p, double *__restrict__ pt,
-         int precond, const DevScalars *ds) {
-    if (ds->done) return;
-    const double beta = ds->beta;
-    const int lane = threadIdx.x & 63;
-    for_each_slice(S, [&](int64_t s) {
-        const int64_t i = s * kWave + lane;
-        if (i < n) {
-            const double zi = precond ? r[i] / D[i] : r[i];
-            const double zti = precond ? rt[i] / D[i] : rt[i];
-            p[i] = zi + beta * p[i];
-            pt[i] = zti + beta * pt[i];
-        }
-    });
+    block_partials<2>(acc, partials + kMaxGrid);
 }
 
 int pbicg_fp64(ldu_t *h, const double *b, double *x, const ldu_pcg_opts &o, bool tr,
@@ -590,10 +958,24 @@ int pbicg_fp64(ldu_t *h, const double *b, double *x, const ldu_pcg_opts &o, bool
         h->pt = h->arena.get<double>(n);
         h->qt = h->arena.get<double>(n);
     }
+    const bool fused = n <= kFusedBicgCells;
+    if (fused && !h->zt) {
+        if (!h->z) {
+            h->z = h->arena.get<double>(n);
+            h->p2 = h->arena.get<double>(n);
+        }
+        h->pt2 = h->arena.get<double>(n);
+        h->zt = h->arena.get<double>(n);
+    }
+    const int Gq = A.pdeg ? G : std::min(G, kPlainF64ProductBlocks);
+    const int Gr = std::min(G, kCgBlocks);
+    double *const p0 = fused ? h->z : h->p, *const pt0 = fused ? h->zt : h->pt;
+    double *const pbuf[2] = {fused ? h->p2 : h->p, h->p};
+    double *const ptbuf[2] = {fused ? h->pt2 : h->pt, h->pt};
     ensure_hist(h, (int64_t)o.max_iter + 2);
     fill_stats_common(stats);
     set_scalars_for_solve(h, o.rel_tol, o.max_iter, st);
-    launch_residual<true, false>(h, A, b, x, h->r, h->p, precond, kResPlain, true, st);
+    launch_residual<true, false>(h, A, b, x, h->r, p0, precond, kResPlain, true, st);
     read_scalars(h, st);
     DevScalars &hs = *h->host;
     if (stats) stats->initial_residual = hs.res;
@@ -612,33 +994,49 @@ int pbicg_fp64(ldu_t *h, const double *b, double *x, const ldu_pcg_opts &o, bool
     double res = hs.res;
     int status = LDU_OK;
     const int every = o.check_every > 0 ? o.check_every : 16;
+    const StepHistory conv{h->hist, h->hist_cap};
     while (res > o.rel_tol) {
-        k_bicg_start<<<G, kBlock, 0, st>>>(n, S, h->r, h->p, h->rt, h->pt, h->dev);
+        k_bicg_start<<<G, kBlock, 0, st>>>(n, S, h->r, p0, h->rt, pt0, h->dev);
+        const int iters0 = hs.iters;
+        int step = 0;  // iterations launched since the (re)start
         for (;;) {
-            for (int k = 0; k < every; ++k) {
-                if (A.pdeg)
-                    k_bicg_q<true><<<G, kBlock, 0, st>>>(A, valT, h->p, h->pt, h->q, h->qt,
-                                                         h->partials, h->dev);
-                else
-                    k_bicg_q<false><<<G, kBlock, 0, st>>>(A, valT, h->p, h->pt, h->q, h->qt,
-                                                          h->partials, h->dev);
-                launch_finalize<1>(h->partials, G, h->dev, EpiAlpha{}, st);
-                k_bicg_update<<<G, kBlock, 0, st>>>(n, S, A.diag, x, h->r, h->rt, h->p, h->q,
-                                                    h->qt, precond, h->partials, h->dev);
-                launch_finalize<2>(h->partials, G, h->dev, EpiBicg{h->hist, h->hist_cap}, st);
-                k_bicg_p<<<G, kBlock, 0, st>>>(n, S, A.diag, h->r, h->rt, h->p, h->pt, precond,
-                                               h->dev);
+            for (int k = 0; k < every; ++k, ++step) {
+                const int mode = step == 0 ? kStepFirst : k == 0 ? kStepReady : kStepReduce;
+                if (!fused)
+                    k_bicg_p<<<mode == kStepFirst ? 1 : Gr, kBlock, 0, st>>>(
+                        n, S, A.diag, h->r, h->rt, x, h->p, h->pt, precond, h->partials, Gr, mode,
+                        h->dev, h->dev + 1, conv);
+                auto product = [&](auto kernel, const DevScalars *in, DevScalars *out) {
+                    kernel<<<Gq, kBlock, 0, st>>>(A, valT, h->z, h->zt, pbuf[step & 1],
+                                                  ptbuf[step & 1], pbuf[(step + 1) & 1],
+                                                  ptbuf[(step + 1) & 1], x, h->q, h->qt,
+                                                  h->partials, Gr, mode, in, out, conv);
+                };
+                if (fused) {
+                    if (A.pdeg) product(k_bicg_pq<true, true>, h->dev, h->dev + 1);
+                    else product(k_bicg_pq<false, true>, h->dev, h->dev + 1);
+                } else {
+                    if (A.pdeg) product(k_bicg_pq<true, false>, h->dev + 1, nullptr);
+                    else product(k_bicg_pq<false, false>, h->dev + 1, nullptr);
+                }
+                k_bicg_r<<<Gr, kBlock, 0, st>>>(n, S, A.diag, h->r, h->rt, h->q, h->qt,
+                                               fused ? h->z : nullptr, fused ? h->zt : nullptr,
+                                               precond, h->partials, Gq, h->dev + 1, h->dev);
             }
+            // the last iteration's test for the host
+            k_step_converge<true><<<1, kBlock, 0, st>>>(h->partials + kMaxGrid, Gr, h->dev, conv);
             HIP_CHECK(hipGetLastError());
             read_scalars(h, st);
             if (hs.done != kRunning) break;
         }
+        // the stopping iteration's x += alpha p (none when alpha itself failed)
+        launch_x_pending(h, x, pbuf[(hs.iters - iters0) & 1], n, S, G, st);
         if (hs.done == kFailed) {
             status = hs.status;
             break;
         }
         // true residual; restart from it (new shadow) if the recursive one drifted
-        launch_residual<true, false>(h, A, b, x, h->r, h->p, precond, kResPlain, false, st);
+        launch_residual<true, false>(h, A, b, x, h->r, p0, precond, kResPlain, false, st);
         read_scalars(h, st);
         res = hs.res;
         if (!std::isfinite(res)) { status = LDU_ERR_NAN; break; }
