@@ -256,13 +256,6 @@ struct Direct {
     const T *x;
     __device__ __forceinline__ T operator()(int32_t j) const { return x[j]; }
 };
-template <typename T>
-struct ViaAgg {  // prolonged vector c_j = ec[agg[j]]
-    const T *ec;
-    const int32_t *agg;
-    __device__ __forceinline__ T operator()(int32_t j) const { return ec[agg[j]]; }
-};
-
 // Offsets of a compressed slice's entries.  Rows are sorted by length
 // within the slice (longest first), so the entries of column k are those of
 // the first cnt_k lanes, cnt_k = #{lanes with length > k}, stored after the

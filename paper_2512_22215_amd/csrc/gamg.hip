@@ -2491,6 +2491,10 @@ static int finish_status(const DevScalars &hs) {
     return LDU_OK;
 }
 
+// standalone cycles launched before the host looks at the residual again, at
+// most: each look costs an idle gap of 20-30 us
+constexpr int kCycleBatch = 8;
+
 int gamg_fp64(ldu_t *h, const double *b, double *x, const ldu_gamg_opts &o, bool tr,
               ldu_stats *stats, hipStream_t st) {
     Level &L = h->levels[0];
@@ -2516,10 +2520,14 @@ int gamg_fp64(ldu_t *h, const double *b, double *x, const ldu_gamg_opts &o, bool
         copy_history(h, stats, 1, st);
         return LDU_OK;
     }
+    const double res0 = hs.res;
     while (hs.done == kRunning) {
-        const double *e = vcycle<double>(c, 0, h->r);
-        k_add<<<G, kBlock, 0, st>>>(L.n, S, e, x, h->dev);
-        launch_residual_cycle(h, A, b, x, h->r, false, G, st);
+        const int batch = next_batch(res0, hs.res, hs.iters - 1, o.rel_tol, kCycleBatch);
+        for (int k = 0; k < batch; ++k) {
+            const double *e = vcycle<double>(c, 0, h->r);
+            k_add<<<G, kBlock, 0, st>>>(L.n, S, e, x, h->dev);
+            launch_residual_cycle(h, A, b, x, h->r, false, G, st);
+        }
         read_scalars(h, st);
     }
     const int status = finish_status(hs);
@@ -2669,8 +2677,11 @@ int pcg_gamg_fp64(ldu_t *h, const double *b, double *x, const ldu_pcg_opts &o, b
         const double *z = vcycle<double>(c, 0, h->r);
         k_pg_start<<<G, kBlock, 0, st>>>(n, S, h->r, z, h->p, h->partials, h->dev);
         launch_finalize<1>(h->partials, G, h->dev, EpiRho{}, st);
+        const double res0 = res;
+        const int iters0 = hs.iters;
         for (;;) {
-            for (int k = 0; k < every; ++k) {
+            const int batch = next_batch(res0, hs.res, hs.iters - iters0, o.rel_tol, every);
+            for (int k = 0; k < batch; ++k) {
                 launch_pcg_q(h, A, h->p, h->q, G, st);
                 if (nt)
                     k_pg_update<true><<<G, kBlock, 0, st>>>(n, S, h->r, h->q, h->partials,
@@ -2843,8 +2854,9 @@ int pcg_gamg_mixed(ldu_t *h, const double *b, double *x, const ldu_pcg_opts &o, 
         const float *z = vcycle<float>(c, 0, h->r32);
         k_mxg_p0<<<G, kBlock, 0, st>>>(n, S, h->r32, z, h->p32, h->partials, h->dev);
         launch_finalize<1>(h->partials, G, h->dev, EpiMxRho{}, st);
+        int batch = every;
         for (;;) {
-            for (int k = 0; k < every; ++k) {
+            for (int k = 0; k < batch; ++k) {
                 launch_mx_q(h, A32, G, st);
                 launch_mx_update_plain(h, n, S, G, st);
                 int blocks = 0;  // the last level-0 kernel may take r.z itself
@@ -2856,6 +2868,7 @@ int pcg_gamg_mixed(ldu_t *h, const double *b, double *x, const ldu_pcg_opts &o, 
             HIP_CHECK(hipGetLastError());
             read_scalars(h, st);
             if (hs.inner_done) break;
+            batch = next_batch(hs.r0, std::sqrt(hs.rr), hs.inner_iters, hs.inner_now * hs.r0, every);
         }
         inner_total += hs.inner_iters;
         launch_mx_refine(h, x, n, S, G, st);
@@ -2900,11 +2913,15 @@ int gamg_mixed(ldu_t *h, const double *b, double *x, const ldu_gamg_opts &o, boo
         copy_history(h, stats, 1, st);
         return LDU_OK;
     }
+    const double res0 = hs.res;
     while (hs.done == kRunning) {
-        k_cast_scaled<<<G, kBlock, 0, st>>>(L.n, S, h->r, L.r32, h->dev);
-        const float *d = vcycle<float>(c, 0, L.r32);
-        k_refine_add<<<G, kBlock, 0, st>>>(L.n, S, d, x, h->dev);
-        launch_residual_cycle(h, A, b, x, h->r, true, G, st);
+        const int batch = next_batch(res0, hs.res, hs.iters - 1, o.rel_tol, kCycleBatch);
+        for (int k = 0; k < batch; ++k) {
+            k_cast_scaled<<<G, kBlock, 0, st>>>(L.n, S, h->r, L.r32, h->dev);
+            const float *d = vcycle<float>(c, 0, L.r32);
+            k_refine_add<<<G, kBlock, 0, st>>>(L.n, S, d, x, h->dev);
+            launch_residual_cycle(h, A, b, x, h->r, true, G, st);
+        }
         read_scalars(h, st);
     }
     const int status = finish_status(hs);

@@ -72,6 +72,17 @@ void read_scalars(ldu_t *h, hipStream_t st) {
     HIP_CHECK(hipStreamSynchronize(st));
 }
 
+// Iterations to launch before the host looks at the scalars again: as many as
+// the solve still needs at the rate it has had from res0 to res in `steps`
+// iterations, at least one and at most `most`.  Iterations launched past the
+// last one return at once but still cost their launches (about 35 of 2.4 us
+// for CG + V-cycle on a million cells).
+int next_batch(double res0, double res, int steps, double tol, int most) {
+    if (steps < 1 || !(res > tol) || !(res < res0) || !(tol > 0.0)) return most;
+    const double left = std::log(res / tol) / std::log(res0 / res) * steps;
+    return left < most ? std::max(1, (int)std::ceil(left)) : most;
+}
+
 void ensure_hist(ldu_t *h, int64_t entries) {
     // the device history keeps the first kMaxHistory entries of a solve; the
     // epilogues write entry k only while k < hist_cap
@@ -1158,6 +1169,7 @@ struct EpiMxInner {
     __device__ void operator()(const double *t, DevScalars *ds) const {
         const int it = ds->inner_iters + 1;
         ds->inner_iters = it;
+        ds->rr = t[0];
         if (sqrt(t[0]) <= ds->inner_now * ds->r0 || it >= ds->inner_max) {
             ds->inner_done = 1;
         } else if (with_beta) {
