@@ -510,7 +510,8 @@ int ldu_level_layout(ldu_handle h, int level, int *compressed, int *col16) {
     if (level < 0) return fail(LDU_ERR_ARG, "bad level");
     if (level > 0 && !h->gamg_ready) return fail(LDU_ERR_STATE, "GAMG hierarchy not set up");
     if (level > 0 && level >= (int)h->levels.size()) return fail(LDU_ERR_ARG, "bad level");
-    const Level &L = level == 0 ? h->L0 : h->levels[level];
+    // the levels that solve; level 0's own numbering serves the products
+    const Level &L = level == 0 ? h->L0 : h->inner.empty() ? h->levels[level] : h->inner[level];
     if (compressed) *compressed = L.A.pdeg != nullptr;
     if (col16) *col16 = L.A.c16 != nullptr;
     return LDU_OK;
@@ -520,7 +521,7 @@ int ldu_level_downleg(ldu_handle h, int level, int *form, int *lanes) {
     if (!h) return fail(LDU_ERR_ARG, "NULL handle");
     if (!h->gamg_ready) return fail(LDU_ERR_STATE, "GAMG hierarchy not set up");
     if (level < 0 || level >= (int)h->levels.size()) return fail(LDU_ERR_ARG, "bad level");
-    const Level &L = h->levels[level];
+    const Level &L = h->inner.empty() ? h->levels[level] : h->inner[level];
     int f = 0, g = 0;
     if (L.ah) {
         f = 3;

@@ -463,16 +463,19 @@ __global__ void k_singular(Sell A, int *flag) {
 // ---------------------------------------------------------------- setup
 // FP32 copies of every level's values; level 0's live with the handle
 static void ensure_f32_levels(ldu_t *h, hipStream_t st) {
-    ensure_f32(h->L0, h->arena, st);
+    ensure_f32(h->L0, h->L0.src ? h->gamg_arena : h->arena, st);  // a renumbered one's: hierarchy
     h->levels[0].A = h->L0.A;
     for (size_t l = 1; l < h->levels.size(); ++l) ensure_f32(h->levels[l], h->gamg_arena, st);
 }
 
-static void alloc_work(Level &L, Arena &ar) {
-    L.r = ar.get<double>(L.n);
-    L.e = ar.get<double>(L.n);
-    L.e2 = ar.get<double>(L.n);
-    L.t = ar.get<double>(L.n);
+static void ensure_work(ldu_t *h) {
+    for (Level &L : h->levels) {
+        if (L.r) continue;
+        L.r = h->gamg_arena.get<double>(L.n);
+        L.e = h->gamg_arena.get<double>(L.n);
+        L.e2 = h->gamg_arena.get<double>(L.n);
+        L.t = h->gamg_arena.get<double>(L.n);
+    }
 }
 
 static void coarse_values(ldu_t *h, Level &F, Level &C, hipStream_t st) {
@@ -652,9 +655,144 @@ static void galerkin(ldu_t *h, Level &F, Level &C, Arena &ar, hipStream_t st) {
 static void ensure_rop(ldu_t *h, const ldu_gamg_opts &o, hipStream_t st);
 static void refresh_rop(ldu_t *h, hipStream_t st);
 
+// ---------------------------------------------------------------- inner numbering
+// On a mesh whose numbering scatters its neighbours every gather of a level-0
+// kernel pulls a cache line of its own from the Infinity Cache (128^3
+// shuffled: 190 us a sweep, 33 us renumbered by level sets), and the coarse
+// levels, numbered by seed cell, inherit it.  The solves then run on copies of
+// the large levels in an order that the hierarchy gives for nothing: the
+// members of an aggregate follow one another, aggregates in the order of their
+// own level, from the coarsest level down, so that cells close in the mesh are
+// close in memory at every scale.  Setup, exports, products and everything in
+// the caller's numbering keep the levels as they are: the hierarchy is the
+// same cell for cell, and a solve differs in the order of its sums only.
+// The two-stage Gauss-Seidel smoother, whose sweeps depend on the numbering,
+// solves on the original levels.  Standalone GAMG, default settings, 128^3
+// shuffled: 71.2 -> 33.1 ms (natural order: 32.8).  Renumbering the coarse
+// levels of meshes that are not scattered changed nothing (200^3 125.6 and
+// 125.2 ms, 128^3 mixed 29.5 and 29.6).
+struct NumberingScope {
+    ldu_t *h;
+    NumberingScope(ldu_t *hh, int smoother)
+        : h(!hh->inner.empty() && smoother == LDU_SMOOTH_JACOBI ? hh : nullptr) {
+        swap();
+    }
+    ~NumberingScope() { swap(); }
+    NumberingScope(const NumberingScope &) = delete;
+    NumberingScope &operator=(const NumberingScope &) = delete;
+    bool active() const { return h != nullptr; }
+
+private:
+    void swap() {
+        if (!h) return;
+        std::swap(h->L0, h->inner_L0);
+        std::swap(h->levels, h->inner);
+    }
+};
+
+// a solve's or a cycle's vectors in the inner numbering
+struct InnerVectors {
+    const double *in;  // b or r
+    double *out;       // x or e
+};
+static InnerVectors inner_vectors(ldu_t *h, bool active, const double *in, double *out,
+                                  bool read_out, hipStream_t st) {
+    if (!active) return {in, out};
+    gather_cells(in, h->inner_order, h->inner_b, h->L0.n, st);
+    if (read_out) gather_cells(out, h->inner_order, h->inner_x, h->L0.n, st);
+    return {h->inner_b, h->inner_x};
+}
+static void inner_result(ldu_t *h, bool active, double *out, hipStream_t st) {
+    if (!active) return;
+    scatter_cells(h->inner_x, h->inner_order, out, h->L0.n, st);
+    HIP_CHECK(hipStreamSynchronize(st));
+}
+
+__global__ void k_rn_identity(int32_t n, int32_t *place) {
+    GRID_STRIDE(i, n) place[i] = (int32_t)i;
+}
+// member counts in the coarse level's order
+__global__ void k_rn_counts(int32_t nc, const int32_t *start, const int32_t *cplace,
+                            int32_t *cnt) {
+    GRID_STRIDE(c, nc) cnt[cplace[c]] = start[c + 1] - start[c];
+}
+__global__ void k_rn_place(int32_t nc, const int32_t *start, const int32_t *cells,
+                           const int32_t *cplace, const int32_t *offs, int32_t *place) {
+    GRID_STRIDE(c, nc) {
+        const int32_t o = offs[cplace[c]];
+        for (int32_t k = start[c]; k < start[c + 1]; ++k) place[cells[k]] = o + (k - start[c]);
+    }
+}
+__global__ void k_rn_order(int32_t n, const int32_t *place, int32_t *order) {
+    GRID_STRIDE(i, n) order[place[i]] = (int32_t)i;
+}
+__global__ void k_rn_agg(int32_t n, const int32_t *order, const int32_t *agg,
+                         const int32_t *cplace, int32_t *out) {
+    GRID_STRIDE(p, n) {
+        const int32_t c = agg[order[p]];
+        out[p] = cplace ? cplace[c] : c;
+    }
+}
+
+static void renumber_levels(ldu_t *h, hipStream_t st) {
+    Arena &ar = h->gamg_arena;
+    Arena tmp(&ar);
+    const size_t nl = h->levels.size();
+    std::vector<int32_t *> place(nl);
+    for (size_t l = nl; l-- > 0;) {  // from the coarsest level down
+        const Level &L = h->levels[l];
+        place[l] = tmp.get<int32_t>(L.n);
+        if (l + 1 == nl) {
+            k_rn_identity<<<grid_n(L.n), kBlock, 0, st>>>(L.n, place[l]);
+            continue;
+        }
+        int32_t *cnt = tmp.get<int32_t>(L.nc), *offs = tmp.get<int32_t>((size_t)L.nc + 1);
+        k_rn_counts<<<grid_n(L.nc), kBlock, 0, st>>>(L.nc, L.aggStart, place[l + 1], cnt);
+        scan_counts_i32(cnt, offs, L.nc, tmp, st);
+        k_rn_place<<<grid_n(L.nc), kBlock, 0, st>>>(L.nc, L.aggStart, L.aggCells, place[l + 1],
+                                                    offs, place[l]);
+    }
+    HIP_CHECK(hipGetLastError());
+    for (size_t l = 0; l < nl; ++l) {
+        const Level &L = h->levels[l];
+        Level N = L;  // small levels share everything with the original
+        if (L.n > kRenumberRows) {
+            const bool coarse = l + 1 < nl && h->levels[l + 1].n > kRenumberRows;
+            int32_t *order = ar.get<int32_t>(L.n);
+            k_rn_order<<<grid_n(L.n), kBlock, 0, st>>>(L.n, place[l], order);
+            build_renumbered(L.A, L.nf, order, place[l], N, ar, st);
+            N.own = N.nb = nullptr;
+            N.upper = N.lower = nullptr;
+            if (l + 1 < nl) {
+                N.agg = ar.get<int32_t>(L.n);
+                k_rn_agg<<<grid_n(L.n), kBlock, 0, st>>>(L.n, order, L.agg,
+                                                         coarse ? place[l + 1] : nullptr, N.agg);
+                agg_lists(N, ar, st);
+            }
+        }
+        h->inner.push_back(N);
+    }
+    h->inner_L0 = h->inner[0];
+    h->inner_order = h->inner[0].order;
+    h->inner_b = ar.get<double>(h->L0.n);
+    h->inner_x = ar.get<double>(h->L0.n);
+    HIP_CHECK(hipStreamSynchronize(st));  // tmp is released after this point
+}
+
+// new values of the original levels into the inner ones
+static void refresh_inner(ldu_t *h, hipStream_t st) {
+    for (size_t l = 0; l < h->inner.size(); ++l) {
+        Level &N = h->inner[l];
+        if (N.src) renumbered_values(h->levels[l].A, N, st);
+        refresh_f32(N, st);
+        N.singular = h->levels[l].singular;
+    }
+}
+
 void gamg_build(ldu_t *h, const ldu_gamg_opts &o, hipStream_t st) {
     h->gamg_ready = false;
     h->levels.clear();
+    h->inner.clear();
     h->gamg_arena.release_all();
     Arena &ar = h->gamg_arena;
     h->levels.push_back(h->L0);
@@ -682,13 +820,16 @@ void gamg_build(ldu_t *h, const ldu_gamg_opts &o, hipStream_t st) {
         h->gamg_arena.release_all();
         throw Error(LDU_ERR_LIMIT, "coarsest GAMG level has more than 8192 cells; raise max_levels");
     }
-    for (auto &L : h->levels) alloc_work(L, ar);
+    detect_singular(h, h->levels.back(), st);
+    if (o.smoother == LDU_SMOOTH_JACOBI && h->levels.size() > 1 && scattered_numbering(h, st))
+        renumber_levels(h, st);
+    NumberingScope scope(h, o.smoother);  // work vectors and R of the levels that solve
+    ensure_work(h);
     h->coarse_work = ar.get<double>(5 * (size_t)h->levels.back().n);
     h->dic_dt = ar.get<double>(h->levels.back().n);
     h->dic_ready = false;
 
     if (h->L0.A.val32) ensure_f32_levels(h, st);
-    detect_singular(h, h->levels.back(), st);
     h->gamg_opts = o;
     h->gamg_ready = true;
     // a Jacobi cycle with one pre-sweep will run its down leg through R (the
@@ -714,7 +855,10 @@ void gamg_refresh_values(ldu_t *h, hipStream_t st) {
     }
     detect_singular(h, h->levels.back(), st);
     h->dic_ready = false;
+    refresh_inner(h, st);
     refresh_rop(h, st);
+    NumberingScope scope(h, LDU_SMOOTH_JACOBI);
+    if (scope.active()) refresh_rop(h, st);
 }
 
 // DIC pivots of the coarsest level (diagonal incomplete Cholesky; the paper's
@@ -2450,6 +2594,7 @@ static void refresh_rop(ldu_t *h, hipStream_t st) {
 }
 
 static VCtx make_ctx(ldu_t *h, const ldu_gamg_opts &o, bool tr, hipStream_t st) {
+    ensure_work(h);
     ensure_rop(h, o, st);
     h->pool.trim();
     if (o.smoother == LDU_SMOOTH_GS2 && o.gs_inner >= 3) {
@@ -2478,11 +2623,14 @@ static void fill_level_stats(ldu_t *h, ldu_stats *stats) {
 
 void gamg_vcycle64(ldu_t *h, const double *r, double *e, const ldu_gamg_opts &o, bool tr,
                    hipStream_t st) {
+    NumberingScope scope(h, o.smoother);
+    const InnerVectors v = inner_vectors(h, scope.active(), r, e, false, st);
     set_scalars_for_solve(h, 0.0, 0, st);
     VCtx c = make_ctx(h, o, tr, st);
-    double *res = vcycle<double>(c, 0, r);
-    HIP_CHECK(hipMemcpyAsync(e, res, sizeof(double) * h->L0.n, hipMemcpyDeviceToDevice, st));
+    double *res = vcycle<double>(c, 0, v.in);
+    HIP_CHECK(hipMemcpyAsync(v.out, res, sizeof(double) * h->L0.n, hipMemcpyDeviceToDevice, st));
     HIP_CHECK(hipStreamSynchronize(st));
+    inner_result(h, scope.active(), e, st);
 }
 
 static int finish_status(const DevScalars &hs) {
@@ -2495,7 +2643,7 @@ static int finish_status(const DevScalars &hs) {
 // most: each look costs an idle gap of 20-30 us
 constexpr int kCycleBatch = 8;
 
-int gamg_fp64(ldu_t *h, const double *b, double *x, const ldu_gamg_opts &o, bool tr,
+static int gamg_fp64_run(ldu_t *h, const double *b, double *x, const ldu_gamg_opts &o, bool tr,
               ldu_stats *stats, hipStream_t st) {
     Level &L = h->levels[0];
     const SellView<double> A = L.A.view(tr);
@@ -2640,7 +2788,7 @@ k_pg_p(int32_t n, int64_t S, double *__restrict__ x, const double *__restrict__ 
     });
 }
 
-int pcg_gamg_fp64(ldu_t *h, const double *b, double *x, const ldu_pcg_opts &o, bool tr,
+static int pcg_gamg_fp64_run(ldu_t *h, const double *b, double *x, const ldu_pcg_opts &o, bool tr,
                   ldu_stats *stats, hipStream_t st) {
     ldu_gamg_opts go = h->gamg_opts;
     go.scale_correction = 0;
@@ -2814,7 +2962,7 @@ struct EpiMxgStart {
     }
 };
 
-int pcg_gamg_mixed(ldu_t *h, const double *b, double *x, const ldu_pcg_opts &o, bool tr,
+static int pcg_gamg_mixed_run(ldu_t *h, const double *b, double *x, const ldu_pcg_opts &o, bool tr,
                    ldu_stats *stats, hipStream_t st) {
     ensure_work32(h, st);
     ldu_gamg_opts go = h->gamg_opts;
@@ -2886,7 +3034,7 @@ int pcg_gamg_mixed(ldu_t *h, const double *b, double *x, const ldu_pcg_opts &o, 
     return status;
 }
 
-int gamg_mixed(ldu_t *h, const double *b, double *x, const ldu_gamg_opts &o, bool tr,
+static int gamg_mixed_run(ldu_t *h, const double *b, double *x, const ldu_gamg_opts &o, bool tr,
                ldu_stats *stats, hipStream_t st) {
     ensure_work32(h, st);
     Level &L = h->levels[0];
@@ -2933,6 +3081,43 @@ int gamg_mixed(ldu_t *h, const double *b, double *x, const ldu_gamg_opts &o, boo
     }
     copy_history(h, stats, hs.iters + 1, st);
     return status;
+}
+
+// ---------------------------------------------------------------- entry points
+// the solves in the numbering that suits them
+template <class Run>
+static int in_numbering(ldu_t *h, int smoother, const double *b, double *x, hipStream_t st,
+                        Run &&run) {
+    NumberingScope scope(h, smoother);
+    const InnerVectors v = inner_vectors(h, scope.active(), b, x, true, st);
+    const int rc = run(v.in, v.out);
+    inner_result(h, scope.active(), x, st);
+    return rc;
+}
+
+int gamg_fp64(ldu_t *h, const double *b, double *x, const ldu_gamg_opts &o, bool tr,
+              ldu_stats *stats, hipStream_t st) {
+    return in_numbering(h, o.smoother, b, x, st, [&](const double *bi, double *xi) {
+        return gamg_fp64_run(h, bi, xi, o, tr, stats, st);
+    });
+}
+int gamg_mixed(ldu_t *h, const double *b, double *x, const ldu_gamg_opts &o, bool tr,
+               ldu_stats *stats, hipStream_t st) {
+    return in_numbering(h, o.smoother, b, x, st, [&](const double *bi, double *xi) {
+        return gamg_mixed_run(h, bi, xi, o, tr, stats, st);
+    });
+}
+int pcg_gamg_fp64(ldu_t *h, const double *b, double *x, const ldu_pcg_opts &o, bool tr,
+                  ldu_stats *stats, hipStream_t st) {
+    return in_numbering(h, h->gamg_opts.smoother, b, x, st, [&](const double *bi, double *xi) {
+        return pcg_gamg_fp64_run(h, bi, xi, o, tr, stats, st);
+    });
+}
+int pcg_gamg_mixed(ldu_t *h, const double *b, double *x, const ldu_pcg_opts &o, bool tr,
+                   ldu_stats *stats, hipStream_t st) {
+    return in_numbering(h, h->gamg_opts.smoother, b, x, st, [&](const double *bi, double *xi) {
+        return pcg_gamg_mixed_run(h, bi, xi, o, tr, stats, st);
+    });
 }
 
 }  // namespace ldu

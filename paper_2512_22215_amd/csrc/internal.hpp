@@ -81,6 +81,13 @@ constexpr int64_t kFusedBicgCells = 1 << 16;
 #define LDU_CG_BLOCKS 1024
 #endif
 constexpr int kCgBlocks = LDU_CG_BLOCKS;
+// meshes of at least this many cells are checked for a scattered numbering
+// when a hierarchy is built; levels above kRenumberRows are renumbered
+#ifndef LDU_RENUMBER_CELLS
+#define LDU_RENUMBER_CELLS 500000
+#endif
+constexpr int64_t kRenumberCells = LDU_RENUMBER_CELLS;
+constexpr int32_t kRenumberRows = 20000;
 constexpr int kMaxLevels = 64;
 constexpr int kMaxCoarseRow = 128; // widest coarse-level row the setup supports
 constexpr double kCoarsestTol = 1e-10;
@@ -286,6 +293,8 @@ struct Level {
     int64_t *ownStart = nullptr;          // [n+1]
     int64_t *slotU = nullptr, *slotL = nullptr;  // [nf] positions in the SELL arrays
     Sell A;
+    int32_t *src = nullptr;  // renumbered levels: source of each entry of A (-1: padding)
+    int32_t *order = nullptr;  // and the cell of each position
     // aggregation to the next level (absent on the coarsest level)
     int32_t nc = 0;
     int32_t *agg = nullptr, *aggStart = nullptr, *aggCells = nullptr;
@@ -336,6 +345,13 @@ struct ldu_t {
     ldu::Arena gamg_arena;       // hierarchy buffers (rebuilt by gamg_setup)
     ldu::Level L0;
     std::vector<ldu::Level> levels;  // levels[0] aliases L0's arrays when built
+    // the same levels renumbered for the solves, on a large mesh whose own
+    // numbering scatters its neighbours (gamg.hip, NumberingScope; empty on
+    // other meshes).  Small levels share their arrays with `levels`.
+    ldu::Level inner_L0;
+    std::vector<ldu::Level> inner;
+    int32_t *inner_order = nullptr;          // cell of each inner position, level 0
+    double *inner_b = nullptr, *inner_x = nullptr;
     bool gamg_ready = false;
     ldu_gamg_opts gamg_opts{};
     bool f32_ready = false;          // FP32 copies of level values exist
@@ -373,6 +389,18 @@ inline int64_t slices_of(int64_t n) { return (n + kWave - 1) / kWave; }
 // relayout.hip
 void build_level_sell(ldu_t *h, Arena &ar, Level &L, bool validate, hipStream_t st);
 void set_level_values(Level &L, hipStream_t st);   // face values -> SELL values
+// slices for n rows of the given lengths (device array), plain or compressed;
+// returns the number of slots
+int64_t layout_rows(Sell &A, int32_t n, const int32_t *deg, int64_t nnz, Arena &ar, Arena &tmp,
+                    hipStream_t st);
+// A with its rows in the order `order` (cell of each position; place: position
+// of each cell) and its columns renumbered, each row in ascending column order
+void build_renumbered(const Sell &A, int64_t nf, const int32_t *order, const int32_t *place,
+                      Level &out, Arena &ar, hipStream_t st);
+void renumbered_values(const Sell &A, Level &L, hipStream_t st);
+bool scattered_numbering(ldu_t *h, hipStream_t st);
+void gather_cells(const double *a, const int32_t *order, double *out, int64_t n, hipStream_t st);
+void scatter_cells(const double *a, const int32_t *order, double *out, int64_t n, hipStream_t st);
 void build_sliced_rows(Sell &A, int32_t n, const int32_t *deg, Arena &ar,
                        hipStream_t st);  // compressed slices for given row lengths
 void assemble_pressure(ldu_t *h, const double *gamma, const double *w, const double *mag_sf,

@@ -464,6 +464,51 @@ __global__ void k_to_f32(const double *a, float *b, int64_t n) {
         b[i] = (float)a[i];
 }
 
+// slices for rows of the given lengths (nnz_rows entries in all): plain ones,
+// or compressed where plain ones would pad by more than 3%
+int64_t layout_rows(Sell &A, int32_t n, const int32_t *deg, int64_t nnz_rows, Arena &ar, Arena &tmp,
+                    hipStream_t st) {
+    const int64_t S = slices_of(n);
+    int64_t *entries = tmp.get<int64_t>(S);
+    A.sptr = ar.get<int64_t>(S + 1);
+    k_slice_entries<<<grid_for(S), kBlock, 0, st>>>(n, S, deg, nullptr, entries);
+    exclusive_scan_i64(entries, A.sptr, S, tmp, st);
+    int64_t nnz = 0;
+    HIP_CHECK(hipMemcpyAsync(&nnz, A.sptr + S, sizeof(int64_t), hipMemcpyDeviceToHost, st));
+    HIP_CHECK(hipStreamSynchronize(st));
+    A.perm = A.iperm = A.pdeg = A.tptr = A.otab = nullptr;
+    int64_t nslots = nnz / kWave;  // plain slices: one slot per 64 entries
+    if (nnz * 100 > 103 * std::max<int64_t>(nnz_rows, kWave)) {
+        // rows of uneven length: compressed slices, lanes ordered by length
+        A.perm = ar.get<int32_t>(S * kWave);
+        A.iperm = ar.get<int32_t>(n);
+        A.pdeg = ar.get<int32_t>(S * kWave);
+        k_slice_sort<<<grid_for(S * kWave), kBlock, 0, st>>>(n, S, deg, A.perm, A.iperm,
+                                                             A.pdeg);
+        int32_t *tlen = tmp.get<int32_t>(S);
+        k_slice_sizes<<<grid_for(S), kBlock, 0, st>>>(S, A.pdeg, entries, tlen);
+        exclusive_scan_i64(entries, A.sptr, S, tmp, st);
+        A.tptr = ar.get<int32_t>(S + 1);
+        scan_counts_i32(tlen, A.tptr, S, tmp, st);
+        int32_t ntab = 0;
+        HIP_CHECK(hipMemcpyAsync(&ntab, A.tptr + S, sizeof(int32_t), hipMemcpyDeviceToHost,
+                                 st));
+        HIP_CHECK(hipMemcpyAsync(&nnz, A.sptr + S, sizeof(int64_t), hipMemcpyDeviceToHost,
+                                 st));
+        HIP_CHECK(hipStreamSynchronize(st));
+        A.otab = ar.get<int32_t>(ntab);
+        nslots = ntab;
+        k_slice_table<<<grid_for(S), kBlock, 0, st>>>(S, A.pdeg, A.tptr, A.otab);
+    }
+    A.n = n;
+    A.nslices = S;
+    A.nnz = nnz;
+    A.col = ar.get<int32_t>(nnz);
+    A.val = ar.get<double>(nnz);
+    A.valT = ar.get<double>(nnz);
+    return nslots;
+}
+
 void build_level_sell(ldu_t *h, Arena &ar, Level &L, bool validate, hipStream_t st) {
     const int32_t n = L.n;
     const int64_t nf = L.nf;
@@ -488,37 +533,8 @@ void build_level_sell(ldu_t *h, Arena &ar, Level &L, bool validate, hipStream_t 
     if (nf > 0) k_count_lower<<<grid_for(nf), kBlock, 0, st>>>(nf, L.nb, cntL);
     int32_t *deg = tmp.get<int32_t>(n);
     k_degree<<<grid_for(n), kBlock, 0, st>>>(n, L.ownStart, cntL, deg);
-    int64_t *entries = tmp.get<int64_t>(S);
-    L.A.sptr = ar.get<int64_t>(S + 1);
-    k_slice_entries<<<grid_for(S), kBlock, 0, st>>>(n, S, deg, nullptr, entries);
-    exclusive_scan_i64(entries, L.A.sptr, S, tmp, st);
-    int64_t nnz = 0;
-    HIP_CHECK(hipMemcpyAsync(&nnz, L.A.sptr + S, sizeof(int64_t), hipMemcpyDeviceToHost, st));
-    HIP_CHECK(hipStreamSynchronize(st));
-    L.A.perm = L.A.iperm = L.A.pdeg = L.A.tptr = L.A.otab = nullptr;
-    int64_t nslots = nnz / kWave;  // plain slices: one slot per 64 entries
-    if (nnz * 100 > 103 * std::max<int64_t>(2 * nf, kWave)) {
-        // rows of uneven length: compressed slices, lanes ordered by length
-        L.A.perm = ar.get<int32_t>(S * kWave);
-        L.A.iperm = ar.get<int32_t>(n);
-        L.A.pdeg = ar.get<int32_t>(S * kWave);
-        k_slice_sort<<<grid_for(S * kWave), kBlock, 0, st>>>(n, S, deg, L.A.perm, L.A.iperm,
-                                                             L.A.pdeg);
-        int32_t *tlen = tmp.get<int32_t>(S);
-        k_slice_sizes<<<grid_for(S), kBlock, 0, st>>>(S, L.A.pdeg, entries, tlen);
-        exclusive_scan_i64(entries, L.A.sptr, S, tmp, st);
-        L.A.tptr = ar.get<int32_t>(S + 1);
-        scan_counts_i32(tlen, L.A.tptr, S, tmp, st);
-        int32_t ntab = 0;
-        HIP_CHECK(hipMemcpyAsync(&ntab, L.A.tptr + S, sizeof(int32_t), hipMemcpyDeviceToHost,
-                                 st));
-        HIP_CHECK(hipMemcpyAsync(&nnz, L.A.sptr + S, sizeof(int64_t), hipMemcpyDeviceToHost,
-                                 st));
-        HIP_CHECK(hipStreamSynchronize(st));
-        L.A.otab = ar.get<int32_t>(ntab);
-        nslots = ntab;
-        k_slice_table<<<grid_for(S), kBlock, 0, st>>>(S, L.A.pdeg, L.A.tptr, L.A.otab);
-    }
+    const int64_t nslots = layout_rows(L.A, n, deg, 2 * nf, ar, tmp, st);
+    const int64_t nnz = L.A.nnz;
     {  // longest row, for kernels that stage a whole row
         int32_t *dmax = tmp.get<int32_t>(1);
         k_fill_i32<<<1, kBlock, 0, st>>>(dmax, 1, 0);
@@ -526,12 +542,6 @@ void build_level_sell(ldu_t *h, Arena &ar, Level &L, bool validate, hipStream_t 
         HIP_CHECK(hipMemcpyAsync(&L.max_row, dmax, sizeof(int32_t), hipMemcpyDeviceToHost, st));
         HIP_CHECK(hipStreamSynchronize(st));
     }
-    L.A.n = n;
-    L.A.nslices = S;
-    L.A.nnz = nnz;
-    L.A.col = ar.get<int32_t>(nnz);
-    L.A.val = ar.get<double>(nnz);
-    L.A.valT = ar.get<double>(nnz);
     L.A.diag = L.diag;
     L.slotU = ar.get<int64_t>(nf);
     L.slotL = ar.get<int64_t>(nf);
@@ -588,6 +598,164 @@ void build_sliced_rows(Sell &A, int32_t n, const int32_t *deg, Arena &ar, hipStr
     A.valT = ar.get<double>(nnz);
     HIP_CHECK(hipGetLastError());
     HIP_CHECK(hipStreamSynchronize(st));  // tmp is released after this point
+}
+
+// ---------------------------------------------------------------- renumbering
+// true row lengths (without padding) in the new order
+__global__ void k_rn_degree(Sell A, const int32_t *order, int32_t *deg) {
+    for (int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; p < A.n;
+         p += (int64_t)gridDim.x * blockDim.x) {
+        const int32_t i = order[p];
+        const int64_t ps = A.iperm ? (int64_t)A.iperm[i] : (int64_t)i;
+        const int w = row_len(A, ps);
+        int d = 0;
+        for (int k = 0; k < w; ++k) d += A.col[entry_at(A, ps, k)] != i;
+        deg[p] = d;
+    }
+}
+
+// columns and sources: an entry's place in its row is the number of entries
+// with a smaller new column.  Rows of at most kRnRegs stored entries are held
+// in registers (all loads of a row together), longer ones are read again for
+// every entry.
+constexpr int kRnRegs = 24;
+
+__global__ void __launch_bounds__(kBlock)
+k_rn_fill(Sell A, const int32_t *order, const int32_t *place, Slots slot, int32_t *col,
+          int32_t *src) {
+    for (int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; p < A.n;
+         p += (int64_t)gridDim.x * blockDim.x) {
+        const int32_t i = order[p];
+        const int64_t ps = A.iperm ? (int64_t)A.iperm[i] : (int64_t)i;
+        const int w = row_len(A, ps);
+        if (w <= kRnRegs) {
+            int32_t e[kRnRegs], c[kRnRegs];
+#pragma unroll
+            for (int k = 0; k < kRnRegs; ++k) e[k] = k < w ? (int32_t)entry_at(A, ps, k) : 0;
+#pragma unroll
+            for (int k = 0; k < kRnRegs; ++k) c[k] = k < w ? A.col[e[k]] : i;
+#pragma unroll
+            for (int k = 0; k < kRnRegs; ++k) c[k] = c[k] != i ? place[c[k]] : INT32_MAX;
+#pragma unroll
+            for (int k = 0; k < kRnRegs; ++k) {
+                if (c[k] == INT32_MAX) continue;  // padding
+                int rank = 0;
+#pragma unroll
+                for (int q = 0; q < kRnRegs; ++q) rank += c[q] < c[k];
+                const int64_t to = slot(p, rank);
+                col[to] = c[k];
+                src[to] = e[k];
+            }
+            continue;
+        }
+        for (int k = 0; k < w; ++k) {
+            const int64_t e = entry_at(A, ps, k);
+            const int32_t j = A.col[e];
+            if (j == i) continue;
+            const int32_t c = place[j];
+            int rank = 0;
+            for (int q = 0; q < w; ++q) {
+                const int32_t o = A.col[entry_at(A, ps, q)];
+                rank += o != i && place[o] < c;
+            }
+            const int64_t to = slot(p, rank);
+            col[to] = c;
+            src[to] = (int32_t)e;
+        }
+    }
+}
+
+__global__ void k_rn_values(int64_t nnz, const int32_t *__restrict__ src,
+                            const double *__restrict__ val, const double *__restrict__ valT,
+                            double *__restrict__ v, double *__restrict__ vT) {
+    for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < nnz;
+         e += (int64_t)gridDim.x * blockDim.x) {
+        const int32_t q = src[e];
+        v[e] = q >= 0 ? val[q] : 0.0;
+        vT[e] = q >= 0 ? valT[q] : 0.0;
+    }
+}
+
+__global__ void k_gather_cells(const double *__restrict__ a, const int32_t *__restrict__ order,
+                               double *__restrict__ out, int64_t n) {
+    for (int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; p < n;
+         p += (int64_t)gridDim.x * blockDim.x)
+        out[p] = a[order[p]];
+}
+__global__ void k_scatter_cells(const double *__restrict__ a, const int32_t *__restrict__ order,
+                                double *__restrict__ out, int64_t n) {
+    for (int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; p < n;
+         p += (int64_t)gridDim.x * blockDim.x)
+        out[order[p]] = a[p];
+}
+void gather_cells(const double *a, const int32_t *order, double *out, int64_t n, hipStream_t st) {
+    k_gather_cells<<<grid_for(n), kBlock, 0, st>>>(a, order, out, n);
+    HIP_CHECK(hipGetLastError());
+}
+void scatter_cells(const double *a, const int32_t *order, double *out, int64_t n,
+                   hipStream_t st) {
+    k_scatter_cells<<<grid_for(n), kBlock, 0, st>>>(a, order, out, n);
+    HIP_CHECK(hipGetLastError());
+}
+
+void renumbered_values(const Sell &A, Level &L, hipStream_t st) {
+    if (L.A.nnz > 0)
+        k_rn_values<<<grid_for(L.A.nnz), kBlock, 0, st>>>(L.A.nnz, L.src, A.val, A.valT, L.A.val,
+                                                          L.A.valT);
+    gather_cells(A.diag, L.order, L.A.diag, L.n, st);
+}
+
+void build_renumbered(const Sell &A, int64_t nf, const int32_t *order, const int32_t *place,
+                      Level &L, Arena &ar, hipStream_t st) {
+    Arena tmp(&ar);
+    const int32_t n = A.n;
+    int32_t *deg = tmp.get<int32_t>(n);
+    k_rn_degree<<<grid_for(n), kBlock, 0, st>>>(A, order, deg);
+    L.A = Sell{};
+    const int64_t nslots = layout_rows(L.A, n, deg, 2 * nf, ar, tmp, st);
+    L.diag = ar.get<double>(n);
+    L.A.diag = L.diag;
+    L.src = ar.get<int32_t>(L.A.nnz);
+    L.order = const_cast<int32_t *>(order);
+    if (L.A.nnz > 0) {
+        k_fill_i32<<<grid_for(L.A.nnz), kBlock, 0, st>>>(L.src, L.A.nnz, -1);
+        const Slots slot{L.A.sptr, L.A.iperm, L.A.tptr, L.A.otab};
+        k_rn_fill<<<grid_for(n), kBlock, 0, st>>>(A, order, place, slot, L.A.col, L.src);
+    }
+    if (!L.A.pdeg)
+        k_fill_pad<<<grid_for(L.A.nslices * kWave), kBlock, 0, st>>>(n, L.A.nslices, L.A.sptr, deg,
+                                                                    L.A.col, L.A.val, L.A.valT);
+    HIP_CHECK(hipGetLastError());
+    build_col16(L.A, nslots, ar, tmp, st);
+    renumbered_values(A, L, st);
+    HIP_CHECK(hipStreamSynchronize(st));  // tmp is released after this point
+}
+
+// sum of |column - row| over the faces
+__global__ void __launch_bounds__(kBlock)
+k_face_span(int64_t nf, const int32_t *__restrict__ own, const int32_t *__restrict__ nb,
+            unsigned long long *out) {
+    unsigned long long s = 0;
+    for (int64_t f = blockIdx.x * (int64_t)kBlock + threadIdx.x; f < nf;
+         f += (int64_t)gridDim.x * kBlock)
+        s += (unsigned long long)(nb[f] - own[f]);
+    for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off);
+    if ((threadIdx.x & 63) == 0) atomicAdd(out, s);
+}
+
+// whether a face joins cells that lie more than a sixteenth of the mesh apart
+// on average: a random numbering has a third, a mesh generator's or a
+// Cuthill-McKee numbering a few layers, n^(2/3)
+bool scattered_numbering(ldu_t *h, hipStream_t st) {
+    const Level &L = h->L0;
+    if (L.n < kRenumberCells || L.nf == 0) return false;
+    Arena tmp(&h->pool);
+    unsigned long long *sum = tmp.get<unsigned long long>(1), host = 0;
+    k_fill_i32<<<1, kBlock, 0, st>>>(reinterpret_cast<int32_t *>(sum), 2, 0);
+    k_face_span<<<std::min(grid_for(L.nf), 2048u), kBlock, 0, st>>>(L.nf, L.own, L.nb, sum);
+    HIP_CHECK(hipMemcpyAsync(&host, sum, sizeof(host), hipMemcpyDeviceToHost, st));
+    HIP_CHECK(hipStreamSynchronize(st));
+    return (double)host > (double)L.nf * (double)L.n / 16.0;
 }
 
 void set_level_values(Level &L, hipStream_t st) {
