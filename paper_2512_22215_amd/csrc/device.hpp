@@ -225,6 +225,145 @@ __device__ __forceinline__ void sum_partials(const double *__restrict__ partials
     for (int k = 0; k < K; ++k) v[k] = total[k];
 }
 
+// mode of a direction update: the partials hold the last residual update's
+// sums; the scalars are current (a reduction of its own ran for the host); the
+// first iteration, whose direction is z itself.
+enum { kStepReduce = 0, kStepReady = 1, kStepFirst = 2 };
+
+struct Step {
+    double alpha, beta;
+    bool go;  // false: the solve has stopped
+};
+
+// the product's p.q, taken by every thread of the residual update that
+// follows: alpha, or breakdown.  Block 0's first thread passes the scalars on
+// from `in` to `out`, which no other block reads
+__device__ __forceinline__ Step step_alpha(const double *__restrict__ partials, int nblocks,
+                                           const DevScalars *in, DevScalars *out) {
+    const bool lead = blockIdx.x == 0 && threadIdx.x == 0;
+    const int done0 = in->done;
+    const double rho = in->rho;
+    if (done0) {
+        if (lead) *out = *in;
+        return {0.0, 0.0, false};
+    }
+    double t[1];
+    sum_partials<1>(partials, nblocks, t);
+    const double pq = t[0];
+    const bool go = isfinite(pq) && fabs(pq) > 1e-300;
+    const double alpha = rho / pq;
+    if (lead) {
+        *out = *in;
+        out->pq = pq;
+        if (go) {
+            out->alpha = alpha;
+            out->x_pending = 1;
+        } else {
+            out->status = LDU_ERR_BREAKDOWN;
+            out->done = kFailed;
+        }
+    }
+    return {alpha, 0.0, go};
+}
+
+// r.z after a V-cycle, taken the same way by the direction update: beta
+__device__ __forceinline__ Step step_beta(int mode, const double *__restrict__ partials,
+                                          int nblocks, const DevScalars *in, DevScalars *out) {
+    const bool lead = blockIdx.x == 0 && threadIdx.x == 0;
+    const int done0 = in->done;
+    Step st{in->alpha, in->beta, done0 == 0};
+    if (done0 || mode != kStepReduce) {
+        if (lead) *out = *in;
+        return st;
+    }
+    const double rho = in->rho;
+    double t[1];
+    sum_partials<1>(partials, nblocks, t);
+    st.beta = t[0] / rho;
+    if (lead) {
+        *out = *in;
+        out->beta = st.beta;
+        out->rho = t[0];
+        out->x_pending = 0;  // the direction update applies it now
+    }
+    return st;
+}
+
+// the same steps of a mixed solve's inner CG
+__device__ __forceinline__ Step step_mx_alpha(const double *__restrict__ partials, int nblocks,
+                                              const DevScalars *in, DevScalars *out) {
+    const bool lead = blockIdx.x == 0 && threadIdx.x == 0;
+    const bool stop = vc_skip(in);
+    const double rho = in->rho;
+    if (stop) {
+        if (lead) *out = *in;
+        return {0.0, 0.0, false};
+    }
+    double t[1];
+    sum_partials<1>(partials, nblocks, t);
+    const bool go = isfinite(t[0]) && fabs(t[0]) > 1e-300;
+    const double alpha = rho / t[0];
+    if (lead) {
+        *out = *in;
+        if (go) out->alpha = alpha;
+        else out->inner_done = 1;
+    }
+    return {alpha, 0.0, go};
+}
+
+__device__ __forceinline__ Step step_mx_beta(int mode, const double *__restrict__ partials,
+                                             int nblocks, const DevScalars *in, DevScalars *out) {
+    const bool lead = blockIdx.x == 0 && threadIdx.x == 0;
+    const bool stop = vc_skip(in);
+    Step st{0.0, in->beta, !stop};
+    if (stop || mode != kStepReduce) {
+        if (lead) *out = *in;
+        return st;
+    }
+    const double rho = in->rho;
+    double t[1];
+    sum_partials<1>(partials, nblocks, t);
+    st.beta = t[0] / rho;
+    if (lead) {
+        *out = *in;
+        out->beta = st.beta;
+        out->rho = t[0];
+    }
+    return st;
+}
+
+// ||r||^2 and r.z of the diagonal form: the inner stop test and beta (in place
+// only for a launch of one block)
+__device__ __forceinline__ Step step_mx_inner(int mode, const double *__restrict__ partials,
+                                              int nblocks, const DevScalars *in,
+                                              DevScalars *out) {
+    const bool lead = blockIdx.x == 0 && threadIdx.x == 0;
+    const bool stop = vc_skip(in);
+    Step st{0.0, in->beta, !stop};
+    if (stop || mode != kStepReduce) {
+        if (lead && in != out) *out = *in;
+        return st;
+    }
+    const double rho = in->rho, limit = in->inner_now * in->r0;
+    const int it = in->inner_iters + 1, most = in->inner_max;
+    double t[2];
+    sum_partials<2>(partials, nblocks, t);
+    st.go = !(sqrt(t[0]) <= limit || it >= most);
+    st.beta = t[1] / rho;
+    if (lead) {
+        if (in != out) *out = *in;
+        out->inner_iters = it;
+        out->rr = t[0];
+        if (st.go) {
+            out->beta = st.beta;
+            out->rho = t[1];
+        } else {
+            out->inner_done = 1;
+        }
+    }
+    return st;
+}
+
 // Loads and stores of the level-0 vector streams.  NT: nontemporal, for
 // vectors too large to stay in the 256 MB Infinity Cache between kernels
 // (kStreamNtCells); below that the plain forms keep them there.

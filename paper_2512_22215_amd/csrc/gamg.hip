@@ -2404,10 +2404,13 @@ static T *vcycle(const VCtx &c, size_t l, const T *r, const T *rdot = nullptr,
         if (gs) {  // backward sweeps: the V-cycle stays symmetric
             gs_sweep<T>(A, r, e, t, e2, w1, false, true, c.o->gs_inner, h->dev, G, st);
         } else {  // the last sweep may take the caller's dot product and correction
+            // with a dot product, blocks past the products' cap would only add zeros
+            const int Gs = last && rdot && !A.pdeg && sizeof(T) == sizeof(double)
+                               ? std::min(G, kPlainF64ProductBlocks) : G;
             launch_jacobi<T>(A, r, e, e2, omega, last ? rdot : nullptr, h->partials,
-                             last ? fc : FineCorr<T>{}, h->dev, G, st);
+                             last ? fc : FineCorr<T>{}, h->dev, Gs, st);
             std::swap(e, e2);
-            if (last && rdot && dotted) *dotted = G;
+            if (last && rdot && dotted) *dotted = Gs;
             if (last && fc.e && corrected) *corrected = true;
         }
     }
@@ -2726,9 +2729,10 @@ struct EpiRho {
 template <bool NT>
 __global__ void __launch_bounds__(kBlock)
 k_pg_update(int32_t n, int64_t S, double *__restrict__ r, const double *__restrict__ q,
-            double *partials, const DevScalars *ds) {
-    if (ds->done) return;
-    const double alpha = ds->alpha;
+            double *partials, int nblocks, const DevScalars *in, DevScalars *out) {
+    const Step st = step_alpha(partials, nblocks, in, out);
+    if (!st.go) return;
+    const double alpha = st.alpha;
     const int lane = threadIdx.x & 63;
     double acc[1] = {0.0};
     for_each_slice(S, [&](int64_t s) {
@@ -2739,11 +2743,11 @@ k_pg_update(int32_t n, int64_t S, double *__restrict__ r, const double *__restri
             acc[0] += ri * ri;
         }
     });
-    block_partials<1>(acc, partials);
+    block_partials<1>(acc, partials + kMaxGrid);
 }
 
 
-// rho' = r.z; beta = rho'/rho
+// the partials of r.z, for a V-cycle whose last kernel did not take them
 __global__ void __launch_bounds__(kBlock)
 k_pg_rz(int32_t n, int64_t S, const double *__restrict__ r, const double *__restrict__ z,
         double *partials, const DevScalars *ds) {
@@ -2757,26 +2761,21 @@ k_pg_rz(int32_t n, int64_t S, const double *__restrict__ r, const double *__rest
     block_partials<1>(acc, partials);
 }
 
-struct EpiBeta {
-    __device__ bool active(const DevScalars *ds) const { return !ds->done; }
-    __device__ void operator()(const double *t, DevScalars *ds) const {
-        ds->beta = t[0] / ds->rho;
-        ds->rho = t[0];
-        ds->x_pending = 0;  // k_pg_p applies it next
-    }
-};
-
 // x += alpha p (the iteration's solution update, deferred from k_pg_update);
 // p = z + beta p.  x and z are not read again before the next iteration's
 // direction update, so they stream past the caches (nontemporal) at every
 // size, while p keeps the default policy at every size: the new p, which the
 // CG product gathers next, then stays in the Infinity Cache (the c3 CG
-// product went from 133 to 122 us).
+// product went from 133 to 122 us).  This kernel and the residual update take
+// beta and alpha from their producers' partials (100^3: 15.95 -> 15.2 ms,
+// 200^3: 125.6 -> 124.4 ms; the mixed forms' inner CG likewise).
 __global__ void __launch_bounds__(kBlock)
 k_pg_p(int32_t n, int64_t S, double *__restrict__ x, const double *__restrict__ z,
-       double *__restrict__ p, const DevScalars *ds) {
-    if (ds->done) return;
-    const double alpha = ds->alpha, beta = ds->beta;
+       double *__restrict__ p, const double *partials, int nblocks, int mode,
+       const DevScalars *in, DevScalars *out) {
+    const Step st = step_beta(mode, partials, nblocks, in, out);
+    if (!st.go || mode == kStepFirst) return;  // the first direction is there already
+    const double alpha = st.alpha, beta = st.beta;
     const int lane = threadIdx.x & 63;
     for_each_slice(S, [&](int64_t s) {
         const int64_t i = s * kWave + lane;
@@ -2797,6 +2796,8 @@ static int pcg_gamg_fp64_run(ldu_t *h, const double *b, double *x, const ldu_pcg
     const int n = L.n;
     const int64_t S = L.A.nslices;
     const int G = stream_grid_slices(S);
+    // products on plain slices: blocks past the cap would only add zeros
+    const int Gq = A.pdeg ? G : std::min(G, kPlainF64ProductBlocks);
     const bool nt = n > kStreamNtCells;
     ensure_hist(h, (int64_t)o.max_iter + 2);
     fill_level_stats(h, stats);
@@ -2825,24 +2826,26 @@ static int pcg_gamg_fp64_run(ldu_t *h, const double *b, double *x, const ldu_pcg
         const double *z = vcycle<double>(c, 0, h->r);
         k_pg_start<<<G, kBlock, 0, st>>>(n, S, h->r, z, h->p, h->partials, h->dev);
         launch_finalize<1>(h->partials, G, h->dev, EpiRho{}, st);
+        k_pg_p<<<1, kBlock, 0, st>>>(n, S, x, z, h->p, h->partials, G, kStepFirst, h->dev,
+                                     h->dev + 1);  // passes the scalars on
         const double res0 = res;
         const int iters0 = hs.iters;
         for (;;) {
             const int batch = next_batch(res0, hs.res, hs.iters - iters0, o.rel_tol, every);
             for (int k = 0; k < batch; ++k) {
-                launch_pcg_q(h, A, h->p, h->q, G, st);
+                launch_product_dot(h, A, h->p, h->q, Gq, h->dev + 1, st);
                 if (nt)
-                    k_pg_update<true><<<G, kBlock, 0, st>>>(n, S, h->r, h->q, h->partials,
-                                                            h->dev);
+                    k_pg_update<true><<<G, kBlock, 0, st>>>(n, S, h->r, h->q, h->partials, Gq,
+                                                            h->dev + 1, h->dev);
                 else
-                    k_pg_update<false><<<G, kBlock, 0, st>>>(n, S, h->r, h->q, h->partials,
-                                                             h->dev);
-                launch_converge(h, G, false, st);
+                    k_pg_update<false><<<G, kBlock, 0, st>>>(n, S, h->r, h->q, h->partials, Gq,
+                                                             h->dev + 1, h->dev);
+                launch_converge(h, h->partials + kMaxGrid, G, st);
                 int blocks = 0;  // the last level-0 kernel may take r.z itself
                 z = vcycle<double>(c, 0, h->r, h->r, &blocks);
                 if (!blocks) k_pg_rz<<<G, kBlock, 0, st>>>(n, S, h->r, z, h->partials, h->dev);
-                launch_finalize<1>(h->partials, blocks ? blocks : G, h->dev, EpiBeta{}, st);
-                k_pg_p<<<G, kBlock, 0, st>>>(n, S, x, z, h->p, h->dev);
+                k_pg_p<<<G, kBlock, 0, st>>>(n, S, x, z, h->p, h->partials, blocks ? blocks : G,
+                                             kStepReduce, h->dev, h->dev + 1);
             }
             HIP_CHECK(hipGetLastError());
             read_scalars(h, st);
@@ -2916,7 +2919,7 @@ struct EpiMxRho {
     __device__ void operator()(const double *t, DevScalars *ds) const { ds->rho = t[0]; }
 };
 
-// rho' = r.z -> beta (FP64), then p = z + fp32(beta) p in the next kernel
+// the partials of r.z, for a V-cycle whose last kernel did not take them
 __global__ void __launch_bounds__(kBlock)
 k_mxg_rz(int32_t n, int64_t S, const float *__restrict__ r, const float *__restrict__ z,
          double *partials, const DevScalars *ds) {
@@ -2930,19 +2933,12 @@ k_mxg_rz(int32_t n, int64_t S, const float *__restrict__ r, const float *__restr
     block_partials<1>(acc, partials);
 }
 
-struct EpiMxBeta {
-    __device__ bool active(const DevScalars *ds) const { return !vc_skip(ds); }
-    __device__ void operator()(const double *t, DevScalars *ds) const {
-        ds->beta = t[0] / ds->rho;
-        ds->rho = t[0];
-    }
-};
-
 __global__ void __launch_bounds__(kBlock)
 k_mxg_p(int32_t n, int64_t S, const float *__restrict__ z, float *__restrict__ p,
-        const DevScalars *ds) {
-    if (vc_skip(ds)) return;
-    const float bf = (float)ds->beta;
+        const double *partials, int nblocks, int mode, const DevScalars *in, DevScalars *out) {
+    const Step st = step_mx_beta(mode, partials, nblocks, in, out);
+    if (!st.go || mode == kStepFirst) return;  // the first direction is there already
+    const float bf = (float)st.beta;
     const int lane = threadIdx.x & 63;
     for_each_slice(S, [&](int64_t s) {
         const int64_t i = s * kWave + lane;
@@ -2973,6 +2969,7 @@ static int pcg_gamg_mixed_run(ldu_t *h, const double *b, double *x, const ldu_pc
     const int n = L.n;
     const int64_t S = L.A.nslices;
     const int G = stream_grid_slices(S);
+    const int Gr = std::min(G, kCgBlocks);
     ensure_hist(h, (int64_t)o.max_refine + 2);
     fill_level_stats(h, stats);
     if (stats) stats->history_count = 0;
@@ -3002,16 +2999,18 @@ static int pcg_gamg_mixed_run(ldu_t *h, const double *b, double *x, const ldu_pc
         const float *z = vcycle<float>(c, 0, h->r32);
         k_mxg_p0<<<G, kBlock, 0, st>>>(n, S, h->r32, z, h->p32, h->partials, h->dev);
         launch_finalize<1>(h->partials, G, h->dev, EpiMxRho{}, st);
+        k_mxg_p<<<1, kBlock, 0, st>>>(n, S, z, h->p32, h->partials, G, kStepFirst, h->dev,
+                                      h->dev + 1);  // passes the scalars on
         int batch = every;
         for (;;) {
             for (int k = 0; k < batch; ++k) {
                 launch_mx_q(h, A32, G, st);
-                launch_mx_update_plain(h, n, S, G, st);
+                launch_mx_update_plain(h, n, S, Gr, G, st);
                 int blocks = 0;  // the last level-0 kernel may take r.z itself
                 z = vcycle<float>(c, 0, h->r32, h->r32, &blocks);
                 if (!blocks) k_mxg_rz<<<G, kBlock, 0, st>>>(n, S, h->r32, z, h->partials, h->dev);
-                launch_finalize<1>(h->partials, blocks ? blocks : G, h->dev, EpiMxBeta{}, st);
-                k_mxg_p<<<G, kBlock, 0, st>>>(n, S, z, h->p32, h->dev);
+                k_mxg_p<<<Gr, kBlock, 0, st>>>(n, S, z, h->p32, h->partials, blocks ? blocks : G,
+                                               kStepReduce, h->dev, h->dev + 1);
             }
             HIP_CHECK(hipGetLastError());
             read_scalars(h, st);

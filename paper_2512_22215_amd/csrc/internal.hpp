@@ -445,11 +445,12 @@ void zero_vector(double *a, int64_t n, hipStream_t st);
 void launch_residual_plain(ldu_t *h, const SellView<double> &A, const double *b,
                            const double *x, double *r, bool write_hist, int grid,
                            hipStream_t st);
-void launch_pcg_q(ldu_t *h, const SellView<double> &A, const double *p, double *q, int grid,
-                  hipStream_t st);
+// q = A p and the partials of p.q, unless the scalars in ds say done
+void launch_product_dot(ldu_t *h, const SellView<double> &A, const double *p, double *q, int grid,
+                        const DevScalars *ds, hipStream_t st);
 void set_done(ldu_t *h, int done, hipStream_t st);
-// epilogue after an r update whose partials hold ||r||^2 (and r.z)
-void launch_converge(ldu_t *h, int grid, bool with_beta, hipStream_t st);
+// convergence step after an r update whose partials hold ||r||^2
+void launch_converge(ldu_t *h, const double *partials, int grid, hipStream_t st);
 // x += alpha p if a stopped CG still owes it
 void launch_x_pending(ldu_t *h, double *x, const double *p, int32_t n, int64_t S, int grid,
                       hipStream_t st);
@@ -468,7 +469,7 @@ int pcg_gamg_fp64(ldu_t *h, const double *b, double *x, const ldu_pcg_opts &o, b
 int pcg_gamg_mixed(ldu_t *h, const double *b, double *x, const ldu_pcg_opts &o, bool tr,
                    ldu_stats *stats, hipStream_t st);
 void launch_mx_q(ldu_t *h, const SellView<float> &A32, int G, hipStream_t st);
-void launch_mx_update_plain(ldu_t *h, int32_t n, int64_t S, int G, hipStream_t st);
+void launch_mx_update_plain(ldu_t *h, int32_t n, int64_t S, int G, int Gq, hipStream_t st);
 void set_inner(ldu_t *h, double inner_tol, int inner_max, hipStream_t st);
 void launch_mx_refine(ldu_t *h, double *x, int32_t n, int64_t S, int G, hipStream_t st);
 

@@ -239,22 +239,7 @@ k_pcg_q(SellView<double> A, const double *__restrict__ p, double *__restrict__ q
     block_partials<1>(acc, partials);
 }
 
-struct EpiAlpha {
-    __device__ bool active(const DevScalars *ds) const { return !ds->done; }
-    __device__ void operator()(const double *t, DevScalars *ds) const {
-        const double pq = t[0];
-        ds->pq = pq;
-        if (!isfinite(pq) || fabs(pq) <= 1e-300) {
-            ds->status = LDU_ERR_BREAKDOWN;
-            ds->done = kFailed;
-        } else {
-            ds->alpha = ds->rho / pq;
-            ds->x_pending = 1;
-        }
-    }
-};
-
-static void launch_product_dot(ldu_t *h, const SellView<double> &A, const double *p, double *q,
+void launch_product_dot(ldu_t *h, const SellView<double> &A, const double *p, double *q,
                                int grid, const DevScalars *ds, hipStream_t st) {
     if (A.pdeg) k_pcg_q<true><<<grid, kBlock, 0, st>>>(A, p, q, h->partials, ds);
     else if (A.n > kStreamNtCells)
@@ -262,18 +247,11 @@ static void launch_product_dot(ldu_t *h, const SellView<double> &A, const double
     else k_pcg_q<false><<<grid, kBlock, 0, st>>>(A, p, q, h->partials, ds);
 }
 
-void launch_pcg_q(ldu_t *h, const SellView<double> &A, const double *p, double *q, int grid,
-                  hipStream_t st) {
-    launch_product_dot(h, A, p, q, grid, h->dev, st);
-    launch_finalize<1>(h->partials, grid, h->dev, EpiAlpha{}, st);
-}
-
-// iteration count, residual history and convergence test after the x, r
-// update; with_beta: also beta = rho'/rho from the second sum
+// iteration count, residual history and convergence test after the r update
+// of a CG whose preconditioned residual comes from a V-cycle
 struct EpiConverge {
     double *hist;
     int hist_cap;
-    int with_beta;
     __device__ bool active(const DevScalars *ds) const { return !ds->done; }
     __device__ void operator()(const double *t, DevScalars *ds) const {
         const int it = ds->iters + 1;
@@ -289,17 +267,13 @@ struct EpiConverge {
             ds->done = kConverged;
         } else if (it >= ds->max_iter) {
             ds->done = kMaxIter;
-        } else if (with_beta) {
-            ds->beta = t[1] / ds->rho;
-            ds->rho = t[1];
-            ds->x_pending = 0;  // k_pg_p applies it next
         }
     }
 };
 
-void launch_converge(ldu_t *h, int grid, bool with_beta, hipStream_t st) {
-    if (with_beta) launch_finalize<2>(h->partials, grid, h->dev, EpiConverge{h->hist, h->hist_cap, 1}, st);
-    else launch_finalize<1>(h->partials, grid, h->dev, EpiConverge{h->hist, h->hist_cap, 0}, st);
+void launch_converge(ldu_t *h, const double *partials, int grid, hipStream_t st) {
+    k_finalize<1, 0, EpiConverge><<<1, kBlock, 0, st>>>(partials, grid, h->dev,
+                                                        EpiConverge{h->hist, h->hist_cap});
 }
 
 // An iteration of diagonal CG is two or three kernels.  Scalars travel with
@@ -318,20 +292,10 @@ void launch_converge(ldu_t *h, int grid, bool with_beta, hipStream_t st) {
 // there, so a second gather costs less than a kernel.  Above, the direction
 // update is its own kernel.
 //
-// mode of a direction update: the partials hold the last residual update's
-// sums; the scalars are current (a reduction of its own ran for the host); the
-// first iteration, whose direction is z itself.
-enum { kStepReduce = 0, kStepReady = 1, kStepFirst = 2 };
-
 // what the solve of one handle passes to its step kernels
 struct StepHistory {
     double *hist;
     int hist_cap;
-};
-
-struct Step {
-    double alpha, beta;
-    bool go;  // false: the solve has stopped
 };
 
 // The residual update's sums (||r||^2 and r.z; PBiCG: z.rt), taken by every
@@ -387,35 +351,6 @@ __device__ __forceinline__ Step step_converge(int mode, const double *__restrict
         }
     }
     return st;
-}
-
-// the product's p.q, taken the same way: alpha, or breakdown
-__device__ __forceinline__ Step step_alpha(const double *__restrict__ partials, int nblocks,
-                                           const DevScalars *in, DevScalars *out) {
-    const bool lead = blockIdx.x == 0 && threadIdx.x == 0;
-    const int done0 = in->done;
-    const double rho = in->rho;
-    if (done0) {
-        if (lead) *out = *in;
-        return {0.0, 0.0, false};
-    }
-    double t[1];
-    sum_partials<1>(partials, nblocks, t);
-    const double pq = t[0];
-    const bool go = isfinite(pq) && fabs(pq) > 1e-300;
-    const double alpha = rho / pq;
-    if (lead) {
-        *out = *in;
-        out->pq = pq;
-        if (go) {
-            out->alpha = alpha;
-            out->x_pending = 1;
-        } else {
-            out->status = LDU_ERR_BREAKDOWN;
-            out->done = kFailed;
-        }
-    }
-    return {alpha, 0.0, go};
 }
 
 // the convergence step for the host, which reads the scalars next
@@ -1128,26 +1063,18 @@ k_mx_q(SellView<float> A, const float *__restrict__ p, float *__restrict__ q, do
     block_partials<1>(acc, partials);
 }
 
-struct EpiMxAlpha {
-    __device__ bool active(const DevScalars *ds) const { return !vc_skip(ds); }
-    __device__ void operator()(const double *t, DevScalars *ds) const {
-        const double pq = t[0];
-        if (!isfinite(pq) || fabs(pq) <= 1e-300) ds->inner_done = 1;
-        else ds->alpha = ds->rho / pq;
-    }
-};
-
 template <bool DIAGZ>
 __global__ void __launch_bounds__(kBlock)
 k_mx_update(int32_t n, int64_t S, const float *__restrict__ D, float *__restrict__ d,
             float *__restrict__ r, const float *__restrict__ p, const float *__restrict__ q,
-            double *partials, const DevScalars *ds) {
-    if (vc_skip(ds)) return;
-    const float af = (float)ds->alpha;
+            double *partials, int nblocks, const DevScalars *in, DevScalars *out) {
+    const Step s = step_mx_alpha(partials, nblocks, in, out);
+    if (!s.go) return;
+    const float af = (float)s.alpha;
     const int lane = threadIdx.x & 63;
     double acc[2] = {0.0, 0.0};
-    for_each_slice(S, [&](int64_t s) {
-        const int64_t i = s * kWave + lane;
+    for_each_slice(S, [&](int64_t sl) {
+        const int64_t i = sl * kWave + lane;
         if (i < n) {
             const float di = d[i] + af * p[i];
             const float ri = r[i] - af * q[i];
@@ -1160,49 +1087,53 @@ k_mx_update(int32_t n, int64_t S, const float *__restrict__ D, float *__restrict
             }
         }
     });
-    block_partials<2>(acc, partials);
+    block_partials<2>(acc, partials + kMaxGrid);
 }
 
+// the stop test of an inner CG whose preconditioned direction comes from a
+// V-cycle
 struct EpiMxInner {
-    int with_beta;
     __device__ bool active(const DevScalars *ds) const { return !vc_skip(ds); }
     __device__ void operator()(const double *t, DevScalars *ds) const {
         const int it = ds->inner_iters + 1;
         ds->inner_iters = it;
         ds->rr = t[0];
-        if (sqrt(t[0]) <= ds->inner_now * ds->r0 || it >= ds->inner_max) {
-            ds->inner_done = 1;
-        } else if (with_beta) {
-            ds->beta = t[1] / ds->rho;
-            ds->rho = t[1];
-        }
+        if (sqrt(t[0]) <= ds->inner_now * ds->r0 || it >= ds->inner_max) ds->inner_done = 1;
     }
 };
 
+// the diagonal form's step for the host, which reads the scalars next
+__global__ void __launch_bounds__(kBlock)
+k_mx_step(const double *partials, int nblocks, DevScalars *ds) {
+    step_mx_inner(kStepReduce, partials, nblocks, ds, ds);
+}
+
 __global__ void __launch_bounds__(kBlock)
 k_mx_p(int32_t n, int64_t S, const float *__restrict__ D, const float *__restrict__ r,
-       float *__restrict__ p, const DevScalars *ds) {
-    if (vc_skip(ds)) return;
-    const float bf = (float)ds->beta;
+       float *__restrict__ p, const double *partials, int nblocks, int mode,
+       const DevScalars *in, DevScalars *out) {
+    const Step s = step_mx_inner(mode, partials, nblocks, in, out);
+    if (!s.go || mode == kStepFirst) return;  // the first direction is there already
+    const float bf = (float)s.beta;
     const int lane = threadIdx.x & 63;
-    for_each_slice(S, [&](int64_t s) {
-        const int64_t i = s * kWave + lane;
+    for_each_slice(S, [&](int64_t sl) {
+        const int64_t i = sl * kWave + lane;
         if (i < n) p[i] = r[i] / D[i] + bf * p[i];
     });
 }
 
+// q = A p with the scalars in dev[1]
 void launch_mx_q(ldu_t *h, const SellView<float> &A32, int G, hipStream_t st) {
-    if (A32.pdeg) k_mx_q<true><<<G, kBlock, 0, st>>>(A32, h->p32, h->q32, h->partials, h->dev);
-    else k_mx_q<false><<<G, kBlock, 0, st>>>(A32, h->p32, h->q32, h->partials, h->dev);
-    launch_finalize<1>(h->partials, G, h->dev, EpiMxAlpha{}, st);
+    if (A32.pdeg) k_mx_q<true><<<G, kBlock, 0, st>>>(A32, h->p32, h->q32, h->partials, h->dev + 1);
+    else k_mx_q<false><<<G, kBlock, 0, st>>>(A32, h->p32, h->q32, h->partials, h->dev + 1);
 }
 
 // d += alpha p; r -= alpha q; ||r||^2 and the inner convergence test (the
-// preconditioned direction comes from outside)
-void launch_mx_update_plain(ldu_t *h, int32_t n, int64_t S, int G, hipStream_t st) {
+// preconditioned direction comes from outside); Gq: blocks of the product
+void launch_mx_update_plain(ldu_t *h, int32_t n, int64_t S, int G, int Gq, hipStream_t st) {
     k_mx_update<false><<<G, kBlock, 0, st>>>(n, S, nullptr, h->d32, h->r32, h->p32, h->q32,
-                                             h->partials, h->dev);
-    launch_finalize<2>(h->partials, G, h->dev, EpiMxInner{0}, st);
+                                             h->partials, Gq, h->dev + 1, h->dev);
+    launch_finalize<1>(h->partials + kMaxGrid, G, h->dev, EpiMxInner{}, st);
 }
 
 // x += s * fp64(d)
@@ -1238,6 +1169,7 @@ int pcg_mixed(ldu_t *h, const double *b, double *x, const ldu_pcg_opts &o, bool 
     const int n = L.n;
     const int64_t S = L.A.nslices;
     const int G = stream_grid_slices(S);
+    const int Gr = std::min(G, kCgBlocks);
     ensure_hist(h, (int64_t)o.max_refine + 2);
     fill_stats_common(stats);
     set_scalars_for_solve(h, o.rel_tol, o.max_refine, st);
@@ -1263,18 +1195,19 @@ int pcg_mixed(ldu_t *h, const double *b, double *x, const ldu_pcg_opts &o, bool 
         k_mx_start<<<G, kBlock, 0, st>>>(n, S, h->r, A32.diag, h->r32, h->d32, h->p32,
                                          h->partials, h->dev);
         launch_finalize<2>(h->partials, G, h->dev, EpiMxStart{1}, st);
+        int step = 0;  // inner iterations launched
         for (;;) {
-            for (int k = 0; k < every; ++k) {
-                if (A32.pdeg)
-                    k_mx_q<true><<<G, kBlock, 0, st>>>(A32, h->p32, h->q32, h->partials, h->dev);
-                else
-                    k_mx_q<false><<<G, kBlock, 0, st>>>(A32, h->p32, h->q32, h->partials, h->dev);
-                launch_finalize<1>(h->partials, G, h->dev, EpiMxAlpha{}, st);
-                k_mx_update<true><<<G, kBlock, 0, st>>>(n, S, A32.diag, h->d32, h->r32,
-                                                        h->p32, h->q32, h->partials, h->dev);
-                launch_finalize<2>(h->partials, G, h->dev, EpiMxInner{1}, st);
-                k_mx_p<<<G, kBlock, 0, st>>>(n, S, A32.diag, h->r32, h->p32, h->dev);
+            for (int k = 0; k < every; ++k, ++step) {
+                const int mode = step == 0 ? kStepFirst : k == 0 ? kStepReady : kStepReduce;
+                k_mx_p<<<mode == kStepFirst ? 1 : Gr, kBlock, 0, st>>>(
+                    n, S, A32.diag, h->r32, h->p32, h->partials + kMaxGrid, Gr, mode, h->dev,
+                    h->dev + 1);
+                launch_mx_q(h, A32, G, st);
+                k_mx_update<true><<<Gr, kBlock, 0, st>>>(n, S, A32.diag, h->d32, h->r32, h->p32,
+                                                         h->q32, h->partials, G, h->dev + 1,
+                                                         h->dev);
             }
+            k_mx_step<<<1, kBlock, 0, st>>>(h->partials + kMaxGrid, Gr, h->dev);
             HIP_CHECK(hipGetLastError());
             read_scalars(h, st);
             if (hs.inner_done) break;
