@@ -416,7 +416,7 @@ struct SliceOffsets {
 // of the slice's rows; the slot count is the slice width, wave-uniform, so
 // the slot bases come from scalar loads).  C16: columns are the slot base
 // plus a 16-bit offset.
-template <bool C16, typename T>
+template <bool C16, typename T, bool NT = true>
 struct PlainWalk {
     const int32_t *cp;
     const uint16_t *hp;
@@ -443,23 +443,23 @@ struct PlainWalk {
         const int64_t o = (int64_t)k * kWave;
         if constexpr (C16) {
             base = bp[k];
-            if (base >= 0) raw = (int32_t)__builtin_nontemporal_load(hp + o);
-            else raw = __builtin_nontemporal_load(cp + o);
+            if (base >= 0) raw = (int32_t)vld<NT>(hp + o);
+            else raw = vld<NT>(cp + o);
         } else {
             base = 0;
-            raw = __builtin_nontemporal_load(cp + o);
+            raw = vld<NT>(cp + o);
         }
-        v = __builtin_nontemporal_load(vp + o);
+        v = vld<NT>(vp + o);
     }
     static __device__ __forceinline__ int32_t column(int32_t raw, int32_t base) {
         return C16 && base >= 0 ? base + raw : raw;
     }
 };
 
-template <bool C16, int B, typename T, class XA, class F>
+template <bool C16, int B, bool NT = true, typename T, class XA, class F>
 __device__ __forceinline__ void plain_entries(const SellView<T> &A, int64_t s, int lane,
                                               const XA &xa, F &&f) {
-    const PlainWalk<C16, T> pw(A, s, lane);
+    const PlainWalk<C16, T, NT> pw(A, s, lane);
     for (int k = 0; k < pw.w; k += B) {
         int32_t c[B], cb[B];
         T v[B];
@@ -470,7 +470,7 @@ __device__ __forceinline__ void plain_entries(const SellView<T> &A, int64_t s, i
 #pragma unroll
         for (int u = 0; u < B; ++u) {
             if (k + u < pw.w) {
-                c[u] = PlainWalk<C16, T>::column(c[u], cb[u]);
+                c[u] = PlainWalk<C16, T, NT>::column(c[u], cb[u]);
                 xv[u] = xa(c[u]);
             }
         }
@@ -482,7 +482,7 @@ __device__ __forceinline__ void plain_entries(const SellView<T> &A, int64_t s, i
 
 // the entries of a compressed-slice row whose slice starts at b0 and whose
 // length is w (see cmp_entries)
-template <int B, typename T, class XA, class F>
+template <int B, bool NT = true, typename T, class XA, class F>
 __device__ __forceinline__ void cmp_entries_at(const SellView<T> &A, int64_t b0, int w, int lane,
                                                const XA &xa, F &&f) {
     const int32_t *cp = A.col + b0 + lane;
@@ -496,8 +496,8 @@ __device__ __forceinline__ void cmp_entries_at(const SellView<T> &A, int64_t b0,
             const bool has = k + u < w;
             const int64_t o = so.next(has);
             if (has) {
-                c[u] = __builtin_nontemporal_load(cp + o);
-                v[u] = __builtin_nontemporal_load(vp + o);
+                c[u] = vld<NT>(cp + o);
+                v[u] = vld<NT>(vp + o);
             }
         }
         T xv[B];
@@ -517,7 +517,10 @@ __device__ __forceinline__ void cmp_entries_at(const SellView<T> &A, int64_t b0,
 template <int B, typename T, class XA, class F>
 __device__ __forceinline__ void cmp_entries(const SellView<T> &A, int64_t s, int lane,
                                             const XA &xa, F &&f) {
-    cmp_entries_at<B>(A, A.sptr[s], A.pdeg[s * kWave + lane], lane, xa, f);
+    const int64_t b0 = A.sptr[s];
+    const int w = A.pdeg[s * kWave + lane];
+    if (A.stream) cmp_entries_at<B, true>(A, b0, w, lane, xa, f);
+    else cmp_entries_at<B, false>(A, b0, w, lane, xa, f);
 }
 
 // The header of a compressed slice as one lane needs it: the slice start, and
@@ -568,8 +571,13 @@ __device__ __forceinline__ void row_entries(const SellView<T> &A, int64_t s, int
     if constexpr (CMP) {
         cmp_entries<B>(A, s, lane, xa, f);
     } else {
-        if (A.c16) plain_entries<true, B>(A, s, lane, xa, f);
-        else plain_entries<false, B>(A, s, lane, xa, f);
+        if (A.stream) {
+            if (A.c16) plain_entries<true, B, true>(A, s, lane, xa, f);
+            else plain_entries<false, B, true>(A, s, lane, xa, f);
+        } else {
+            if (A.c16) plain_entries<true, B, false>(A, s, lane, xa, f);
+            else plain_entries<false, B, false>(A, s, lane, xa, f);
+        }
     }
 }
 

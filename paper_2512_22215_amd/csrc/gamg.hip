@@ -988,8 +988,9 @@ k_vc_jacobi(SellView<T> A, const T *__restrict__ r, const T *__restrict__ e,
                 }
                 const T ri = r[i], di = A.diag[i], ei = e[i];
                 T y = di * ei;  // the row's order: diagonal, then columns
-                cmp_entries_at<kCmpBatch>(A, hd.b0, hd.w, lane, Direct<T>{e},
-                                          [&](int32_t, T v, T xv) { y = y + v * xv; });
+                auto add = [&](int32_t, T v, T xv) { y = y + v * xv; };
+                if (A.stream) cmp_entries_at<kCmpBatch, true>(A, hd.b0, hd.w, lane, Direct<T>{e}, add);
+                else cmp_entries_at<kCmpBatch, false>(A, hd.b0, hd.w, lane, Direct<T>{e}, add);
                 finish(i, y, ri, di, ei, k0, k1);
             }
         });
@@ -2309,7 +2310,11 @@ static T *vcycle(const VCtx &c, size_t l, const T *r, const T *rdot = nullptr,
         HIP_CHECK(hipGetLastError());
         return e;
     }
-    const SellView<T> A = lview<T>(L, c.tr);
+    SellView<T> A = lview<T>(L, c.tr);
+    // a cycle without the one-pass down leg sweeps the level several times in
+    // a row (matrix, and r, e, its second buffer, t and D)
+    A.stream = rop_level<T>(c, l) ||
+               L.A.bytes(sizeof(T)) + 5 * (int64_t)sizeof(T) * L.n > kCacheBytes;
     const int64_t S = L.A.nslices;
     const int G = stream_grid_slices(S);
     const T omega = (T)c.o->omega;
@@ -2649,7 +2654,8 @@ constexpr int kCycleBatch = 8;
 static int gamg_fp64_run(ldu_t *h, const double *b, double *x, const ldu_gamg_opts &o, bool tr,
               ldu_stats *stats, hipStream_t st) {
     Level &L = h->levels[0];
-    const SellView<double> A = L.A.view(tr);
+    SellView<double> A = L.A.view(tr);
+    A.stream = L.A.bytes(sizeof(double)) + 5 * (int64_t)sizeof(double) * L.n > kCacheBytes;
     const int64_t S = L.A.nslices;
     const int G = stream_grid_slices(S);
     ensure_hist(h, (int64_t)o.max_cycles + 2);

@@ -88,6 +88,16 @@ constexpr int kCgBlocks = LDU_CG_BLOCKS;
 #endif
 constexpr int64_t kRenumberCells = LDU_RENUMBER_CELLS;
 constexpr int32_t kRenumberRows = 20000;
+// A matrix is read with the default cache policy (SellView::stream false) when
+// it and the vectors used between two passes over it fit the 256 MB Infinity
+// Cache, else nontemporally, so that it leaves the vectors there.  Diagonal CG,
+// streaming against keeping the matrix: 100^3 (100 MB) 26.3 and 24.9 ms, 125^3
+// (211 MB) 57.9 and 52.2, 150^3 (364 MB) 109.0 and 118.3; PBiCG 100^3 (188 MB)
+// 7.49 and 6.80 ms, 125^3 (367 MB) 12.8 and 13.3; standalone GAMG, whose
+// cycles sweep a level several times in a row, 128^3 33.6 and 31.9 ms; CG +
+// V-cycle passes over each level's operators once in turn and streams them
+// (100^3 15.5 and 16.3 ms, 200^3 125.0 and 132.8).
+constexpr int64_t kCacheBytes = int64_t(240) << 20;
 constexpr int kMaxLevels = 64;
 constexpr int kMaxCoarseRow = 128; // widest coarse-level row the setup supports
 constexpr double kCoarsestTol = 1e-10;
@@ -128,6 +138,7 @@ struct SellView {
     const int32_t *otab;   // compressed slices: offset of entry k within slice s
     const uint16_t *c16;   // column minus its slot base (NULL: use col)
     const int32_t *cbase;  // smallest column of each slot (-1: slot uses col)
+    bool stream = true;    // columns and values are read past the caches
 };
 
 // scalars shared between the kernels of one solve; device resident
@@ -222,6 +233,10 @@ struct Sell {
     uint16_t *c16 = nullptr;
     int32_t *cbase = nullptr;
 
+    // bytes of one pass over columns and values of this size each
+    int64_t bytes(size_t value) const {
+        return nnz * (int64_t)((c16 ? sizeof(uint16_t) : sizeof(int32_t)) + value);
+    }
     __host__ __device__ SellView<double> view(bool transpose) const {
         return {n,    nslices, sptr, col,  transpose ? valT : val, diag, perm, iperm, pdeg,
                 tptr, otab,    c16,  cbase};

@@ -565,7 +565,9 @@ static void fill_stats_common(ldu_stats *stats) {
 int pcg_fp64(ldu_t *h, const double *b, double *x, const ldu_pcg_opts &o, bool tr,
              ldu_stats *stats, hipStream_t st, bool own_hist) {
     const Level &L = h->L0;
-    const SellView<double> A = L.A.view(tr);
+    SellView<double> A = L.A.view(tr);
+    // six vectors: x, r, p, q, D and the two-kernel form's z
+    A.stream = L.A.bytes(sizeof(double)) + 6 * (int64_t)sizeof(double) * L.n > kCacheBytes;
     const int n = L.n;
     const int64_t S = L.A.nslices;
     const int G = stream_grid_slices(S);
@@ -699,12 +701,12 @@ k_bicg_start(int32_t n, int64_t S, const double *__restrict__ r, const double *_
 // the entries of one row for A and for A^T together (valT holds A^T at the
 // same positions), so that columns and slot bases are read once: q and qt add
 // v x(c) and vt xt(c) in column order
-template <bool C16, class X, class XT>
+template <bool C16, bool NT, class X, class XT>
 __device__ __forceinline__ void plain_pair(const SellView<double> &A, const double *valT,
                                            int64_t s, int lane, const X &x, const XT &xt,
                                            double &q, double &qt) {
     constexpr int B = 8;
-    const PlainWalk<C16, double> pw(A, s, lane);
+    const PlainWalk<C16, double, NT> pw(A, s, lane);
     const double *tp = valT + A.sptr[s] + lane;
     for (int k = 0; k < pw.w; k += B) {
         int32_t c[B], cb[B];
@@ -713,12 +715,12 @@ __device__ __forceinline__ void plain_pair(const SellView<double> &A, const doub
         for (int u = 0; u < B; ++u)
             if (k + u < pw.w) {
                 pw.load(k + u, c[u], cb[u], v[u]);
-                vt[u] = __builtin_nontemporal_load(tp + (int64_t)(k + u) * kWave);
+                vt[u] = vld<NT>(tp + (int64_t)(k + u) * kWave);
             }
 #pragma unroll
         for (int u = 0; u < B; ++u)
             if (k + u < pw.w) {
-                c[u] = PlainWalk<C16, double>::column(c[u], cb[u]);
+                c[u] = PlainWalk<C16, double, NT>::column(c[u], cb[u]);
                 xv[u] = x(c[u]);
                 xtv[u] = xt(c[u]);
             }
@@ -736,8 +738,13 @@ __device__ __forceinline__ void pair_entries(const SellView<double> &A, const do
                                              int64_t s, int lane, const X &x, const XT &xt,
                                              double &q, double &qt) {
     if constexpr (!CMP) {
-        if (A.c16) plain_pair<true>(A, valT, s, lane, x, xt, q, qt);
-        else plain_pair<false>(A, valT, s, lane, x, xt, q, qt);
+        if (A.stream) {
+            if (A.c16) plain_pair<true, true>(A, valT, s, lane, x, xt, q, qt);
+            else plain_pair<false, true>(A, valT, s, lane, x, xt, q, qt);
+        } else {
+            if (A.c16) plain_pair<true, false>(A, valT, s, lane, x, xt, q, qt);
+            else plain_pair<false, false>(A, valT, s, lane, x, xt, q, qt);
+        }
     } else {
         constexpr int B = 12;
         const int64_t b0 = A.sptr[s];
@@ -893,7 +900,9 @@ k_bicg_r(int32_t n, int64_t S, const double *__restrict__ D, double *__restrict_
 int pbicg_fp64(ldu_t *h, const double *b, double *x, const ldu_pcg_opts &o, bool tr,
                ldu_stats *stats, hipStream_t st) {
     const Level &L = h->L0;
-    const SellView<double> A = L.A.view(tr);
+    SellView<double> A = L.A.view(tr);
+    // ten vectors, and the values of A and of A^T
+    A.stream = L.A.bytes(2 * sizeof(double)) + 10 * (int64_t)sizeof(double) * L.n > kCacheBytes;
     const double *valT = tr ? L.A.val : L.A.valT;
     const int n = L.n;
     const int64_t S = L.A.nslices;
