@@ -653,6 +653,7 @@ static void galerkin(ldu_t *h, Level &F, Level &C, Arena &ar, hipStream_t st) {
 }
 
 static void ensure_rop(ldu_t *h, const ldu_gamg_opts &o, hipStream_t st);
+static void ensure_gen(ldu_t *h, const ldu_gamg_opts &o, hipStream_t st);
 static void refresh_rop(ldu_t *h, hipStream_t st);
 
 // ---------------------------------------------------------------- inner numbering
@@ -840,6 +841,7 @@ void gamg_build(ldu_t *h, const ldu_gamg_opts &o, hipStream_t st) {
         q.scale_correction = 0;
         ensure_rop(h, q, st);
     }
+    ensure_gen(h, o, st);
     h->pool.trim();
 }
 
@@ -1445,9 +1447,9 @@ __device__ __forceinline__ T csr_row_sum(const CsrView<T> &R, int64_t c, int g, 
 // wave covers 64 / G consecutive rows.  R's results never had to follow the
 // row's column order (R's rows are sums the oracle forms in two steps,
 // residual then restriction).
-template <int G, bool NT, typename T>
+template <int G, bool NT, typename T, class XA>
 __global__ void __launch_bounds__(kBlock)
-k_vc_rrestrict_csr(CsrView<T> R, const T *__restrict__ r, T *__restrict__ rc,
+k_vc_rrestrict_csr(CsrView<T> R, XA x, T *__restrict__ rc,
                T *__restrict__ ec_first, const T *__restrict__ Dc, T omega,
                const DevScalars *ds) {
     if (vc_skip(ds)) return;
@@ -1460,7 +1462,7 @@ k_vc_rrestrict_csr(CsrView<T> R, const T *__restrict__ r, T *__restrict__ rc,
         // the coarse diagonal is loaded before the row, so its round trip
         // overlaps the row's gathers
         const T dc = (ec_first && g == 0 && c < R.n) ? Dc[c] : T(1);
-        const T acc = csr_row_sum<G, NT>(R, c, g, Direct<T>{r});
+        const T acc = csr_row_sum<G, NT>(R, c, g, x);
         if (c < R.n && g == 0) {
             rc[c] = acc;
             if (ec_first) ec_first[c] = omega * acc / dc;
@@ -1629,18 +1631,19 @@ static int launch_up_csr(const CsrView<T> &U, const T *r, const T *ec, T *e, con
     return G;
 }
 
-template <typename T>
-static void launch_rrestrict_csr(const CsrView<T> &R, const T *r, T *rc, T *ec_first, const T *Dc,
-                             T omega, const DevScalars *ds, hipStream_t st) {
+// x: the vector R's columns refer to (r, or (r, e) for W)
+template <typename T, class XA>
+static void launch_rrestrict_csr(const CsrView<T> &R, const XA &x, T *rc, T *ec_first, const T *Dc,
+                                 T omega, const DevScalars *ds, hipStream_t st) {
     const int64_t chunks = (R.n + kWave / R.group - 1) / (kWave / R.group);
     const int G = stream_grid_slices(chunks);
     const bool nt = R.nnz * (int64_t)(sizeof(int32_t) + sizeof(T)) > kCsrCachedBytes;
     with_group(R.group, [&](auto lanes) {
         constexpr int L = decltype(lanes)::value;
         if (nt)
-            k_vc_rrestrict_csr<L, true, T><<<G, kBlock, 0, st>>>(R, r, rc, ec_first, Dc, omega, ds);
+            k_vc_rrestrict_csr<L, true, T, XA><<<G, kBlock, 0, st>>>(R, x, rc, ec_first, Dc, omega, ds);
         else
-            k_vc_rrestrict_csr<L, false, T><<<G, kBlock, 0, st>>>(R, r, rc, ec_first, Dc, omega, ds);
+            k_vc_rrestrict_csr<L, false, T, XA><<<G, kBlock, 0, st>>>(R, x, rc, ec_first, Dc, omega, ds);
     });
 }
 
@@ -1675,6 +1678,206 @@ k_vc_energy(SellView<T> A, const T *__restrict__ ec, const T *__restrict__ rc, d
 // the factor from its two sums
 __device__ __forceinline__ double correction_scale(const double (&v)[2]) {
     return (isfinite(v[1]) && fabs(v[1]) > 1e-300) ? v[0] / v[1] : 1.0;
+}
+
+// ---------------------------------------------------------------- small levels, general cycles
+// Small levels of cycles without the one-pass down leg (two pre-sweeps,
+// scaled corrections: the solver's defaults) with G lanes per row, as R and U:
+//   sweep:    e' = e + omega (r - A e) / D
+//   restrict: r_c = P^T r - (P^T A) e        (W over (r, e))
+//   up:       e' = e0 + s P e_c + omega D^-1 (r - A (e0 + s P e_c))
+//                = e0 + omega (r - A e0) / D + s Q e_c,  Q = (I - omega D^-1 A) P
+//   energy:   e.r and e.A e of the coarse level
+// A row of V holds A's entries (diagonal included) and behind them Q's.  A
+// level takes five launches of about 4 us for two sweeps each way; with a lane
+// per row, and residual, member sums, correction and sweep apart, it took seven
+// of 4-12 us.  Standalone GAMG, default settings: 128^3 33.2 -> 27.9
+// ms, 64^3 12.3 -> 8.8 ms, 16^3 3.8 -> 2.5 ms.
+// one row of V by G lanes: the sums over its A entries (e) and, with UP, its Q
+// entries (ec); every lane of the wave calls this
+template <int G, bool UP, typename T>
+__device__ __forceinline__ void v_row_sums(const CsrView<T> &V, const int64_t *__restrict__ qptr,
+                                           int64_t i, int g, const T *__restrict__ e,
+                                           const T *__restrict__ ec, T &sa, T &sq) {
+    constexpr int U = kCsrBatch;
+    sa = sq = T(0);
+    if (i < V.n) {
+        const int64_t e1 = UP ? V.rptr[i + 1] : qptr[i];
+        for (int64_t k0 = V.rptr[i] + g; k0 < e1; k0 += (int64_t)G * U) {
+            int32_t cc[U];
+            T vv[U], xv[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int64_t k = k0 + (int64_t)u * G;
+                if (k < e1) {
+                    cc[u] = V.col[k];
+                    vv[u] = V.val[k];
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (k0 + (int64_t)u * G < e1) {
+                    if constexpr (UP) xv[u] = cc[u] < V.n ? e[cc[u]] : ec[cc[u] - V.n];
+                    else xv[u] = e[cc[u]];
+                }
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (k0 + (int64_t)u * G < e1) {
+                    if (!UP || cc[u] < V.n) sa = sa + vv[u] * xv[u];
+                    else sq = sq + vv[u] * xv[u];
+                }
+        }
+    }
+#pragma unroll
+    for (int off = G / 2; off > 0; off >>= 1) {
+        sa = sa + __shfl_xor(sa, off);
+        if constexpr (UP) sq = sq + __shfl_xor(sq, off);
+    }
+}
+
+// eo = e + omega (r - A e) / D, with UP plus s Q ec (s from the nblocks
+// partials of an energy kernel, 1 without any); DOT: partials of rdot . eo in
+// dots
+template <int G, bool UP, bool DOT, typename T>
+__global__ void __launch_bounds__(kBlock)
+k_gen_sweep(CsrView<T> V, const int64_t *__restrict__ qptr, const T *__restrict__ D,
+            const T *__restrict__ r, const T *__restrict__ e, const T *__restrict__ ec,
+            T *__restrict__ eo, T omega, const double *__restrict__ scale, int nblocks,
+            const T *__restrict__ rdot, double *dots, const DevScalars *ds) {
+    if (vc_skip(ds)) return;
+    T sc = T(1);
+    if (UP && nblocks > 0) {
+        double v[2];
+        sum_partials<2>(scale, nblocks, v);
+        sc = (T)correction_scale(v);
+    }
+    constexpr int RPW = kWave / G;
+    const int lane = threadIdx.x & 63;
+    const int g = lane % G;
+    const int64_t chunks = (V.n + RPW - 1) / RPW;
+    double acc[1] = {0.0};
+    for_each_slice(chunks, [&](int64_t s) {
+        const int64_t i = s * RPW + lane / G;
+        const bool own = i < V.n && g == 0;
+        const T ri = own ? r[i] : T(0), di = own ? D[i] : T(1), ei = own ? e[i] : T(0);
+        T sa, sq;
+        v_row_sums<G, UP>(V, qptr, i, g, e, ec, sa, sq);
+        if (own) {
+            T z = ei + omega * (ri - sa) / di;
+            if constexpr (UP) z = z + sc * sq;
+            eo[i] = z;
+            if constexpr (DOT) acc[0] += (double)rdot[i] * (double)z;
+        }
+    });
+    if constexpr (DOT) block_partials<1>(acc, dots);
+}
+
+// partials of e.r and e.A e
+template <int G, typename T>
+__global__ void __launch_bounds__(kBlock)
+k_gen_energy(CsrView<T> V, const int64_t *__restrict__ qptr, const T *__restrict__ e,
+             const T *__restrict__ r, double *partials, const DevScalars *ds) {
+    if (vc_skip(ds)) return;
+    constexpr int RPW = kWave / G;
+    const int lane = threadIdx.x & 63;
+    const int g = lane % G;
+    const int64_t chunks = (V.n + RPW - 1) / RPW;
+    double acc[2] = {0.0, 0.0};
+    for_each_slice(chunks, [&](int64_t s) {
+        const int64_t i = s * RPW + lane / G;
+        const bool own = i < V.n && g == 0;
+        const T ri = own ? r[i] : T(0), ei = own ? e[i] : T(0);
+        T sa, sq;
+        v_row_sums<G, false>(V, qptr, i, g, e, e, sa, sq);
+        if (own) {
+            acc[0] += (double)ei * (double)ri;
+            acc[1] += (double)ei * (double)sa;
+        }
+    });
+    block_partials<2>(acc, partials);
+}
+
+// V's columns and values: U's structure, with A's own entries in place of S's
+__global__ void k_gen_fill(Sell A, Csr V, int64_t *qptr, const int32_t *__restrict__ agg,
+                           double omega) {
+    GRID_STRIDE(i, A.n) {
+        const int64_t e0 = V.rptr[i], e1 = V.rptr[i + 1];
+        const double w = omega / A.diag[i];
+        int64_t s = e0, q0 = e0;
+        for_row_entries(A, (int32_t)i, [&](int32_t, int64_t) { ++q0; });
+        qptr[i] = q0;
+        int64_t q = q0;  // end of the aggregates found so far
+        for_row_entries(A, (int32_t)i, [&](int32_t j, int64_t e) {
+            const double a = e < 0 ? A.diag[j] : A.val[e], at = e < 0 ? A.diag[j] : A.valT[e];
+            V.col[s] = j;
+            V.val[s] = a;
+            V.valT[s] = at;
+            ++s;
+            const int32_t c = A.n + agg[j];
+            int64_t k = q0;
+            while (k < q && V.col[k] != c) ++k;
+            if (k == q) {
+                V.col[k] = c;
+                V.val[k] = V.valT[k] = 0.0;
+                ++q;
+            }
+            V.val[k] = V.val[k] + a;
+            V.valT[k] = V.valT[k] + at;
+        });
+        const int32_t own = A.n + agg[i];
+        for (int64_t k = q0; k < e1; ++k) {
+            const double p = V.col[k] == own ? 1.0 : 0.0;
+            V.val[k] = p - w * V.val[k];
+            V.valT[k] = p - w * V.valT[k];
+        }
+    }
+}
+
+// W: the members of row c (value 1, columns j), then its P^T A entries
+// (columns n + j), from the gathered pairs of k_rop_gather
+__global__ void k_w_count(int32_t nc, const int32_t *__restrict__ start,
+                          const int32_t *__restrict__ rdeg, int64_t *cnt) {
+    GRID_STRIDE(c, nc) cnt[c] = rdeg[c] + (start[c + 1] - start[c]);
+}
+__global__ void k_w_link(int32_t nc, int32_t n, Csr W, const int32_t *__restrict__ start,
+                         const int32_t *__restrict__ cells, const int64_t *__restrict__ tstart,
+                         const int32_t *__restrict__ tcol, int64_t *ws0, int32_t *wsn) {
+    GRID_STRIDE(c, nc) {
+        int64_t e = W.rptr[c];
+        for (int32_t k = start[c]; k < start[c + 1]; ++k, ++e) {
+            W.col[e] = cells[k];
+            W.val[e] = W.valT[e] = 1.0;
+            ws0[e] = 0;
+            wsn[e] = 0;
+        }
+        const int64_t o1 = tstart[c + 1];
+        for (int64_t a = tstart[c]; a < o1; ++e) {
+            int64_t b = a + 1;
+            while (b < o1 && tcol[b] == tcol[a]) ++b;
+            W.col[e] = n + tcol[a];
+            ws0[e] = a;
+            wsn[e] = (int32_t)(b - a);
+            a = b;
+        }
+    }
+}
+__global__ void k_w_values(int64_t nnz, int32_t n, Csr W, const int64_t *__restrict__ ws0,
+                           const int32_t *__restrict__ wsn, const int64_t *__restrict__ src,
+                           const double *__restrict__ aval, const double *__restrict__ avalT,
+                           const double *__restrict__ D) {
+    for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < nnz;
+         e += (int64_t)gridDim.x * blockDim.x) {
+        if (wsn[e] == 0) continue;  // a member
+        const double dj = D[W.col[e] - n];
+        double v = 0.0, vT = 0.0;
+        for (int64_t k = ws0[e]; k < ws0[e] + wsn[e]; ++k) {
+            const int64_t q = src[k];
+            v = v + (q < 0 ? dj : aval[q]);
+            vT = vT + (q < 0 ? dj : avalT[q]);
+        }
+        W.val[e] = -v;
+        W.valT[e] = -vT;
+    }
 }
 
 // e += s c, with s from the nblocks partials of k_vc_energy (1 without any).
@@ -2217,6 +2420,12 @@ template <>
 CsrView<double> upview<double>(const Level &L, bool tr) { return L.Uc.view(tr); }
 template <>
 CsrView<float> upview<float>(const Level &L, bool tr) { return L.Uc.view32(tr); }
+template <typename T>
+static CsrView<T> vview(const Csr &M, bool tr);
+template <>
+CsrView<double> vview<double>(const Csr &M, bool tr) { return M.view(tr); }
+template <>
+CsrView<float> vview<float>(const Csr &M, bool tr) { return M.view32(tr); }
 // R's values of this precision exist (either layout)
 template <typename T>
 static const T *ahval(const Level &L, bool tr);
@@ -2262,13 +2471,111 @@ template <typename T>
 static bool up_level(const VCtx &c, size_t l) {
     return rop_level<T>(c, l) && c.o->n_post > 0 && upview<T>(c.h->levels[l], c.tr).val;
 }
+// level l of a Jacobi cycle without the one-pass down leg runs through V and W
+static bool gen_cycle(const ldu_gamg_opts &o) {
+    return o.smoother == LDU_SMOOTH_JACOBI && !rop_cycle(o) && o.n_pre > 0 && o.n_post > 0;
+}
+template <typename T>
+static bool gen_level(const VCtx &c, size_t l) {
+    const Level &L = c.h->levels[l];
+    return gen_cycle(*c.o) && L.g_ready && L.g_omega == c.o->omega && vview<T>(L.V, c.tr).val;
+}
 // level l's unscaled correction is applied by the coarse level's last kernel
 // (a coarse level that runs through U leaves it to level l)
 template <typename T>
 static bool takes_correction(const VCtx &c, size_t l) {
-    const bool coarse_up = l + 2 < c.h->levels.size() && up_level<T>(c, l + 1);
+    const bool coarse_leaves =
+        l + 2 < c.h->levels.size() && (up_level<T>(c, l + 1) || gen_level<T>(c, l + 1));
     return !c.o->scale_correction && c.h->levels[l].n <= kFuseCorrRows && !up_level<T>(c, l) &&
-           !coarse_up;
+           !gen_level<T>(c, l) && !coarse_leaves;
+}
+
+template <typename T>
+static T *vcycle(const VCtx &c, size_t l, const T *r, const T *rdot = nullptr,
+                 int *dotted = nullptr, bool e_ready = false, FineCorr<T> fc = {},
+                 bool *corrected = nullptr);
+
+// sums of the scaling factor over level l (the coarse one); the number of partials
+template <typename T>
+static int launch_energy(const VCtx &c, size_t l, const T *ec, const T *rc) {
+    ldu_t *h = c.h;
+    const Level &C = h->levels[l];
+    if (l + 1 < h->levels.size() && gen_level<T>(c, l)) {
+        const CsrView<T> V = vview<T>(C.V, c.tr);
+        const int G = stream_grid_slices((V.n + kWave / V.group - 1) / (kWave / V.group));
+        with_group(V.group, [&](auto lanes) {
+            k_gen_energy<decltype(lanes)::value, T>
+                <<<G, kBlock, 0, c.st>>>(V, C.qptr, ec, rc, h->partials, h->dev);
+        });
+        return G;
+    }
+    const SellView<T> A = lview<T>(C, c.tr);
+    // blocks past the products' cap would only add zeros
+    int G = stream_grid_slices(A.nslices);
+    if (!A.pdeg) G = std::min(G, kPlainF64ProductBlocks);
+    if (A.pdeg) k_vc_energy<true, T><<<G, kBlock, 0, c.st>>>(A, ec, rc, h->partials, h->dev);
+    else k_vc_energy<false, T><<<G, kBlock, 0, c.st>>>(A, ec, rc, h->partials, h->dev);
+    return G;
+}
+
+// one sweep (or, with ec, the up leg) through V; the number of blocks, of
+// partials with rdot (CG's cycles, which take it, do not scale)
+template <typename T>
+static int launch_gen_sweep(const VCtx &c, const Level &L, const T *r, const T *e, const T *ec,
+                            T *eo, int scale_blocks, const T *rdot) {
+    const CsrView<T> V = vview<T>(L.V, c.tr);
+    const T *D = lview<T>(L, c.tr).diag;
+    const T omega = (T)c.o->omega;
+    const int G = stream_grid_slices((V.n + kWave / V.group - 1) / (kWave / V.group));
+    ldu_t *h = c.h;
+    with_group(V.group, [&](auto lanes) {
+        constexpr int N = decltype(lanes)::value;
+        auto run = [&](auto kernel) {
+            kernel<<<G, kBlock, 0, c.st>>>(V, L.qptr, D, r, e, ec, eo, omega, h->partials,
+                                           scale_blocks, rdot, h->partials, h->dev);
+        };
+        if (ec && rdot) run(k_gen_sweep<N, true, true, T>);
+        else if (ec) run(k_gen_sweep<N, true, false, T>);
+        else if (rdot) run(k_gen_sweep<N, false, true, T>);
+        else run(k_gen_sweep<N, false, false, T>);
+    });
+    return G;
+}
+
+// the levels from a small one down, through V and W
+template <typename T>
+static T *vcycle_gen(const VCtx &c, size_t l, const T *r, const T *rdot, int *dotted,
+                     bool e_ready) {
+    ldu_t *h = c.h;
+    Level &L = h->levels[l], &C = h->levels[l + 1];
+    hipStream_t st = c.st;
+    T *e = lvec<T>(L, 1), *e2 = lvec<T>(L, 2);
+    const T omega = (T)c.o->omega;
+    if (!e_ready) {
+        const int64_t S = L.A.nslices;
+        k_vc_first<T><<<stream_grid_slices(S), kBlock, 0, st>>>(
+            L.n, S, r, lview<T>(L, c.tr).diag, e, omega, h->dev);
+    }
+    for (int k = 1; k < c.o->n_pre; ++k) {
+        launch_gen_sweep<T>(c, L, r, e, nullptr, e2, 0, nullptr);
+        std::swap(e, e2);
+    }
+    T *rc = lvec<T>(C, 0);
+    const bool c_first = l + 2 < h->levels.size();  // the coarse level's first sweep
+    launch_rrestrict_csr<T>(vview<T>(L.W, c.tr), Stacked<T>{r, e, L.n}, rc,
+                            c_first ? lvec<T>(C, 1) : nullptr, lview<T>(C, c.tr).diag, omega,
+                            h->dev, st);
+    const T *ec = vcycle<T>(c, l + 1, rc, nullptr, nullptr, c_first);
+    const int scale_blocks = c.o->scale_correction ? launch_energy<T>(c, l + 1, ec, rc) : 0;
+    for (int k = 0; k < c.o->n_post; ++k) {
+        const T *rd = k + 1 == c.o->n_post ? rdot : nullptr;
+        const int blocks = launch_gen_sweep<T>(c, L, r, e, k == 0 ? ec : nullptr, e2,
+                                               k == 0 ? scale_blocks : 0, rd);
+        std::swap(e, e2);
+        if (rd && dotted) *dotted = blocks;
+    }
+    HIP_CHECK(hipGetLastError());
+    return e;
 }
 
 // One V-cycle e = V(l, r); returns the buffer holding e.  With rdot, the
@@ -2279,9 +2586,8 @@ static bool takes_correction(const VCtx &c, size_t l) {
 // correction e_f += P e, applied here by the kernel that produces e when it
 // can (*corrected tells the caller).
 template <typename T>
-static T *vcycle(const VCtx &c, size_t l, const T *r, const T *rdot = nullptr,
-                 int *dotted = nullptr, bool e_ready = false, FineCorr<T> fc = {},
-                 bool *corrected = nullptr) {
+static T *vcycle(const VCtx &c, size_t l, const T *r, const T *rdot, int *dotted, bool e_ready,
+                 FineCorr<T> fc, bool *corrected) {
     if (dotted) *dotted = 0;
     if (corrected) *corrected = false;
     ldu_t *h = c.h;
@@ -2310,6 +2616,7 @@ static T *vcycle(const VCtx &c, size_t l, const T *r, const T *rdot = nullptr,
         HIP_CHECK(hipGetLastError());
         return e;
     }
+    if (gen_level<T>(c, l)) return vcycle_gen<T>(c, l, r, rdot, dotted, e_ready);
     SellView<T> A = lview<T>(L, c.tr);
     // a cycle without the one-pass down leg sweeps the level several times in
     // a row (matrix, and r, e, its second buffer, t and D)
@@ -2369,7 +2676,7 @@ static T *vcycle(const VCtx &c, size_t l, const T *r, const T *rdot = nullptr,
             k_vc_rrestrict_cmp<T><<<stream_grid_slices(R.nslices), kBlock, 0, st>>>(
                 R, r, rc, ec_first, lview<T>(C, c.tr).diag, omega, h->dev);
         } else {
-            launch_rrestrict_csr<T>(rcview<T>(L, c.tr), r, rc, ec_first, lview<T>(C, c.tr).diag,
+            launch_rrestrict_csr<T>(rcview<T>(L, c.tr), Direct<T>{r}, rc, ec_first, lview<T>(C, c.tr).diag,
                                     omega, h->dev, st);
         }
     } else {
@@ -2383,17 +2690,8 @@ static T *vcycle(const VCtx &c, size_t l, const T *r, const T *rdot = nullptr,
     const T *ec = vcycle<T>(c, l + 1, rc, nullptr, nullptr, c_first,
                             fuse_corr ? FineCorr<T>{e, L.aggStart, L.aggCells} : FineCorr<T>{},
                             &done_corr);
-    int scale_blocks = 0;  // partials of the scaling factor's sums
-    if (c.o->scale_correction) {
-        const SellView<T> Ac = lview<T>(C, c.tr);
-        // blocks past the products' cap would only add zeros
-        scale_blocks = stream_grid_slices(Ac.nslices);
-        if (!Ac.pdeg) scale_blocks = std::min(scale_blocks, kPlainF64ProductBlocks);
-        if (Ac.pdeg)
-            k_vc_energy<true, T><<<scale_blocks, kBlock, 0, st>>>(Ac, ec, rc, h->partials, h->dev);
-        else
-            k_vc_energy<false, T><<<scale_blocks, kBlock, 0, st>>>(Ac, ec, rc, h->partials, h->dev);
-    }
+    // partials of the scaling factor's sums
+    const int scale_blocks = c.o->scale_correction ? launch_energy<T>(c, l + 1, ec, rc) : 0;
     int post = 0;  // post-sweeps done
     if (up) {
         const bool last = c.o->n_post == 1;
@@ -2593,8 +2891,84 @@ static void ensure_rop(ldu_t *h, const ldu_gamg_opts &o, hipStream_t st) {
     }
 }
 
+// V and W for the small levels of the other Jacobi cycles: structure once per
+// hierarchy, values again after new coefficients or another omega, FP32 copies
+// once the FP32 path is in use
+static void gen_structure(ldu_t *h, size_t l, hipStream_t st) {
+    Level &L = h->levels[l];
+    const Level &C = h->levels[l + 1];
+    Arena &ar = h->gamg_arena;
+    Arena tmp(&h->pool);
+    auto alloc = [&](Csr &M, int32_t n, const int64_t *cnt) {
+        M = Csr{};
+        M.n = n;
+        M.rptr = ar.get<int64_t>((size_t)n + 1);
+        exclusive_scan_i64(cnt, M.rptr, n, tmp, st);
+        HIP_CHECK(hipMemcpyAsync(&M.nnz, M.rptr + n, sizeof(int64_t), hipMemcpyDeviceToHost, st));
+        HIP_CHECK(hipStreamSynchronize(st));
+        M.col = ar.get<int32_t>(M.nnz);
+        M.val = ar.get<double>(M.nnz);
+        M.valT = ar.get<double>(M.nnz);
+        M.group = csr_group(M.nnz, n);
+    };
+    int64_t *cnt = tmp.get<int64_t>(L.n);
+    k_up_count<<<grid_n(L.n), kBlock, 0, st>>>(L.A, L.agg, cnt);
+    alloc(L.V, L.n, cnt);
+    L.qptr = ar.get<int64_t>(L.n);
+    int64_t *tstart = tmp.get<int64_t>((size_t)C.n + 1);
+    k_rop_count<<<grid_n(C.n), kBlock, 0, st>>>(C.n, L.aggStart, L.aggCells, L.A, cnt);
+    exclusive_scan_i64(cnt, tstart, C.n, tmp, st);
+    int64_t total = 0;
+    HIP_CHECK(hipMemcpyAsync(&total, tstart + C.n, sizeof(int64_t), hipMemcpyDeviceToHost, st));
+    HIP_CHECK(hipStreamSynchronize(st));
+    int32_t *tcol = tmp.get<int32_t>(total), *rdeg = tmp.get<int32_t>(C.n);
+    L.w_src = ar.get<int64_t>(total);
+    k_rop_gather<<<grid_n((int64_t)C.n * kWave), kBlock, 0, st>>>(C.n, L.aggStart, L.aggCells, L.A,
+                                                                 tstart, tcol, L.w_src, rdeg);
+    k_w_count<<<grid_n(C.n), kBlock, 0, st>>>(C.n, L.aggStart, rdeg, cnt);
+    alloc(L.W, C.n, cnt);
+    L.w_src0 = ar.get<int64_t>(L.W.nnz);
+    L.w_srcn = ar.get<int32_t>(L.W.nnz);
+    k_w_link<<<grid_n(C.n), kBlock, 0, st>>>(C.n, L.n, L.W, L.aggStart, L.aggCells, tstart, tcol,
+                                            L.w_src0, L.w_srcn);
+    HIP_CHECK(hipGetLastError());
+    HIP_CHECK(hipStreamSynchronize(st));  // tmp is released after this point
+    L.g_ready = false;
+}
+
+static void ensure_gen(ldu_t *h, const ldu_gamg_opts &o, hipStream_t st) {
+    if (!gen_cycle(o)) return;
+    const bool f32 = h->L0.A.val32 != nullptr;
+    for (size_t l = 0; l + 1 < h->levels.size(); ++l) {
+        Level &L = h->levels[l];
+        if (L.n > kUpRows) continue;
+        if (!L.V.rptr) gen_structure(h, l, st);
+        const bool fresh = L.g_ready && L.g_omega == o.omega;
+        if (!fresh) {
+            k_gen_fill<<<grid_n(L.n), kBlock, 0, st>>>(L.A, L.V, L.qptr, L.agg, o.omega);
+            k_w_values<<<grid_n(L.W.nnz), kBlock, 0, st>>>(L.W.nnz, L.n, L.W, L.w_src0, L.w_srcn,
+                                                          L.w_src, L.A.val, L.A.valT, L.A.diag);
+            L.g_omega = o.omega;
+            L.g_ready = true;
+        }
+        for (Csr *M : {&L.V, &L.W}) {
+            const bool made = f32 && !M->val32;
+            if (made) {
+                M->val32 = h->gamg_arena.get<float>(M->nnz);
+                M->valT32 = h->gamg_arena.get<float>(M->nnz);
+            }
+            if (M->val32 && (made || !fresh)) {
+                k_rop_f32<<<grid_n(M->nnz), kBlock, 0, st>>>(M->val, M->val32, M->nnz);
+                k_rop_f32<<<grid_n(M->nnz), kBlock, 0, st>>>(M->valT, M->valT32, M->nnz);
+            }
+        }
+        HIP_CHECK(hipGetLastError());
+    }
+}
+
 // new level coefficients: R's values follow at once (same omega)
 static void refresh_rop(ldu_t *h, hipStream_t st) {
+    for (Level &L : h->levels) L.g_ready = false;  // V and W: by the next cycle that uses them
     for (size_t l = 0; l + 1 < h->levels.size(); ++l)
         if ((h->levels[l].R.sptr || h->levels[l].Rc.rptr || h->levels[l].ah) &&
             h->levels[l].r_ready)
@@ -2604,6 +2978,7 @@ static void refresh_rop(ldu_t *h, hipStream_t st) {
 static VCtx make_ctx(ldu_t *h, const ldu_gamg_opts &o, bool tr, hipStream_t st) {
     ensure_work(h);
     ensure_rop(h, o, st);
+    ensure_gen(h, o, st);
     h->pool.trim();
     if (o.smoother == LDU_SMOOTH_GS2 && o.gs_inner >= 3) {
         for (auto &L : h->levels) {

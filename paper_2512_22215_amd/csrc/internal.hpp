@@ -333,6 +333,15 @@ struct Level {
     // on small levels (kUpRows) the up leg of the same cycles as one operator
     // over the stacked vector (r, e_c): e = U (r, e_c), a row per cell
     Csr Uc;
+    // small levels of the other Jacobi cycles (several pre-sweeps, or scaled
+    // corrections): rows of A with their Q entries behind (V; qptr: where they
+    // start), and the restriction of the residual over (r, e) (W)
+    Csr V, W;
+    int64_t *qptr = nullptr;
+    int64_t *w_src = nullptr, *w_src0 = nullptr;  // sources of W's entries, as R's
+    int32_t *w_srcn = nullptr;                    // (count 0: a member, value 1)
+    double g_omega = 0.0;
+    bool g_ready = false;                 // V's and W's values match the coefficients
     int64_t *r_src = nullptr;             // sources of R's entries, by entry in runs:
     int64_t *r_src0 = nullptr;            //   first source of each entry of R
     int32_t *r_srcn = nullptr;            //   and their count (source -1: a diagonal)
