@@ -1452,7 +1452,7 @@ __global__ void __launch_bounds__(kBlock)
 k_vc_rrestrict_csr(CsrView<T> R, XA x, T *__restrict__ rc,
                T *__restrict__ ec_first, const T *__restrict__ Dc, T omega,
                const DevScalars *ds) {
-    if (vc_skip(ds)) return;
+    const bool skip = vc_skip(ds);  // tested before the stores, off the chain of loads
     constexpr int RPW = kWave / G;
     const int lane = threadIdx.x & 63;
     const int g = lane % G;
@@ -1463,7 +1463,7 @@ k_vc_rrestrict_csr(CsrView<T> R, XA x, T *__restrict__ rc,
         // overlaps the row's gathers
         const T dc = (ec_first && g == 0 && c < R.n) ? Dc[c] : T(1);
         const T acc = csr_row_sum<G, NT>(R, c, g, x);
-        if (c < R.n && g == 0) {
+        if (c < R.n && g == 0 && !skip) {
             rc[c] = acc;
             if (ec_first) ec_first[c] = omega * acc / dc;
         }
@@ -1501,7 +1501,7 @@ template <int G, bool DOT, typename T>
 __global__ void __launch_bounds__(kBlock)
 k_vc_up_csr(CsrView<T> U, const T *__restrict__ r, const T *__restrict__ ec, T *__restrict__ e,
             const T *__restrict__ rdot, double *partials, const DevScalars *ds) {
-    if (vc_skip(ds)) return;
+    const bool skip = vc_skip(ds);  // tested before the stores, off the chain of loads
     constexpr int RPW = kWave / G;
     const int lane = threadIdx.x & 63;
     const int g = lane % G;
@@ -1510,11 +1510,12 @@ k_vc_up_csr(CsrView<T> U, const T *__restrict__ r, const T *__restrict__ ec, T *
     for_each_slice(chunks, [&](int64_t s) {
         const int64_t i = s * RPW + lane / G;
         const T z = csr_row_sum<G, false>(U, i, g, Stacked<T>{r, ec, U.n});
-        if (i < U.n && g == 0) {
+        if (i < U.n && g == 0 && !skip) {
             e[i] = z;
             if constexpr (DOT) acc[0] += (double)rdot[i] * (double)z;
         }
     });
+    if (skip) return;
     if constexpr (DOT) block_partials<1>(acc, partials);
 }
 
@@ -1744,7 +1745,7 @@ k_gen_sweep(CsrView<T> V, const int64_t *__restrict__ qptr, const T *__restrict_
             const T *__restrict__ r, const T *__restrict__ e, const T *__restrict__ ec,
             T *__restrict__ eo, T omega, const double *__restrict__ scale, int nblocks,
             const T *__restrict__ rdot, double *dots, const DevScalars *ds) {
-    if (vc_skip(ds)) return;
+    const bool skip = vc_skip(ds);  // tested before the stores, off the chain of loads
     T sc = T(1);
     if (UP && nblocks > 0) {
         double v[2];
@@ -1765,10 +1766,11 @@ k_gen_sweep(CsrView<T> V, const int64_t *__restrict__ qptr, const T *__restrict_
         if (own) {
             T z = ei + omega * (ri - sa) / di;
             if constexpr (UP) z = z + sc * sq;
-            eo[i] = z;
+            if (!skip) eo[i] = z;
             if constexpr (DOT) acc[0] += (double)rdot[i] * (double)z;
         }
     });
+    if (skip) return;
     if constexpr (DOT) block_partials<1>(acc, dots);
 }
 
@@ -1777,7 +1779,7 @@ template <int G, typename T>
 __global__ void __launch_bounds__(kBlock)
 k_gen_energy(CsrView<T> V, const int64_t *__restrict__ qptr, const T *__restrict__ e,
              const T *__restrict__ r, double *partials, const DevScalars *ds) {
-    if (vc_skip(ds)) return;
+    const bool skip = vc_skip(ds);
     constexpr int RPW = kWave / G;
     const int lane = threadIdx.x & 63;
     const int g = lane % G;
@@ -1794,6 +1796,7 @@ k_gen_energy(CsrView<T> V, const int64_t *__restrict__ qptr, const T *__restrict
             acc[1] += (double)ei * (double)sa;
         }
     });
+    if (skip) return;
     block_partials<2>(acc, partials);
 }
 
