@@ -378,59 +378,45 @@ __global__ void k_set_values(int64_t nf, const int64_t *slotU, const int64_t *sl
     }
 }
 
-// slot bases for 16-bit columns: the smallest column of each slot, and a
-// flag when some slot spans more than 65535 columns
-__device__ __forceinline__ void slot_span(const int64_t *sptr, const int32_t *pdeg,
-                                          const int32_t *tptr, const int32_t *otab, int64_t s,
-                                          int k, int64_t &e0, int &cnt, int64_t &bi) {
-    if (pdeg) {
-        const int32_t *ot = otab + tptr[s];
-        e0 = sptr[s] + ot[k];
-        cnt = ot[k + 1] - ot[k];
-        bi = tptr[s] + k;
-    } else {
-        e0 = sptr[s] + (int64_t)k * kWave;
-        cnt = kWave;
-        bi = (sptr[s] >> 6) + k;
+// smallest and largest value over a wave
+__device__ __forceinline__ void wave_range(int32_t &lo, int32_t &hi) {
+    for (int d = kWave / 2; d > 0; d >>= 1) {
+        const int32_t a = __shfl_xor(lo, d, kWave), b = __shfl_xor(hi, d, kWave);
+        lo = a < lo ? a : lo;
+        hi = b > hi ? b : hi;
     }
 }
 
-__global__ void k_col16_bases(int64_t S, const int64_t *sptr, const int32_t *pdeg,
-                              const int32_t *tptr, const int32_t *otab, const int32_t *col,
-                              int32_t *cbase, unsigned long long *narrow) {
-    for (int64_t s = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; s < S;
-         s += (int64_t)gridDim.x * blockDim.x) {
-        const int w = pdeg ? pdeg[s * kWave] : (int)((sptr[s + 1] - sptr[s]) >> 6);
-        for (int k = 0; k < w; ++k) {
-            int64_t e0, bi;
-            int cnt;
-            slot_span(sptr, pdeg, tptr, otab, s, k, e0, cnt, bi);
-            int32_t lo = col[e0], hi = col[e0];
-            for (int l = 1; l < cnt; ++l) {
-                const int32_t c = col[e0 + l];
-                lo = c < lo ? c : lo;
-                hi = c > hi ? c : hi;
-            }
+// 16-bit columns of plain slices: the smallest column of each slot (the 64
+// k-th entries of a slice) and every entry minus it.  One wave per slice, a
+// lane per entry: a thread per slice walked its 64 entries serially, 64
+// strided reads per wave at each step.  200^3: bases and offsets 861 ->
+// 214 us, a 121 x 117 x 130 box 215 -> 51.
+__global__ void __launch_bounds__(kBlock)
+k_col16_bases(int64_t S, const int64_t *__restrict__ sptr, const int32_t *__restrict__ col,
+              int32_t *cbase, int32_t *narrow) {
+    const int lane = threadIdx.x & 63;
+    bool fit = false;
+    for_each_slice(S, [&](int64_t s) {
+        const int64_t b0 = sptr[s], b1 = sptr[s + 1];
+        for (int64_t e = b0; e < b1; e += kWave) {
+            int32_t lo = col[e + lane], hi = lo;
+            wave_range(lo, hi);
             const bool fits = (int64_t)hi - lo <= 65535;
-            cbase[bi] = fits ? lo : -1;  // -1: this slot reads the 32-bit columns
-            if (fits) atomicAdd(narrow, 1ull);
+            if (lane == 0) cbase[e >> 6] = fits ? lo : -1;  // -1: reads the 32-bit columns
+            fit = fit || fits;
         }
-    }
+    });
+    if (lane == 0 && fit) *narrow = 1;  // one value from every wave
 }
 
-__global__ void k_col16_fill(int64_t S, const int64_t *sptr, const int32_t *pdeg,
-                             const int32_t *tptr, const int32_t *otab, const int32_t *col,
-                             const int32_t *cbase, uint16_t *c16) {
-    for (int64_t s = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; s < S;
-         s += (int64_t)gridDim.x * blockDim.x) {
-        const int w = pdeg ? pdeg[s * kWave] : (int)((sptr[s + 1] - sptr[s]) >> 6);
-        for (int k = 0; k < w; ++k) {
-            int64_t e0, bi;
-            int cnt;
-            slot_span(sptr, pdeg, tptr, otab, s, k, e0, cnt, bi);
-            const int32_t b = cbase[bi];
-            for (int l = 0; l < cnt; ++l) c16[e0 + l] = b >= 0 ? (uint16_t)(col[e0 + l] - b) : 0;
-        }
+__global__ void __launch_bounds__(kBlock)
+k_col16_fill(int64_t nnz, const int32_t *__restrict__ col, const int32_t *__restrict__ cbase,
+             uint16_t *__restrict__ c16) {
+    for (int64_t e = blockIdx.x * (int64_t)kBlock + threadIdx.x; e < nnz;
+         e += (int64_t)gridDim.x * kBlock) {
+        const int32_t b = cbase[e >> 6];
+        c16[e] = b >= 0 ? (uint16_t)(col[e] - b) : 0;
     }
 }
 
@@ -442,17 +428,15 @@ static void build_col16(Sell &A, int64_t nslots, Arena &ar, Arena &tmp, hipStrea
     // the narrower columns save (measured on the Galerkin levels)
     if (A.nnz == 0 || nslots == 0 || A.pdeg) return;
     int32_t *cbase = ar.get<int32_t>(nslots);
-    unsigned long long *narrow = tmp.get<unsigned long long>(1);
-    HIP_CHECK(hipMemsetAsync(narrow, 0, sizeof(unsigned long long), st));
-    k_col16_bases<<<grid_for(A.nslices), kBlock, 0, st>>>(A.nslices, A.sptr, A.pdeg, A.tptr,
-                                                         A.otab, A.col, cbase, narrow);
-    unsigned long long hnarrow = 0;
+    int32_t *narrow = tmp.get<int32_t>(1), hnarrow = 0;
+    HIP_CHECK(hipMemsetAsync(narrow, 0, sizeof(hnarrow), st));
+    k_col16_bases<<<stream_grid_slices(A.nslices), kBlock, 0, st>>>(A.nslices, A.sptr, A.col, cbase,
+                                                                 narrow);
     HIP_CHECK(hipMemcpyAsync(&hnarrow, narrow, sizeof(hnarrow), hipMemcpyDeviceToHost, st));
     HIP_CHECK(hipStreamSynchronize(st));
     if (hnarrow == 0) return;
     uint16_t *c16 = ar.get<uint16_t>(A.nnz);
-    k_col16_fill<<<grid_for(A.nslices), kBlock, 0, st>>>(A.nslices, A.sptr, A.pdeg, A.tptr,
-                                                        A.otab, A.col, cbase, c16);
+    k_col16_fill<<<grid_for(A.nnz), kBlock, 0, st>>>(A.nnz, A.col, cbase, c16);
     HIP_CHECK(hipGetLastError());
     A.c16 = c16;
     A.cbase = cbase;
