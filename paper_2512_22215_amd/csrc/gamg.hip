@@ -1606,6 +1606,60 @@ __global__ void k_up_fill(Sell A, Csr U, const int32_t *__restrict__ agg, double
     }
 }
 
+// ---------------------------------------------------------------- up leg of a large plain level
+// A large plain-slice level (form: scaled slices) has t = (I - omega A D^-1) r
+// from its down leg.  Its up leg to the end of the first post-sweep is
+//   e = S r + (I - omega D^-1 A) P e_c,   S r = omega D^-1 (r + t),
+// that is  e_i = c_i + omega (r_i + t_i - (A P e_c)_i) / D_i,  c = P e_c:  a
+// product with A's values that gathers from the coarse vector (AC: A's slices
+// with their columns mapped to aggregates).  The correction (r, D, the map and
+// e_c in, e out) and the sweep after it (A, e, r, D in) were two passes.
+// 200^3 in FP64: correction and sweep 44 + 137 us, this kernel 160 (columns
+// mapped in the kernel, e_c[agg[j]], chain two gathers: 204); CG + V-cycle
+// 124.7 -> 123.5 ms there, 15.3 -> 14.8 ms on 100^3.
+template <bool DOT, typename T>
+__global__ void __launch_bounds__(kBlock)
+k_vc_up_slices(SellView<T> AC, const int32_t *__restrict__ agg, const T *__restrict__ r,
+               const T *__restrict__ t, const T *__restrict__ ec, T *__restrict__ e, T omega,
+               double *partials, const DevScalars *ds) {
+    if (vc_skip(ds)) return;
+    const int lane = threadIdx.x & 63;
+    double acc[1] = {0.0};
+    for_each_slice<product_cap<false, T>()>(AC.nslices, [&](int64_t s) {
+        const int64_t i = s * kWave + lane;
+        if (i < AC.n) {
+            const T ci = ec[agg[i]];
+            const T di = vld<DOT>(AC.diag + i);
+            T y = di * ci;
+            row_entries<false, 8>(AC, s, lane, Direct<T>{ec},
+                                  [&](int32_t, T v, T xv) { y = y + v * xv; });
+            // with DOT the iteration reads neither r nor D before its CG product
+            const T ri = vld<DOT>(r + i);
+            const T zi = ci + omega * (ri + vld<true>(t + i) - y) / di;
+            e[i] = zi;
+            if constexpr (DOT) acc[0] += (double)ri * (double)zi;
+        }
+    });
+    if constexpr (DOT) block_partials<1>(acc, partials);
+}
+
+template <typename T>
+static int launch_up_slices(const Level &L, SellView<T> A, const T *r, const T *t, const T *ec,
+                            T *e, T omega, bool dot, double *partials, const DevScalars *ds,
+                            hipStream_t st) {
+    A.c16 = L.ac16;
+    A.cbase = L.acbase;
+    A.col = L.ac32;
+    int G = stream_grid_slices(A.nslices);
+    // with a dot product, blocks past the products' cap would only add zeros
+    if (dot && sizeof(T) == sizeof(double)) G = std::min(G, kPlainF64ProductBlocks);
+    if (dot)
+        k_vc_up_slices<true, T><<<G, kBlock, 0, st>>>(A, L.agg, r, t, ec, e, omega, partials, ds);
+    else
+        k_vc_up_slices<false, T><<<G, kBlock, 0, st>>>(A, L.agg, r, t, ec, e, omega, partials, ds);
+    return G;
+}
+
 // f(std::integral_constant<int, lanes per row>)
 template <class F>
 static void with_group(int group, F &&f) {
@@ -2633,21 +2687,25 @@ static T *vcycle(const VCtx &c, size_t l, const T *r, const T *rdot, int *dotted
     const bool rop = rop_level<T>(c, l);
     // small levels: first sweep, correction and first post-sweep as U (r, e_c)
     const bool up = up_level<T>(c, l);
+    // scaled slices: the same from the down leg's t (a dot product is the one
+    // with r itself; a finer level's correction rides on a sweep)
+    const bool up_slices = rop && L.ah && c.o->n_post > 0 &&
+                           (c.o->n_post > 1 || ((!rdot || rdot == r) && !fc.e));
     // without correction scaling, on levels small enough to be bound by launch
     // latency, the coarse level applies e += P e_c itself (a scatter through
     // the member lists: on large levels the gather form of k_vc_correct moves
     // fewer bytes)
-    const bool fuse_corr = takes_correction<T>(c, l);
+    const bool fuse_corr = takes_correction<T>(c, l) && !up_slices;
     // with the one-pass down leg nothing reads the first sweep before the
     // correction, which then forms it itself
-    const bool defer_first = rop && !e_ready && !fuse_corr;
+    const bool defer_first = rop && !e_ready && !fuse_corr && !up_slices;
     if (gs) {  // forward two-stage Gauss-Seidel sweeps, the first from e = 0
         if (c.o->n_pre == 0) k_vc_zero<T><<<G, kBlock, 0, st>>>(L.n, S, e, h->dev);
         for (int k = 0; k < c.o->n_pre; ++k)
             gs_sweep<T>(A, r, e, t, e2, w1, k == 0, false, c.o->gs_inner, h->dev, G, st);
     } else {
         if (c.o->n_pre == 0) k_vc_zero<T><<<G, kBlock, 0, st>>>(L.n, S, e, h->dev);
-        else if (!e_ready && !defer_first && !up)
+        else if (!e_ready && !defer_first && !up && !up_slices)
             k_vc_first<T><<<G, kBlock, 0, st>>>(L.n, S, r, A.diag, e, omega, h->dev);
         for (int k = 1; k < c.o->n_pre; ++k) {
             launch_jacobi<T>(A, r, e, e2, omega, nullptr, nullptr, {}, h->dev, G, st);
@@ -2701,6 +2759,12 @@ static T *vcycle(const VCtx &c, size_t l, const T *r, const T *rdot, int *dotted
         const int blocks = launch_up_csr<T>(upview<T>(L, c.tr), r, ec, e, last ? rdot : nullptr,
                                             h->partials, h->dev, st);
         if (last && rdot && dotted) *dotted = blocks;
+        post = 1;
+    } else if (up_slices) {
+        const bool dot = c.o->n_post == 1 && rdot;
+        const int blocks = launch_up_slices<T>(L, A, r, t, ec, e, omega, dot, h->partials, h->dev,
+                                               st);
+        if (dot && dotted) *dotted = blocks;
         post = 1;
     } else if (!done_corr)
         k_vc_correct<T><<<G, kBlock, 0, st>>>(L.n, S, ec, L.agg, e, h->partials, scale_blocks,
@@ -2775,6 +2839,9 @@ static void rop_structure(ldu_t *h, size_t l, hipStream_t st) {
     if (!L.A.pdeg && C.n > kCsrMaxRows) {  // a large plain-slice level: Ah over its own slices
         L.ah = h->gamg_arena.get<double>(L.A.nnz);
         L.ahT = h->gamg_arena.get<double>(L.A.nnz);
+        Arena tmp(&h->pool);
+        aggregate_columns(L, h->gamg_arena, tmp, st);
+        HIP_CHECK(hipStreamSynchronize(st));  // tmp is released after this point
         L.r_ready = false;
         return;
     }

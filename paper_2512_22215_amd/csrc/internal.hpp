@@ -329,6 +329,10 @@ struct Level {
     // with the values -omega a_ij / D_j stored at A's positions (ah; ahT the
     // same for A^T; padding 0), then the member sums of t
     double *ah = nullptr, *ahT = nullptr;
+    // scaled slices: A's columns mapped to aggregates, for the up leg's
+    // A P e_c (ac32 only when some slot is too wide for 16 bits)
+    uint16_t *ac16 = nullptr;
+    int32_t *acbase = nullptr, *ac32 = nullptr;
     float *ah32 = nullptr, *ahT32 = nullptr;
     // on small levels (kUpRows) the up leg of the same cycles as one operator
     // over the stacked vector (r, e_c): e = U (r, e_c), a row per cell
@@ -417,6 +421,8 @@ void set_level_values(Level &L, hipStream_t st);   // face values -> SELL values
 // returns the number of slots
 int64_t layout_rows(Sell &A, int32_t n, const int32_t *deg, int64_t nnz, Arena &ar, Arena &tmp,
                     hipStream_t st);
+// the columns of a level's plain slices mapped through its aggregate map
+void aggregate_columns(Level &L, Arena &ar, Arena &tmp, hipStream_t st);
 // A with its rows in the order `order` (cell of each position; place: position
 // of each cell) and its columns renumbered, each row in ascending column order
 void build_renumbered(const Sell &A, int64_t nf, const int32_t *order, const int32_t *place,

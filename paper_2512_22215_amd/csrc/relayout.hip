@@ -442,6 +442,55 @@ static void build_col16(Sell &A, int64_t nslots, Arena &ar, Arena &tmp, hipStrea
     A.cbase = cbase;
 }
 
+// The aggregate map composed with plain slices' columns, agg[col], as 16-bit
+// columns of the same slots (positions past the last row are not read, and do
+// not widen their slot).
+__global__ void __launch_bounds__(kBlock)
+k_agg_columns(int64_t S, int64_t n, const int64_t *__restrict__ sptr,
+              const int32_t *__restrict__ col, const int32_t *__restrict__ agg, int32_t *cbase,
+              uint16_t *__restrict__ c16, int32_t *wide) {
+    const int lane = threadIdx.x & 63;
+    bool over = false;
+    for_each_slice(S, [&](int64_t s) {
+        const int64_t b0 = sptr[s], b1 = sptr[s + 1];
+        const bool row = s * kWave + lane < n;
+        for (int64_t e = b0; e < b1; e += kWave) {
+            const int32_t c = row ? agg[col[e + lane]] : 0;
+            int32_t lo = row ? c : INT32_MAX, hi = row ? c : 0;
+            wave_range(lo, hi);
+            const bool fits = hi - lo <= 65535;
+            if (lane == 0) cbase[e >> 6] = fits ? lo : -1;
+            c16[e + lane] = fits && row ? (uint16_t)(c - lo) : 0;
+            over = over || !fits;
+        }
+    });
+    if (lane == 0 && over) *wide = 1;
+}
+
+__global__ void k_agg_columns32(int64_t nnz, const int32_t *col, const int32_t *agg,
+                                int32_t *out) {
+    for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < nnz;
+         e += (int64_t)gridDim.x * blockDim.x)
+        out[e] = agg[col[e]];
+}
+
+void aggregate_columns(Level &L, Arena &ar, Arena &tmp, hipStream_t st) {
+    const Sell &A = L.A;
+    L.ac32 = nullptr;
+    L.ac16 = ar.get<uint16_t>(A.nnz);
+    L.acbase = ar.get<int32_t>(A.nnz / kWave);
+    int32_t *wide = tmp.get<int32_t>(1), hwide = 0;
+    HIP_CHECK(hipMemsetAsync(wide, 0, sizeof(hwide), st));
+    k_agg_columns<<<stream_grid_slices(A.nslices), kBlock, 0, st>>>(
+        A.nslices, A.n, A.sptr, A.col, L.agg, L.acbase, L.ac16, wide);
+    HIP_CHECK(hipMemcpyAsync(&hwide, wide, sizeof(hwide), hipMemcpyDeviceToHost, st));
+    HIP_CHECK(hipStreamSynchronize(st));
+    if (hwide == 0) return;
+    L.ac32 = ar.get<int32_t>(A.nnz);  // read by the slots that are too wide
+    k_agg_columns32<<<grid_for(A.nnz), kBlock, 0, st>>>(A.nnz, A.col, L.agg, L.ac32);
+    HIP_CHECK(hipGetLastError());
+}
+
 __global__ void k_to_f32(const double *a, float *b, int64_t n) {
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
          i += (int64_t)gridDim.x * blockDim.x)
