@@ -41,6 +41,26 @@ __device__ __forceinline__ SliceWalkRange slice_walk_range(int64_t S, int G) {
     return r;
 }
 
+// Indexes [0, n) in units of `per`, a unit per block: with a grid of a multiple
+// of 8 blocks (at least 64) block b works in XCD b % 8's contiguous eighth (of
+// whole units), so that neighbouring rows, faces and aggregates share that
+// XCD's L2.  Set-up and refresh of the levels read their neighbours by index:
+// on a 121 x 117 x 130 box set-up and solve 57.6 -> 56.1 ms (the coarse face
+// lists 2.4 -> 1.7 ms, the coarse values 2.3 -> 1.9), results unchanged.
+struct GridRange {
+    int64_t begin, end, step;
+    bool once;
+};
+__device__ __forceinline__ GridRange grid_range(int64_t n, int per) {
+    const int G = gridDim.x, nx = (G >= 64 && (G & 7) == 0) ? 8 : 1;
+    const int64_t units = (n + per - 1) / per, R = (units + nx - 1) / nx * per;
+    const int64_t lo = (blockIdx.x % nx) * R, hi = lo + R < n ? lo + R : n;
+    return {lo + (int64_t)(blockIdx.x / nx) * per, hi, (int64_t)(G / nx) * per, true};
+}
+#define GRID_STRIDE(i, n)                                                            \
+    for (GridRange gr_ = grid_range(n, blockDim.x); gr_.once; gr_.once = false)      \
+        for (int64_t i = gr_.begin + threadIdx.x; i < gr_.end; i += gr_.step)
+
 // true once the solve has stopped (done) or the current inner solve of a
 // mixed-precision solve has (inner_done, always 0 in FP64 solves): the
 // kernels of an iteration then return at once.  Both flags are read unconditionally (bitwise or), so

@@ -60,12 +60,8 @@ __device__ __forceinline__ bool better(double w1, uint64_t h1, int32_t j1, doubl
 static unsigned grid_n(int64_t n) {
     int64_t g = (n + kBlock - 1) / kBlock;
     g = g > 8192 ? 8192 : (g < 1 ? 1 : g);
-    return (unsigned)g;
+    return (unsigned)(g >= 64 ? (g + 7) & ~int64_t(7) : g);
 }
-#define GRID_STRIDE(i, n)                                                         \
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < (n); \
-         i += (int64_t)gridDim.x * blockDim.x)
-
 // best neighbour of row i among those whose matched state equals want_matched
 __device__ int32_t best_neighbour(const Sell &A, int32_t i, const int32_t *partner,
                                   bool want_matched) {
@@ -291,9 +287,9 @@ __device__ int coarse_row_group(const Sell &A, const int32_t *agg, const int32_t
 
 // the group's rows, the same number of steps for every lane of a wave
 #define ROW_GROUPS(a, n)                                                                  \
-    for (int64_t a0_ = blockIdx.x * (int64_t)kRowGroups; a0_ < (n);                       \
-         a0_ += (int64_t)gridDim.x * kRowGroups)                                          \
-        if (const int64_t a = a0_ + threadIdx.x / kRowLanes; true)
+    for (GridRange gr_ = grid_range(n, kRowGroups); gr_.once; gr_.once = false)            \
+        for (int64_t a0_ = gr_.begin; a0_ < gr_.end; a0_ += gr_.step)                      \
+            if (const int64_t a = a0_ + threadIdx.x / kRowLanes; true)
 
 __global__ void __launch_bounds__(kBlock)
 k_coarse_count(Sell A, int32_t nc, const int32_t *agg, const int32_t *start,
@@ -1155,8 +1151,8 @@ k_rop_gather(int32_t nc, const int32_t *__restrict__ start, const int32_t *__res
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const uint64_t below = (uint64_t(1) << lane) - 1;
     int32_t *pc = sc[wv], *psrc = ss[wv];
-    for (int64_t c = blockIdx.x * (int64_t)kWavesPerBlock + wv; c < nc;
-         c += (int64_t)gridDim.x * kWavesPerBlock) {
+    const GridRange gr = grid_range(nc, kWavesPerBlock);
+    for (int64_t c = gr.begin + wv; c < gr.end; c += gr.step) {
         const int64_t o = tstart[c];
         const int m = (int)(tstart[c + 1] - o);
         const bool lds = m <= kGatherPairs;
@@ -1310,8 +1306,7 @@ __global__ void k_rop_values(int64_t nnz, M R, const int64_t *__restrict__ rs0,
                              const int32_t *__restrict__ rsn, const int64_t *__restrict__ src,
                              const double *__restrict__ aval, const double *__restrict__ avalT,
                              const double *__restrict__ D, double omega) {
-    for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < nnz;
-         e += (int64_t)gridDim.x * blockDim.x) {
+    GRID_STRIDE(e, nnz) {
         const double dj = D[R.col[e]];
         double v = 0.0, vT = 0.0;
         for (int64_t k = rs0[e]; k < rs0[e] + rsn[e]; ++k) {
@@ -1330,8 +1325,7 @@ __global__ void k_rop_values(int64_t nnz, M R, const int64_t *__restrict__ rs0,
 }
 
 __global__ void k_rop_f32(const double *a, float *b, int64_t n) {
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
-         i += (int64_t)gridDim.x * blockDim.x)
+    GRID_STRIDE(i, n)
         b[i] = (float)a[i];
 }
 
@@ -1341,8 +1335,7 @@ __global__ void k_ahat_values(int64_t nnz, const int32_t *__restrict__ col,
                               const double *__restrict__ val, const double *__restrict__ valT,
                               const double *__restrict__ D, double omega, double *__restrict__ ah,
                               double *__restrict__ ahT) {
-    for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < nnz;
-         e += (int64_t)gridDim.x * blockDim.x) {
+    GRID_STRIDE(e, nnz) {
         const double dj = D[col[e]];
         ah[e] = (-omega * val[e]) / dj;
         ahT[e] = (-omega * valT[e]) / dj;
@@ -1922,8 +1915,7 @@ __global__ void k_w_values(int64_t nnz, int32_t n, Csr W, const int64_t *__restr
                            const int32_t *__restrict__ wsn, const int64_t *__restrict__ src,
                            const double *__restrict__ aval, const double *__restrict__ avalT,
                            const double *__restrict__ D) {
-    for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < nnz;
-         e += (int64_t)gridDim.x * blockDim.x) {
+    GRID_STRIDE(e, nnz) {
         if (wsn[e] == 0) continue;  // a member
         const double dj = D[W.col[e] - n];
         double v = 0.0, vT = 0.0;

@@ -110,8 +110,7 @@ void scan_counts_i32(const int32_t *cnt, int32_t *out, int64_t n, Arena &tmp,
 // ---------------------------------------------------------------- checks
 __global__ void k_validate(int32_t n, int64_t nf, const int32_t *own, const int32_t *nb,
                            int *flag) {
-    for (int64_t f = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; f < nf;
-         f += (int64_t)gridDim.x * blockDim.x) {
+    GRID_STRIDE(f, nf) {
         const int32_t o = own[f], b = nb[f];
         bool bad = o < 0 || o >= b || b >= n;
         if (f > 0) {
@@ -123,14 +122,14 @@ __global__ void k_validate(int32_t n, int64_t nf, const int32_t *own, const int3
 }
 
 __global__ void k_check_finite(const double *a, int64_t n, int *flag) {
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
-         i += (int64_t)gridDim.x * blockDim.x)
+    GRID_STRIDE(i, n)
         if (!isfinite(a[i])) atomicOr(flag, 2);
 }
 
 static unsigned grid_for(int64_t n) {
     int64_t g = (n + kBlock - 1) / kBlock;
     if (g > 8192) g = 8192;
+    if (g >= 64) g = (g + 7) & ~int64_t(7);
     return (unsigned)(g < 1 ? 1 : g);
 }
 
@@ -153,22 +152,19 @@ __global__ void k_own_start(int32_t n, int64_t nf, const int32_t *own, int64_t *
 }
 
 __global__ void k_count_lower(int64_t nf, const int32_t *nb, int32_t *cntL) {
-    for (int64_t f = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; f < nf;
-         f += (int64_t)gridDim.x * blockDim.x)
+    GRID_STRIDE(f, nf)
         atomicAdd(&cntL[nb[f]], 1);
 }
 
 __global__ void k_degree(int32_t n, const int64_t *ownStart, const int32_t *cntL, int32_t *deg) {
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
-         i += (int64_t)gridDim.x * blockDim.x)
+    GRID_STRIDE(i, n)
         deg[i] = cntL[i] + (int32_t)(ownStart[i + 1] - ownStart[i]);
 }
 
 // entries of slice s = 64 x (longest row stored in the slice)
 __global__ void k_slice_entries(int32_t n, int64_t S, const int32_t *deg, const int32_t *perm,
                                 int64_t *entries) {
-    for (int64_t s = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; s < S;
-         s += (int64_t)gridDim.x * blockDim.x) {
+    GRID_STRIDE(s, S) {
         int64_t w = 0;
         for (int l = 0; l < kWave; ++l) {
             const int64_t p = s * kWave + l;
@@ -204,8 +200,7 @@ __global__ void k_slice_sort(int32_t n, int64_t S, const int32_t *deg, int32_t *
 // entries of a compressed slice (sum of its row lengths) and the length of
 // its offset table (longest row + 1)
 __global__ void k_slice_sizes(int64_t S, const int32_t *pdeg, int64_t *entries, int32_t *tlen) {
-    for (int64_t s = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; s < S;
-         s += (int64_t)gridDim.x * blockDim.x) {
+    GRID_STRIDE(s, S) {
         int64_t e = 0;
         for (int l = 0; l < kWave; ++l) e += pdeg[s * kWave + l];
         entries[s] = e;
@@ -215,8 +210,7 @@ __global__ void k_slice_sizes(int64_t S, const int32_t *pdeg, int64_t *entries, 
 
 // otab[tptr[s] + k] = entries of slice s in its columns 0..k-1
 __global__ void k_slice_table(int64_t S, const int32_t *pdeg, const int32_t *tptr, int32_t *otab) {
-    for (int64_t s = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; s < S;
-         s += (int64_t)gridDim.x * blockDim.x) {
+    GRID_STRIDE(s, S) {
         const int w = pdeg[s * kWave];
         int32_t off = 0;
         for (int k = 0; k <= w; ++k) {
@@ -233,8 +227,7 @@ __global__ void k_slice_table(int64_t S, const int32_t *pdeg, const int32_t *tpt
 __global__ void __launch_bounds__(kBlock) k_max_i32(const int32_t *a, int64_t n, int32_t *out) {
     __shared__ int32_t sm[kBlock];
     int32_t m = 0;
-    for (int64_t i = blockIdx.x * (int64_t)kBlock + threadIdx.x; i < n;
-         i += (int64_t)gridDim.x * kBlock)
+    GRID_STRIDE(i, n)
         m = a[i] > m ? a[i] : m;
     sm[threadIdx.x] = m;
     __syncthreads();
@@ -247,8 +240,7 @@ __global__ void __launch_bounds__(kBlock) k_max_i32(const int32_t *a, int64_t n,
 }
 
 __global__ void k_fill_i32(int32_t *a, int64_t n, int32_t v) {
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
-         i += (int64_t)gridDim.x * blockDim.x)
+    GRID_STRIDE(i, n)
         a[i] = v;
 }
 
@@ -267,8 +259,7 @@ struct Slots {
 __global__ void k_fill_upper(int64_t nf, const int32_t *own, const int32_t *nb,
                              const int64_t *ownStart, const int32_t *cntL, Slots slot,
                              int32_t *col, int64_t *slotU) {
-    for (int64_t f = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; f < nf;
-         f += (int64_t)gridDim.x * blockDim.x) {
+    GRID_STRIDE(f, nf) {
         const int32_t i = own[f];
         const int64_t pos = slot(i, cntL[i] + (f - ownStart[i]));
         col[pos] = nb[f];
@@ -280,8 +271,7 @@ __global__ void k_fill_upper(int64_t nf, const int32_t *own, const int32_t *nb,
 // orders them by column, which makes the final layout deterministic
 __global__ void k_fill_lower(int64_t nf, const int32_t *own, const int32_t *nb, Slots slot,
                              int32_t *cursor, int32_t *col, int64_t *faceAt) {
-    for (int64_t f = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; f < nf;
-         f += (int64_t)gridDim.x * blockDim.x) {
+    GRID_STRIDE(f, nf) {
         const int32_t j = nb[f];
         const int k = atomicAdd(&cursor[j], 1);
         const int64_t pos = slot(j, k);
@@ -296,8 +286,7 @@ constexpr int kSortRegs = 8;
 
 __global__ void k_sort_lower(int32_t n, Slots slot, const int32_t *cntL, int32_t *col,
                              int64_t *faceAt, int64_t *slotL) {
-    for (int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; j < n;
-         j += (int64_t)gridDim.x * blockDim.x) {
+    GRID_STRIDE(j, n) {
         const int m = cntL[j];
         if (m <= kSortRegs) {
             int64_t pos[kSortRegs], f[kSortRegs];
@@ -350,8 +339,7 @@ __global__ void k_sort_lower(int32_t n, Slots slot, const int32_t *cntL, int32_t
 __global__ void k_fill_pad(int32_t n, int64_t S, const int64_t *sptr, const int32_t *deg,
                            int32_t *col, double *val, double *valT) {
     const int64_t rows = S * kWave;
-    for (int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; p < rows;
-         p += (int64_t)gridDim.x * blockDim.x) {
+    GRID_STRIDE(p, rows) {
         const int64_t s = p >> 6;
         const int64_t w = (sptr[s + 1] - sptr[s]) >> 6;
         const int64_t d = (p < n) ? deg[p] : 0;
@@ -367,8 +355,7 @@ __global__ void k_fill_pad(int32_t n, int64_t S, const int64_t *sptr, const int3
 __global__ void k_set_values(int64_t nf, const int64_t *slotU, const int64_t *slotL,
                              const double *upper, const double *lower, double *val,
                              double *valT) {
-    for (int64_t f = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; f < nf;
-         f += (int64_t)gridDim.x * blockDim.x) {
+    GRID_STRIDE(f, nf) {
         const double u = upper[f], l = lower[f];
         const int64_t pu = slotU[f], pl = slotL[f];
         val[pu] = u;
@@ -413,8 +400,7 @@ k_col16_bases(int64_t S, const int64_t *__restrict__ sptr, const int32_t *__rest
 __global__ void __launch_bounds__(kBlock)
 k_col16_fill(int64_t nnz, const int32_t *__restrict__ col, const int32_t *__restrict__ cbase,
              uint16_t *__restrict__ c16) {
-    for (int64_t e = blockIdx.x * (int64_t)kBlock + threadIdx.x; e < nnz;
-         e += (int64_t)gridDim.x * kBlock) {
+    GRID_STRIDE(e, nnz) {
         const int32_t b = cbase[e >> 6];
         c16[e] = b >= 0 ? (uint16_t)(col[e] - b) : 0;
     }
@@ -469,8 +455,7 @@ k_agg_columns(int64_t S, int64_t n, const int64_t *__restrict__ sptr,
 
 __global__ void k_agg_columns32(int64_t nnz, const int32_t *col, const int32_t *agg,
                                 int32_t *out) {
-    for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < nnz;
-         e += (int64_t)gridDim.x * blockDim.x)
+    GRID_STRIDE(e, nnz)
         out[e] = agg[col[e]];
 }
 
@@ -492,8 +477,7 @@ void aggregate_columns(Level &L, Arena &ar, Arena &tmp, hipStream_t st) {
 }
 
 __global__ void k_to_f32(const double *a, float *b, int64_t n) {
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
-         i += (int64_t)gridDim.x * blockDim.x)
+    GRID_STRIDE(i, n)
         b[i] = (float)a[i];
 }
 
@@ -636,8 +620,7 @@ void build_sliced_rows(Sell &A, int32_t n, const int32_t *deg, Arena &ar, hipStr
 // ---------------------------------------------------------------- renumbering
 // true row lengths (without padding) in the new order
 __global__ void k_rn_degree(Sell A, const int32_t *order, int32_t *deg) {
-    for (int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; p < A.n;
-         p += (int64_t)gridDim.x * blockDim.x) {
+    GRID_STRIDE(p, A.n) {
         const int32_t i = order[p];
         const int64_t ps = A.iperm ? (int64_t)A.iperm[i] : (int64_t)i;
         const int w = row_len(A, ps);
@@ -656,8 +639,7 @@ constexpr int kRnRegs = 24;
 __global__ void __launch_bounds__(kBlock)
 k_rn_fill(Sell A, const int32_t *order, const int32_t *place, Slots slot, int32_t *col,
           int32_t *src) {
-    for (int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; p < A.n;
-         p += (int64_t)gridDim.x * blockDim.x) {
+    GRID_STRIDE(p, A.n) {
         const int32_t i = order[p];
         const int64_t ps = A.iperm ? (int64_t)A.iperm[i] : (int64_t)i;
         const int w = row_len(A, ps);
@@ -701,8 +683,7 @@ k_rn_fill(Sell A, const int32_t *order, const int32_t *place, Slots slot, int32_
 __global__ void k_rn_values(int64_t nnz, const int32_t *__restrict__ src,
                             const double *__restrict__ val, const double *__restrict__ valT,
                             double *__restrict__ v, double *__restrict__ vT) {
-    for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < nnz;
-         e += (int64_t)gridDim.x * blockDim.x) {
+    GRID_STRIDE(e, nnz) {
         const int32_t q = src[e];
         v[e] = q >= 0 ? val[q] : 0.0;
         vT[e] = q >= 0 ? valT[q] : 0.0;
@@ -711,14 +692,12 @@ __global__ void k_rn_values(int64_t nnz, const int32_t *__restrict__ src,
 
 __global__ void k_gather_cells(const double *__restrict__ a, const int32_t *__restrict__ order,
                                double *__restrict__ out, int64_t n) {
-    for (int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; p < n;
-         p += (int64_t)gridDim.x * blockDim.x)
+    GRID_STRIDE(p, n)
         out[p] = a[order[p]];
 }
 __global__ void k_scatter_cells(const double *__restrict__ a, const int32_t *__restrict__ order,
                                 double *__restrict__ out, int64_t n) {
-    for (int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; p < n;
-         p += (int64_t)gridDim.x * blockDim.x)
+    GRID_STRIDE(p, n)
         out[order[p]] = a[p];
 }
 void gather_cells(const double *a, const int32_t *order, double *out, int64_t n, hipStream_t st) {
@@ -769,8 +748,7 @@ __global__ void __launch_bounds__(kBlock)
 k_face_span(int64_t nf, const int32_t *__restrict__ own, const int32_t *__restrict__ nb,
             unsigned long long *out) {
     unsigned long long s = 0;
-    for (int64_t f = blockIdx.x * (int64_t)kBlock + threadIdx.x; f < nf;
-         f += (int64_t)gridDim.x * kBlock)
+    GRID_STRIDE(f, nf)
         s += (unsigned long long)(nb[f] - own[f]);
     for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off);
     if ((threadIdx.x & 63) == 0) atomicAdd(out, s);
