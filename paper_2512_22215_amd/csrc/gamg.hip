@@ -393,7 +393,9 @@ __global__ void k_coarse_celllist(int32_t nc, const int32_t *agg, const int32_t 
 }
 
 // coarse values from the recorded lists (the sums of k_coarse_values and
-// k_coarse_diag, term for term)
+// k_coarse_diag, term for term); a few terms' loads are in flight at a time, a
+// small level's rows being one chain of loads each.  Six levels of a 151^3
+// merged hierarchy: 503 -> 409 us a refresh.
 __global__ void k_coarse_values_list(int64_t ncf, const int64_t *__restrict__ cfs,
                                      const int32_t *__restrict__ cff,
                                      const double *__restrict__ fup,
@@ -401,10 +403,24 @@ __global__ void k_coarse_values_list(int64_t ncf, const int64_t *__restrict__ cf
                                      double *__restrict__ clo) {
     GRID_STRIDE(c, ncf) {
         double up = 0.0, lo = 0.0;
-        for (int64_t k = cfs[c]; k < cfs[c + 1]; ++k) {
-            const int32_t g = cff[k];
-            if (g >= 0) { up += fup[g]; lo += flo[g]; }
-            else { up += flo[~g]; lo += fup[~g]; }
+        const int64_t k1 = cfs[c + 1];
+        for (int64_t k = cfs[c]; k < k1; k += 4) {
+            int32_t g[4];
+            double u[4], l[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) g[q] = k + q < k1 ? cff[k + q] : 0;
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                if (k + q < k1) {
+                    u[q] = g[q] >= 0 ? fup[g[q]] : flo[~g[q]];
+                    l[q] = g[q] >= 0 ? flo[g[q]] : fup[~g[q]];
+                }
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                if (k + q < k1) {
+                    up += u[q];
+                    lo += l[q];
+                }
         }
         cup[c] = up;
         clo[c] = lo;
@@ -419,10 +435,31 @@ __global__ void k_coarse_diag_list(int32_t nc, const int32_t *__restrict__ start
                                    const double *__restrict__ flo, double *__restrict__ cdiag) {
     GRID_STRIDE(a, nc) {
         double d = 0.0;
-        for (int32_t k = start[a]; k < start[a + 1]; ++k) d += fdiag[cells[k]];
-        for (int64_t k = cis[a]; k < cis[a + 1]; ++k) {
-            const int32_t f = cif[k];
-            d += (fup[f] + flo[f]);
+        const int32_t k1 = start[a + 1];
+        const int64_t m0 = cis[a], m1 = cis[a + 1];
+        for (int32_t k = start[a]; k < k1; k += 8) {
+            int32_t i[8];
+            double x[8];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) i[q] = k + q < k1 ? cells[k + q] : 0;
+#pragma unroll
+            for (int q = 0; q < 8; ++q)
+                if (k + q < k1) x[q] = fdiag[i[q]];
+#pragma unroll
+            for (int q = 0; q < 8; ++q)
+                if (k + q < k1) d += x[q];
+        }
+        for (int64_t k = m0; k < m1; k += 8) {
+            int32_t f[8];
+            double x[8];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) f[q] = k + q < m1 ? cif[k + q] : 0;
+#pragma unroll
+            for (int q = 0; q < 8; ++q)
+                if (k + q < m1) x[q] = fup[f[q]] + flo[f[q]];
+#pragma unroll
+            for (int q = 0; q < 8; ++q)
+                if (k + q < m1) d += x[q];
         }
         cdiag[a] = d;
     }
@@ -1300,24 +1337,33 @@ __global__ void k_widen(int32_t n, const int32_t *__restrict__ a, int64_t *__res
 
 // values of R (and of its A^T form) from the level's coefficients: each entry
 // sums its sources in member order, (1 - omega) for a diagonal and
-// -omega a / D_j for an entry a of column j
+// -omega a / D_j for an entry a of column j.  Bound by the scattered reads of
+// a; four sources are in flight (430,000 fine rows, merged: 449 -> 343 us)
 template <class M>
 __global__ void k_rop_values(int64_t nnz, M R, const int64_t *__restrict__ rs0,
                              const int32_t *__restrict__ rsn, const int64_t *__restrict__ src,
                              const double *__restrict__ aval, const double *__restrict__ avalT,
                              const double *__restrict__ D, double omega) {
     GRID_STRIDE(e, nnz) {
+        const int64_t k0 = rs0[e], k1 = k0 + rsn[e];
         const double dj = D[R.col[e]];
         double v = 0.0, vT = 0.0;
-        for (int64_t k = rs0[e]; k < rs0[e] + rsn[e]; ++k) {
-            const int64_t q = src[k];
-            if (q < 0) {
-                v = v + (1.0 - omega);
-                vT = vT + (1.0 - omega);
-            } else {
-                v = v + (-omega * aval[q]) / dj;
-                vT = vT + (-omega * avalT[q]) / dj;
+        for (int64_t k = k0; k < k1; k += 4) {
+            int64_t q[4];
+            double a[4], t[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) q[u] = k + u < k1 ? src[k + u] : -1;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                a[u] = q[u] < 0 ? 0.0 : aval[q[u]];
+                t[u] = q[u] < 0 ? 0.0 : avalT[q[u]];
             }
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (k + u < k1) {
+                    v = v + (q[u] < 0 ? 1.0 - omega : (-omega * a[u]) / dj);
+                    vT = vT + (q[u] < 0 ? 1.0 - omega : (-omega * t[u]) / dj);
+                }
         }
         R.val[e] = v;
         R.valT[e] = vT;
@@ -1564,37 +1610,125 @@ __global__ void k_up_count(Sell A, const int32_t *__restrict__ agg, int64_t *cnt
     }
 }
 
-// U's columns and values (val: A, valT: A^T) for this omega
-__global__ void k_up_fill(Sell A, Csr U, const int32_t *__restrict__ agg, double omega) {
-    GRID_STRIDE(i, A.n) {
+// row i of U by one lane
+__device__ void up_row(const Sell &A, const Csr &U, const int32_t *agg, double omega, int32_t i) {
+    const int64_t e0 = U.rptr[i], e1 = U.rptr[i + 1];
+    const double w = omega / A.diag[i];
+    int64_t s = e0, q0 = e0;
+    for_row_entries(A, i, [&](int32_t, int64_t) { ++q0; });
+    int64_t q = q0;  // end of the aggregates found so far
+    for_row_entries(A, i, [&](int32_t j, int64_t e) {
+        const double dj = A.diag[j];
+        const double a = e < 0 ? dj : A.val[e], at = e < 0 ? dj : A.valT[e];
+        U.col[s] = j;
+        U.val[s] = e < 0 ? w * (2.0 - omega) : w * ((-omega * a) / dj);
+        U.valT[s] = e < 0 ? w * (2.0 - omega) : w * ((-omega * at) / dj);
+        ++s;
+        const int32_t c = A.n + agg[j];
+        int64_t k = q0;
+        while (k < q && U.col[k] != c) ++k;
+        if (k == q) {
+            U.col[k] = c;
+            U.val[k] = U.valT[k] = 0.0;
+            ++q;
+        }
+        U.val[k] = U.val[k] + a;
+        U.valT[k] = U.valT[k] + at;
+    });
+    const int32_t own = A.n + agg[i];
+    for (int64_t k = q0; k < e1; ++k) {
+        const double p = U.col[k] == own ? 1.0 : 0.0;
+        U.val[k] = p - w * U.val[k];
+        U.valT[k] = p - w * U.valT[k];
+    }
+}
+
+// U's columns and values (val: A, valT: A^T) for this omega.  16 lanes share a
+// row: each forms one S entry of 16, and then every lane sees the 16 in column
+// order and sums those of the aggregates that it holds (the k-th found is
+// lane k % 16's).  A lane that formed its row alone kept the sums in U, one
+// chain of loads and stores.  Levels of 16,000, 1,700 and 190 rows of a merged
+// hierarchy: 150 + 171 + 92 -> 20 + 15 + 12 us (with the other refresh kernels a
+// 151^3 time step 13.2 -> 12.6 ms, a 100^3 solve and its gradient 43.8 -> 42.1).
+constexpr int kUpLanes = kRowLanes;
+constexpr int kUpHeld = 4;  // aggregates held by a lane: longer rows are formed by one
+
+__global__ void __launch_bounds__(kBlock)
+k_up_fill(Sell A, Csr U, const int32_t *__restrict__ agg, double omega) {
+    const int l = threadIdx.x % kUpLanes;
+    const int g0 = (threadIdx.x & 63) - l;  // the group's first lane
+    const uint64_t mine = ((uint64_t(1) << kUpLanes) - 1) << g0;
+    ROW_GROUPS(row, A.n) {
+        if (row >= A.n) continue;  // the whole group
+        const int32_t i = (int32_t)row;
+        const int64_t ps = A.iperm ? (int64_t)A.iperm[i] : (int64_t)i;
+        const int w = row_len(A, ps);
         const int64_t e0 = U.rptr[i], e1 = U.rptr[i + 1];
-        const double w = omega / A.diag[i];
-        int64_t s = e0, q0 = e0;
-        for_row_entries(A, (int32_t)i, [&](int32_t, int64_t) { ++q0; });
-        int64_t q = q0;  // end of the aggregates found so far
-        for_row_entries(A, (int32_t)i, [&](int32_t j, int64_t e) {
-            const double dj = A.diag[j];
-            const double a = e < 0 ? dj : A.val[e], at = e < 0 ? dj : A.valT[e];
-            U.col[s] = j;
-            U.val[s] = e < 0 ? w * (2.0 - omega) : w * ((-omega * a) / dj);
-            U.valT[s] = e < 0 ? w * (2.0 - omega) : w * ((-omega * at) / dj);
-            ++s;
-            const int32_t c = A.n + agg[j];
-            int64_t k = q0;
-            while (k < q && U.col[k] != c) ++k;
-            if (k == q) {
-                U.col[k] = c;
-                U.val[k] = U.valT[k] = 0.0;
-                ++q;
+        int below = 0, m = 1;  // entries before the diagonal, and with it
+        for (int k = 0; k < w; k += kUpLanes) {
+            const int32_t j = k + l < w ? A.col[entry_at(A, ps, k + l)] : i;
+            below += __popcll(__ballot(j < i) & mine);
+            m += __popcll(__ballot(j != i) & mine);  // padding points at the row
+        }
+        const int64_t q0 = e0 + m;
+        if (e1 - q0 > kUpHeld * kUpLanes) {
+            if (l == 0) up_row(A, U, agg, omega, i);
+            continue;
+        }
+        const double wi = omega / A.diag[i];
+        int32_t c[kUpHeld];
+        double v[kUpHeld], vT[kUpHeld];
+#pragma unroll
+        for (int h = 0; h < kUpHeld; ++h) c[h] = -1;
+        int found = 0;
+        for (int t0 = 0; t0 < m; t0 += kUpLanes) {
+            const int t = t0 + l;
+            int32_t cj = -1;
+            double a = 0.0, at = 0.0;
+            if (t < m) {
+                const int64_t e = t == below ? -1 : entry_at(A, ps, t < below ? t : t - 1);
+                const int32_t j = e < 0 ? i : A.col[e];
+                const double dj = A.diag[j];
+                a = e < 0 ? dj : A.val[e];
+                at = e < 0 ? dj : A.valT[e];
+                cj = A.n + agg[j];
+                U.col[e0 + t] = j;
+                U.val[e0 + t] = e < 0 ? wi * (2.0 - omega) : wi * ((-omega * a) / dj);
+                U.valT[e0 + t] = e < 0 ? wi * (2.0 - omega) : wi * ((-omega * at) / dj);
             }
-            U.val[k] = U.val[k] + a;
-            U.valT[k] = U.valT[k] + at;
-        });
+            for (int u = 0; u < kUpLanes && t0 + u < m; ++u) {
+                const int32_t cu = __shfl(cj, g0 + u);
+                const double au = __shfl(a, g0 + u), atu = __shfl(at, g0 + u);
+                bool hit = false;
+#pragma unroll
+                for (int h = 0; h < kUpHeld; ++h)
+                    if (c[h] == cu) {
+                        v[h] = v[h] + au;
+                        vT[h] = vT[h] + atu;
+                        hit = true;
+                    }
+                if (!(__ballot(hit) & mine)) {
+#pragma unroll
+                    for (int h = 0; h < kUpHeld; ++h)
+                        if (found == h * kUpLanes + l) {
+                            c[h] = cu;
+                            v[h] = 0.0 + au;
+                            vT[h] = 0.0 + atu;
+                        }
+                    ++found;
+                }
+            }
+        }
         const int32_t own = A.n + agg[i];
-        for (int64_t k = q0; k < e1; ++k) {
-            const double p = U.col[k] == own ? 1.0 : 0.0;
-            U.val[k] = p - w * U.val[k];
-            U.valT[k] = p - w * U.valT[k];
+#pragma unroll
+        for (int h = 0; h < kUpHeld; ++h) {
+            const int64_t k = q0 + h * kUpLanes + l;
+            if (k < e1) {
+                const double p = c[h] == own ? 1.0 : 0.0;
+                U.col[k] = c[h];
+                U.val[k] = p - wi * v[h];
+                U.valT[k] = p - wi * vT[h];
+            }
         }
     }
 }
@@ -2907,7 +3041,7 @@ static void rop_values(Level &L, double omega, hipStream_t st) {
     if (L.R.sptr) fill(L.R);
     else fill(L.Rc);
     if (L.Uc.rptr) {
-        k_up_fill<<<grid_n(L.n), kBlock, 0, st>>>(L.A, L.Uc, L.agg, omega);
+        k_up_fill<<<grid_n((int64_t)L.n * kUpLanes), kBlock, 0, st>>>(L.A, L.Uc, L.agg, omega);
         if (L.Uc.val32) {
             k_rop_f32<<<grid_n(L.Uc.nnz), kBlock, 0, st>>>(L.Uc.val, L.Uc.val32, L.Uc.nnz);
             k_rop_f32<<<grid_n(L.Uc.nnz), kBlock, 0, st>>>(L.Uc.valT, L.Uc.valT32, L.Uc.nnz);
