@@ -71,7 +71,7 @@ typedef struct {
     double rel_tol;       /* stop at ||r||/||b|| <= rel_tol */
     double abs_tol;       /* unused, reserved: must be 0 */
     int max_iter;         /* FP64: CG iterations; MIXED: per inner solve cap is inner_max_iter */
-    int check_every;      /* host reads the convergence flag every k iterations (>= 1) */
+    int check_every;      /* host reads the convergence flag at least every k iterations (>= 1) */
     int precond;          /* 0 none, 1 diagonal, 2 one GAMG V-cycle (the handle's
                              hierarchy and sweep settings from gamg_setup, or the
                              defaults; correction scaling off so that the
@@ -244,8 +244,9 @@ int gamg_level_export(ldu_handle h, int level, int32_t *agg, int32_t *owner,
 int ldu_level_layout(ldu_handle h, int level, int *compressed, int *col16);
 /* The form of level l's one-pass down leg, r_c = P^T (I - omega A D^-1) r,
  * which cycles with one Jacobi pre-sweep from zero and no correction scaling
- * use (HOST outputs, lanes may be NULL): 0 not built (the coarsest level, or
- * no such cycle has run on this hierarchy); 1 the operator R in compressed
+ * use (HOST outputs, lanes may be NULL; the up leg that goes with it, one
+ * operator on small levels and one product on form 3, is not reported): 0 not
+ * built (the coarsest level, or no such cycle has run on this hierarchy); 1 the operator R in compressed
  * slices; 2 R in CSR, with *lanes lanes per row; 3 a product over the
  * level's own slices with stored values -omega a_ij / D_j, then the member
  * sums.  LDU_ERR_STATE without a hierarchy, LDU_ERR_ARG for a bad level. */

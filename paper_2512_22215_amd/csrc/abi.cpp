@@ -133,6 +133,12 @@ int fail(int code, const std::string &msg) {
     return code;
 }
 
+// a call that failed part way leaves no temporary memory for a later one,
+// which may run on another stream (the free waits for the device)
+void give_back(ldu_t *h) {
+    if (h) h->pool.trim();
+}
+
 template <class F>
 int guarded(ldu_t *h, F &&f) {
     if (h && h->poisoned) return fail(LDU_ERR_STATE, "handle is poisoned by an earlier HIP error");
@@ -141,10 +147,13 @@ int guarded(ldu_t *h, F &&f) {
         return f();
     } catch (const Error &e) {
         if (h && e.code == LDU_ERR_HIP) h->poisoned = true;
+        give_back(h);
         return fail(e.code, e.what());
     } catch (const std::bad_alloc &) {
+        give_back(h);
         return fail(LDU_ERR_NOMEM, "host allocation failed");
     } catch (const std::exception &e) {
+        give_back(h);
         return fail(LDU_ERR_ARG, e.what());
     }
 }
