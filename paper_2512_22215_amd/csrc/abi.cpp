@@ -395,7 +395,7 @@ int ldu_amul_f32(ldu_handle h, const float *x, float *y, void *hip_stream) {
     if (!h || !x || !y) return fail(LDU_ERR_ARG, "NULL argument");
     return guarded(h, [&] {
         hipStream_t st = S(hip_stream);
-        ensure_f32(h->L0, h->arena, st);
+        ensure_f32(h->L0, h->arena, true, st);
         if (h->gamg_ready) h->levels[0].A = h->L0.A;
         launch_amul32(h->L0.A.view32(false), x, y, st);
         return LDU_OK;

@@ -496,9 +496,9 @@ __global__ void k_singular(Sell A, int *flag) {
 // ---------------------------------------------------------------- setup
 // FP32 copies of every level's values; level 0's live with the handle
 static void ensure_f32_levels(ldu_t *h, hipStream_t st) {
-    ensure_f32(h->L0, h->L0.src ? h->gamg_arena : h->arena, st);  // a renumbered one's: hierarchy
+    ensure_f32(h->L0, h->L0.src ? h->gamg_arena : h->arena, !h->L0.src, st);  // a renumbered one's: hierarchy
     h->levels[0].A = h->L0.A;
-    for (size_t l = 1; l < h->levels.size(); ++l) ensure_f32(h->levels[l], h->gamg_arena, st);
+    for (size_t l = 1; l < h->levels.size(); ++l) ensure_f32(h->levels[l], h->gamg_arena, false, st);
 }
 
 static void ensure_work(ldu_t *h) {

@@ -436,7 +436,7 @@ void build_sliced_rows(Sell &A, int32_t n, const int32_t *deg, Arena &ar,
 void assemble_pressure(ldu_t *h, const double *gamma, const double *w, const double *mag_sf,
                        const double *delta, const double *diag_bc, const double *phi,
                        const double *b_bc, double *b, hipStream_t st);
-void ensure_f32(Level &L, Arena &ar, hipStream_t st);
+void ensure_f32(Level &L, Arena &ar, bool own, hipStream_t st);
 void refresh_f32(Level &L, hipStream_t st);
 void exclusive_scan_i64(const int64_t *in, int64_t *out, int64_t n, Arena &tmp,
                         hipStream_t st);  // out has n+1 entries

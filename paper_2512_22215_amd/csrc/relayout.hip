@@ -784,11 +784,19 @@ void refresh_f32(Level &L, hipStream_t st) {
     HIP_CHECK(hipGetLastError());
 }
 
-void ensure_f32(Level &L, Arena &ar, hipStream_t st) {
+// `own`: arrays of their own.  A single matrix asks for these three alone, and
+// a chunk sized by what the handle holds takes longer than they do: the first
+// FP32 product on 69,120 cells 350 us from a chunk, 40 us from arrays.
+void ensure_f32(Level &L, Arena &ar, bool own, hipStream_t st) {
     if (L.A.val32) return;
-    L.A.val32 = ar.get<float>(L.A.nnz);
-    L.A.valT32 = ar.get<float>(L.A.nnz);
-    L.A.diag32 = ar.get<float>(L.n);
+    auto floats = [&](int64_t n) {
+        return own ? static_cast<float *>(ar.alloc_own(sizeof(float) * (size_t)n))
+                   : ar.get<float>(n);
+    };
+    float *v = floats(L.A.nnz), *vT = floats(L.A.nnz);
+    L.A.diag32 = floats(L.n);
+    L.A.val32 = v;
+    L.A.valT32 = vT;
     refresh_f32(L, st);
 }
 

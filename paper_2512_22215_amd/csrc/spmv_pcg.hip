@@ -1172,7 +1172,7 @@ void launch_mx_refine(ldu_t *h, double *x, int32_t n, int64_t S, int G, hipStrea
 int pcg_mixed(ldu_t *h, const double *b, double *x, const ldu_pcg_opts &o, bool tr,
               ldu_stats *stats, hipStream_t st) {
     Level &L = h->L0;
-    ensure_f32(L, h->arena, st);
+    ensure_f32(L, h->arena, true, st);
     const SellView<double> A = L.A.view(tr);
     const SellView<float> A32 = L.A.view32(tr);
     const int n = L.n;
