@@ -1742,9 +1742,11 @@ k_up_fill(Sell A, Csr U, const int32_t *__restrict__ agg, double omega) {
 // product with A's values that gathers from the coarse vector (AC: A's slices
 // with their columns mapped to aggregates).  The correction (r, D, the map and
 // e_c in, e out) and the sweep after it (A, e, r, D in) were two passes.
-// 200^3 in FP64: correction and sweep 44 + 137 us, this kernel 160 (columns
+// 200^3 in FP64: correction and sweep 44 + 137 us, this kernel 161 (columns
 // mapped in the kernel, e_c[agg[j]], chain two gathers: 204); CG + V-cycle
-// 124.7 -> 123.5 ms there, 15.3 -> 14.8 ms on 100^3.
+// 124.7 -> 122.4 ms there, 15.3 -> 14.8 ms on 100^3.  The map is read past the
+// caches and D through them: the CG product that follows finds D there (132
+// -> 125 us; 123.1 -> 122.3 ms).
 template <bool DOT, typename T>
 __global__ void __launch_bounds__(kBlock)
 k_vc_up_slices(SellView<T> AC, const int32_t *__restrict__ agg, const T *__restrict__ r,
@@ -1756,12 +1758,13 @@ k_vc_up_slices(SellView<T> AC, const int32_t *__restrict__ agg, const T *__restr
     for_each_slice<product_cap<false, T>()>(AC.nslices, [&](int64_t s) {
         const int64_t i = s * kWave + lane;
         if (i < AC.n) {
-            const T ci = ec[agg[i]];
-            const T di = vld<DOT>(AC.diag + i);
+            const T ci = ec[vld<true>(agg + i)];
+            const T di = AC.diag[i];
             T y = di * ci;
             row_entries<false, 8>(AC, s, lane, Direct<T>{ec},
                                   [&](int32_t, T v, T xv) { y = y + v * xv; });
-            // with DOT the iteration reads neither r nor D before its CG product
+            // with DOT the iteration does not read r before its CG product (which
+            // finds D, read with the default policy, in the Infinity Cache)
             const T ri = vld<DOT>(r + i);
             const T zi = ci + omega * (ri + vld<true>(t + i) - y) / di;
             e[i] = zi;
