@@ -1,6 +1,6 @@
 /*
- * ldu_bench.h -- bandwidth-ceiling kernels exported by libldu.so beside the
- * solver ABI of ldu.h.  They are measurement aids, not part of the solve:
+ * ldu_bench.h -- bandwidth-ceiling kernels (and a switch for tests, at the
+ * end) exported by libldu.so beside the solver ABI of ldu.h.  They are measurement aids, not part of the solve:
  * each streams plain double arrays with no index stream and no gathers, so
  * its achieved rate is the HBM ceiling a streaming solver kernel is compared
  * with (the product and vector kernels of Sec. 4.3's profile are all
@@ -35,6 +35,14 @@ int ldu_stream_copy(const double *a, double *b, int64_t n, int blocks,
 int ldu_stream_cg_update(double *x, double *r, const double *p, const double *q,
                          double alpha, int64_t n, int blocks, int nontemporal,
                          void *hip_stream);
+
+/* For tests of calls that run out of device memory: the n-th array that the
+ * handle asks for from now on is refused, and the call that asks for it
+ * returns LDU_ERR_NOMEM; the arrays after it are granted again.  n = 0 refuses
+ * none.  Returns the arrays asked for since the last call of this function, or
+ * -1 for a NULL handle. */
+struct ldu_t;
+int64_t ldu_deny_memory(struct ldu_t *h, int64_t n);
 
 #ifdef __cplusplus
 }

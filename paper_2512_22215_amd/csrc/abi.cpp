@@ -12,6 +12,7 @@
 #include <rocprofiler-sdk-roctx/roctx.h>
 
 #include "internal.hpp"
+#include "ldu_bench.h"
 
 namespace ldu {
 
@@ -87,7 +88,12 @@ void Arena::reserve(size_t bytes) {
     if (chunks_.empty() || chunks_.back().bytes - used_ < bytes) add_chunk(bytes);
 }
 
+void Arena::check_denied() {
+    if (pool_ && pool_->denied()) throw Error(LDU_ERR_NOMEM, "device array refused on request");
+}
+
 void *Arena::alloc(size_t bytes) {
+    check_denied();
     bytes = (std::max(bytes, size_t(16)) + 255) & ~size_t(255);
     reserve(bytes);
     void *p = chunks_.back().p + used_;
@@ -96,6 +102,7 @@ void *Arena::alloc(size_t bytes) {
 }
 
 void *Arena::alloc_own(size_t bytes) {
+    check_denied();
     own_.reserve(own_.size() + 1);
     own_.push_back(device_alloc(std::max(bytes, size_t(16))));
     return own_.back();
@@ -243,6 +250,14 @@ void ldu_gamg_default_opts(ldu_gamg_opts *o) {
 }
 
 const char *ldu_last_error(void) { return g_last_error.c_str(); }
+
+int64_t ldu_deny_memory(ldu_handle h, int64_t n) {
+    if (!h) return -1;
+    const int64_t asked = h->pool.asked;
+    h->pool.asked = 0;
+    h->pool.deny = n;
+    return asked;
+}
 
 int ldu_create(int32_t nCells, int64_t nFaces, const int32_t *owner, const int32_t *neighbour,
                const double *diag, const double *upper, const double *lower, void *hip_stream,

@@ -504,10 +504,11 @@ static void ensure_f32_levels(ldu_t *h, hipStream_t st) {
 static void ensure_work(ldu_t *h) {
     for (Level &L : h->levels) {
         if (L.r) continue;
-        L.r = h->gamg_arena.get<double>(L.n);
+        double *r = h->gamg_arena.get<double>(L.n);
         L.e = h->gamg_arena.get<double>(L.n);
         L.e2 = h->gamg_arena.get<double>(L.n);
         L.t = h->gamg_arena.get<double>(L.n);
+        L.r = r;  // last: the four exist
     }
 }
 
@@ -2922,10 +2923,11 @@ static void ensure_work32(ldu_t *h, hipStream_t st) {
     ensure_f32_levels(h, st);
     for (auto &L : h->levels) {
         if (!L.r32) {
-            L.r32 = h->gamg_arena.get<float>(L.n);
+            float *r = h->gamg_arena.get<float>(L.n);
             L.e32 = h->gamg_arena.get<float>(L.n);
             L.e232 = h->gamg_arena.get<float>(L.n);
             L.t32 = h->gamg_arena.get<float>(L.n);
+            L.r32 = r;  // last: the four exist
         }
     }
 }
@@ -2942,9 +2944,8 @@ static int csr_group(int64_t nnz, int32_t n) {
     return g;
 }
 
-// U's row bounds and arrays for level l (columns and values: k_up_fill)
-static void up_structure(ldu_t *h, size_t l, hipStream_t st) {
-    Level &L = h->levels[l];
+// U's row bounds and arrays for a level (columns and values: k_up_fill)
+static void up_structure(ldu_t *h, Level &L, hipStream_t st) {
     Arena tmp(&h->pool);
     Csr &U = L.Uc;
     U = Csr{};
@@ -2962,9 +2963,11 @@ static void up_structure(ldu_t *h, size_t l, hipStream_t st) {
 }
 
 // R's structure for level l (once per hierarchy): its slices and, per
-// entry, the run of sources its value sums
+// entry, the run of sources its value sums.  It is formed on a copy of the
+// level: the pointers that say that it exists appear with everything that
+// belongs to them, or, when memory runs out part way, not at all.
 static void rop_structure(ldu_t *h, size_t l, hipStream_t st) {
-    Level &L = h->levels[l];
+    Level L = h->levels[l];
     const Level &C = h->levels[l + 1];
     if (!L.A.pdeg && C.n > kCsrMaxRows) {  // a large plain-slice level: Ah over its own slices
         L.ah = h->gamg_arena.get<double>(L.A.nnz);
@@ -2973,6 +2976,7 @@ static void rop_structure(ldu_t *h, size_t l, hipStream_t st) {
         aggregate_columns(L, h->gamg_arena, tmp, st);
         HIP_CHECK(hipStreamSynchronize(st));  // tmp is released after this point
         L.r_ready = false;
+        h->levels[l] = L;
         return;
     }
     Arena tmp(&h->pool);
@@ -3013,10 +3017,11 @@ static void rop_structure(ldu_t *h, size_t l, hipStream_t st) {
         L.r_srcn = h->gamg_arena.get<int32_t>(R.nnz);
         k_rop_link_csr<<<grid_n(C.n), kBlock, 0, st>>>(C.n, R, tstart, tcol, L.r_src0, L.r_srcn);
     }
-    if (L.Rc.rptr && L.n <= kUpRows) up_structure(h, l, st);
+    if (L.Rc.rptr && L.n <= kUpRows) up_structure(h, L, st);
     HIP_CHECK(hipGetLastError());
     HIP_CHECK(hipStreamSynchronize(st));  // tmp is released after this point
     L.r_ready = false;
+    h->levels[l] = L;
 }
 
 // R's values (and their FP32 copies, when present) for the given omega
@@ -3056,6 +3061,13 @@ static void rop_values(Level &L, double omega, hipStream_t st) {
     L.r_ready = true;
 }
 
+// FP32 copies of an operator's values: both, or none when memory runs out
+static void make_f32(ldu_t *h, int64_t nnz, float *&v, float *&vT) {
+    float *a = h->gamg_arena.get<float>(nnz);
+    vT = h->gamg_arena.get<float>(nnz);
+    v = a;
+}
+
 // R for every level but the coarsest, for the cycles whose down leg it
 // replaces: structure once per hierarchy, values again after new
 // coefficients or another omega, FP32 copies once the FP32 path is in use
@@ -3069,15 +3081,13 @@ static void ensure_rop(ldu_t *h, const ldu_gamg_opts &o, hipStream_t st) {
         if (!fresh) rop_values(L, o.omega, st);
         auto f32_copies = [&](auto &R) {
             if (!f32 || R.val32) return;  // values are current: only the FP32 copies are new
-            R.val32 = h->gamg_arena.get<float>(R.nnz);
-            R.valT32 = h->gamg_arena.get<float>(R.nnz);
+            make_f32(h, R.nnz, R.val32, R.valT32);
             k_rop_f32<<<grid_n(R.nnz), kBlock, 0, st>>>(R.val, R.val32, R.nnz);
             k_rop_f32<<<grid_n(R.nnz), kBlock, 0, st>>>(R.valT, R.valT32, R.nnz);
         };
         if (L.ah) {
             if (f32 && !L.ah32) {
-                L.ah32 = h->gamg_arena.get<float>(L.A.nnz);
-                L.ahT32 = h->gamg_arena.get<float>(L.A.nnz);
+                make_f32(h, L.A.nnz, L.ah32, L.ahT32);
                 k_rop_f32<<<grid_n(L.A.nnz), kBlock, 0, st>>>(L.ah, L.ah32, L.A.nnz);
                 k_rop_f32<<<grid_n(L.A.nnz), kBlock, 0, st>>>(L.ahT, L.ahT32, L.A.nnz);
             }
@@ -3095,7 +3105,7 @@ static void ensure_rop(ldu_t *h, const ldu_gamg_opts &o, hipStream_t st) {
 // hierarchy, values again after new coefficients or another omega, FP32 copies
 // once the FP32 path is in use
 static void gen_structure(ldu_t *h, size_t l, hipStream_t st) {
-    Level &L = h->levels[l];
+    Level L = h->levels[l];  // a copy, as in rop_structure
     const Level &C = h->levels[l + 1];
     Arena &ar = h->gamg_arena;
     Arena tmp(&h->pool);
@@ -3134,6 +3144,7 @@ static void gen_structure(ldu_t *h, size_t l, hipStream_t st) {
     HIP_CHECK(hipGetLastError());
     HIP_CHECK(hipStreamSynchronize(st));  // tmp is released after this point
     L.g_ready = false;
+    h->levels[l] = L;
 }
 
 static void ensure_gen(ldu_t *h, const ldu_gamg_opts &o, hipStream_t st) {
@@ -3153,10 +3164,7 @@ static void ensure_gen(ldu_t *h, const ldu_gamg_opts &o, hipStream_t st) {
         }
         for (Csr *M : {&L.V, &L.W}) {
             const bool made = f32 && !M->val32;
-            if (made) {
-                M->val32 = h->gamg_arena.get<float>(M->nnz);
-                M->valT32 = h->gamg_arena.get<float>(M->nnz);
-            }
+            if (made) make_f32(h, M->nnz, M->val32, M->valT32);
             if (M->val32 && (made || !fresh)) {
                 k_rop_f32<<<grid_n(M->nnz), kBlock, 0, st>>>(M->val, M->val32, M->nnz);
                 k_rop_f32<<<grid_n(M->nnz), kBlock, 0, st>>>(M->valT, M->valT32, M->nnz);

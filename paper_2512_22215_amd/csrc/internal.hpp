@@ -183,6 +183,9 @@ public:
     Chunk take(size_t bytes);
     void put(Chunk c) { free_.push_back(c); }
     void trim();
+    // whether the array asked for now is refused (ldu_deny_memory)
+    bool denied() { return ++asked && deny > 0 && --deny == 0; }
+    int64_t asked = 0, deny = 0;
 
 private:
     std::vector<Chunk> free_;
@@ -211,6 +214,7 @@ public:
 
 private:
     void add_chunk(size_t bytes);
+    void check_denied();
     std::vector<Chunk> chunks_;
     std::vector<void *> own_;
     size_t used_ = 0, total_ = 0;  // of the last chunk; of all chunks

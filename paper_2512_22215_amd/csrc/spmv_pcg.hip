@@ -562,6 +562,16 @@ static void fill_stats_common(ldu_stats *stats) {
     stats->history_count = 0;
 }
 
+// z and the second direction of the two-kernel forms.  The pointer that says
+// that a set of arrays exists is set last, here and wherever a call allocates:
+// a call that runs out of memory part way leaves the set as not there.
+static void ensure_direction(ldu_t *h) {
+    if (h->z) return;
+    double *z = h->arena.get<double>(h->L0.n);
+    h->p2 = h->arena.get<double>(h->L0.n);
+    h->z = z;
+}
+
 int pcg_fp64(ldu_t *h, const double *b, double *x, const ldu_pcg_opts &o, bool tr,
              ldu_stats *stats, hipStream_t st, bool own_hist) {
     const Level &L = h->L0;
@@ -576,10 +586,7 @@ int pcg_fp64(ldu_t *h, const double *b, double *x, const ldu_pcg_opts &o, bool t
     // the allocation-free entry point has no room for the two-kernel form's
     // vectors; the results are the same bit for bit
     const bool fused = own_hist && n <= kFusedCgCells;
-    if (fused && !h->z) {
-        h->z = h->arena.get<double>(n);
-        h->p2 = h->arena.get<double>(n);
-    }
+    if (fused) ensure_direction(h);
     // products on plain slices: blocks past the cap would only add zeros; the
     // residual update: see kCgBlocks
     const int Gq = A.pdeg ? G : std::min(G, kPlainF64ProductBlocks);
@@ -909,16 +916,14 @@ int pbicg_fp64(ldu_t *h, const double *b, double *x, const ldu_pcg_opts &o, bool
     const int G = stream_grid_slices(S);
     const int precond = o.precond ? 1 : 0;
     if (!h->rt) {  // shadow vectors, allocated on the handle's first PBiCG solve
-        h->rt = h->arena.get<double>(n);
-        h->pt = h->arena.get<double>(n);
+        double *rt = h->arena.get<double>(n), *pt = h->arena.get<double>(n);
         h->qt = h->arena.get<double>(n);
+        h->pt = pt;
+        h->rt = rt;
     }
     const bool fused = n <= kFusedBicgCells;
+    if (fused) ensure_direction(h);
     if (fused && !h->zt) {
-        if (!h->z) {
-            h->z = h->arena.get<double>(n);
-            h->p2 = h->arena.get<double>(n);
-        }
         h->pt2 = h->arena.get<double>(n);
         h->zt = h->arena.get<double>(n);
     }

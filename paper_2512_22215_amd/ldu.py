@@ -31,8 +31,9 @@ EXPORTED = (
 )
 
 
-# ldu_bench.h: bandwidth-ceiling kernels (measurement aids)
-BENCH_EXPORTED = ("ldu_stream_read", "ldu_stream_copy", "ldu_stream_cg_update")
+# ldu_bench.h: bandwidth-ceiling kernels (measurement aids), refused arrays (tests)
+BENCH_EXPORTED = ("ldu_stream_read", "ldu_stream_copy", "ldu_stream_cg_update",
+                  "ldu_deny_memory")
 
 
 class LduError(RuntimeError):
@@ -115,6 +116,7 @@ def lib():
     L.ldu_coeff_grad.argtypes = [vp, vp, vp, vp, vp, vp, vp]
     L.ldu_assemble_pressure.argtypes = [vp] * 13
     L.ldu_last_error.restype = C.c_char_p
+    L.ldu_deny_memory.argtypes, L.ldu_deny_memory.restype = [vp, i64], i64
     # bandwidth-ceiling kernels of ldu_bench.h
     L.ldu_stream_read.argtypes = [vp, i64, vp, i, i, vp]
     L.ldu_stream_copy.argtypes = [vp, vp, i64, i, i, vp]
