@@ -17,7 +17,7 @@ LIB = os.path.join(HERE, "libldu.so")
 
 def sources():
     csrc = os.path.join(HERE, "csrc")
-    return sorted(glob.glob(os.path.join(csrc, "*.hip"))) + [os.path.join(csrc, "abi.cpp")]
+    return sorted(glob.glob(os.path.join(csrc, "*.hip")) + glob.glob(os.path.join(csrc, "*.cpp")))
 
 
 def build(verbose: bool = False) -> str:

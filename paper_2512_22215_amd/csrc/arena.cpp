@@ -1,0 +1,125 @@
+// Arrays of a handle, cut from chunks of device memory (arena.hpp).
+#include "arena.hpp"
+
+#include <hip/hip_runtime_api.h>
+
+#include <algorithm>
+
+#include "ldu.h"
+
+namespace ldu {
+
+static void *try_alloc(size_t bytes) {
+    void *p = nullptr;
+    if (hipMalloc(&p, bytes) == hipSuccess) return p;
+    (void)hipGetLastError();
+    return nullptr;
+}
+
+// device memory for a request; where there is none, the chunks that lie free in
+// the handle's pool go back first (their free waits for the device)
+static void *device_alloc(size_t bytes, ChunkPool *pool) {
+    void *p = try_alloc(bytes);
+    if (!p && pool && pool->trim()) p = try_alloc(bytes);
+    if (!p) throw Error(LDU_ERR_NOMEM, "hipMalloc of " + std::to_string(bytes) + " bytes failed");
+    return p;
+}
+
+// a chunk for a request of `bytes` beside `total` bytes held already: half as
+// much again, at least 64 KiB (small matrices keep to what the runtime hands
+// out of its own pages) and at most 512 MiB, or just the request when that
+// much is not there
+static Chunk new_chunk(size_t bytes, size_t total, ChunkPool *pool) {
+    Chunk c;
+    c.bytes = std::max(bytes, std::min(std::max(total / 2, size_t(64) << 10), size_t(512) << 20));
+    void *p = c.bytes > bytes ? try_alloc(c.bytes) : nullptr;
+    if (!p) {
+        c.bytes = bytes;
+        p = device_alloc(bytes, pool);
+    }
+    c.p = static_cast<char *>(p);
+    return c;
+}
+
+Chunk ChunkPool::take(size_t bytes) {
+    size_t best = free_.size();
+    for (size_t k = 0; k < free_.size(); ++k)
+        if (free_[k].bytes >= bytes && (best == free_.size() || free_[k].bytes < free_[best].bytes))
+            best = k;
+    if (best < free_.size()) {
+        const Chunk c = free_[best];
+        free_[best] = free_.back();
+        free_.pop_back();
+        return c;
+    }
+    const Chunk c = new_chunk(bytes, total_, this);
+    total_ += c.bytes;
+    return c;
+}
+
+bool ChunkPool::trim() {
+    const bool any = !free_.empty();
+    for (const Chunk &c : free_) {
+        (void)hipFree(c.p);
+        total_ -= c.bytes;
+    }
+    free_.clear();
+    return any;
+}
+
+Arena::~Arena() { release_all(); }
+
+void Arena::add_chunk(size_t bytes) {
+    chunks_.reserve(chunks_.size() + 1);
+    const Chunk c = temporary_ ? pool_->take(bytes) : new_chunk(bytes, total_, pool_);
+    chunks_.push_back(c);
+    total_ += c.bytes;
+    used_ = 0;
+}
+
+void Arena::reserve(size_t bytes) {
+    if (chunks_.empty() || chunks_.back().bytes - used_ < bytes) add_chunk(bytes);
+}
+
+void Arena::check_denied() {
+    if (pool_ && pool_->denied()) throw Error(LDU_ERR_NOMEM, "device array refused on request");
+}
+
+void *Arena::alloc(size_t bytes) {
+    check_denied();
+    bytes = (std::max(bytes, size_t(16)) + 255) & ~size_t(255);
+    reserve(bytes);
+    void *p = chunks_.back().p + used_;
+    used_ += bytes;
+    return p;
+}
+
+void *Arena::alloc_own(size_t bytes) {
+    check_denied();
+    own_.reserve(own_.size() + 1);
+    own_.push_back(device_alloc(std::max(bytes, size_t(16)), pool_));
+    return own_.back();
+}
+
+void Arena::release(void *p) {
+    for (size_t k = 0; k < own_.size(); ++k)
+        if (own_[k] == p) {
+            (void)hipFree(p);
+            own_[k] = own_.back();
+            own_.pop_back();
+            return;
+        }
+}
+
+void Arena::release_all() {
+    for (const Chunk &c : chunks_) {
+        if (temporary_) pool_->put(c);
+        else (void)hipFree(c.p);
+    }
+    chunks_.clear();
+    for (void *p : own_) (void)hipFree(p);
+    own_.clear();
+    used_ = total_ = 0;
+}
+
+}  // namespace ldu

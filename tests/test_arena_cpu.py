@@ -1,0 +1,87 @@
+"""Device-memory arenas (csrc/arena.cpp) on the host: compiled with a device allocator of a
+fixed size that hands out host memory, so that every request, refusal and free is seen.
+"""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2512_22215_amd", "csrc")
+HIP = "/opt/rocm/include"
+
+HEAD = r"""
+#include <hip/hip_runtime_api.h>
+#include <cstdio>
+#include <cstdlib>
+#include <map>
+#include "arena.hpp"
+#include "ldu.h"
+using namespace ldu;
+static size_t room = 0;                  // bytes the device has left
+static std::map<void *, size_t> live;
+extern "C" hipError_t hipMalloc(void **p, size_t n) {
+    if (n > room) return hipErrorOutOfMemory;
+    room -= n;
+    *p = std::malloc(n);
+    live[*p] = n;
+    return hipSuccess;
+}
+extern "C" hipError_t hipFree(void *p) {
+    if (!live.count(p)) { std::printf("free of unknown memory\n"); std::exit(2); }
+    room += live[p];
+    live.erase(p);
+    std::free(p);
+    return hipSuccess;
+}
+extern "C" hipError_t hipGetLastError(void) { return hipSuccess; }
+#define CHECK(x) do { if (!(x)) { std::printf("line %d: %s\n", __LINE__, #x); return 1; } } while (0)
+constexpr size_t MiB = size_t(1) << 20;
+static bool refused(Arena &a, size_t n) {
+    try { a.alloc(n); } catch (const Error &e) { return e.code == LDU_ERR_NOMEM; }
+    return false;
+}
+"""
+
+PROGRAMS = {
+    # free chunks of the pool go back before a request is refused
+    "pool-first": r"""
+int main() {
+    room = 100 * MiB;
+    ChunkPool pool;
+    {
+        Arena a;
+        a.use_pool(&pool);
+        { Arena tmp(&a); tmp.alloc(60 * MiB); }
+        CHECK(room == 40 * MiB);             // kept for the next temporary
+        a.alloc(70 * MiB);
+        CHECK(room == 30 * MiB);
+        { Arena tmp(&a); tmp.alloc(20 * MiB); }
+        a.alloc_own(25 * MiB);
+        CHECK(room == 5 * MiB);
+        CHECK(refused(a, 6 * MiB));
+        a.alloc(5 * MiB);
+    }
+    CHECK(room == 100 * MiB);
+    { Arena tmp(&pool); tmp.alloc(60 * MiB); }
+    { Arena tmp(&pool); tmp.alloc(90 * MiB); }   // the larger chunk in place of the smaller
+    pool.trim();
+    CHECK(room == 100 * MiB && live.empty());
+    return 0;
+}
+""",
+}
+
+
+@pytest.mark.skipif(not shutil.which("g++") or not os.path.isdir(os.path.join(HIP, "hip")),
+                    reason="needs g++ and the HIP headers")
+@pytest.mark.parametrize("name", list(PROGRAMS))
+def test_arena(name, tmp_path):
+    src, exe = tmp_path / "arena_test.cpp", tmp_path / "arena_test"
+    src.write_text(HEAD + PROGRAMS[name])
+    subprocess.run(["g++", "-std=c++17", "-O1", "-g", "-D__HIP_PLATFORM_AMD__", "-I", HIP,
+                    "-I", CSRC, "-I", os.path.join(ROOT, "include"), "-o", str(exe), str(src),
+                    os.path.join(CSRC, "arena.cpp")], check=True, timeout=300)
+    p = subprocess.run([str(exe)], capture_output=True, text=True, timeout=60)
+    assert p.returncode == 0, p.stdout
