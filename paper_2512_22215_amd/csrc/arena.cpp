@@ -47,7 +47,8 @@ Chunk ChunkPool::take(size_t bytes) {
         if (free_[k].bytes >= bytes && (best == free_.size() || free_[k].bytes < free_[best].bytes))
             best = k;
     if (best < free_.size()) {
-        const Chunk c = free_[best];
+        Chunk c = free_[best];
+        c.used = 0;
         free_[best] = free_.back();
         free_.pop_back();
         return c;
@@ -69,16 +70,18 @@ bool ChunkPool::trim() {
 
 Arena::~Arena() { release_all(); }
 
-void Arena::add_chunk(size_t bytes) {
+// the fullest chunk that has room for `bytes`, or a new one: a large array that
+// needs a chunk of its own leaves the rest of the others to later arrays
+Chunk &Arena::chunk_for(size_t bytes) {
+    Chunk *best = nullptr;
+    for (Chunk &c : chunks_)
+        if (c.bytes - c.used >= bytes && (!best || c.bytes - c.used < best->bytes - best->used))
+            best = &c;
+    if (best) return *best;
     chunks_.reserve(chunks_.size() + 1);
-    const Chunk c = temporary_ ? pool_->take(bytes) : new_chunk(bytes, total_, pool_);
-    chunks_.push_back(c);
-    total_ += c.bytes;
-    used_ = 0;
-}
-
-void Arena::reserve(size_t bytes) {
-    if (chunks_.empty() || chunks_.back().bytes - used_ < bytes) add_chunk(bytes);
+    chunks_.push_back(temporary_ ? pool_->take(bytes) : new_chunk(bytes, total_, pool_));
+    total_ += chunks_.back().bytes;
+    return chunks_.back();
 }
 
 void Arena::check_denied() {
@@ -88,9 +91,9 @@ void Arena::check_denied() {
 void *Arena::alloc(size_t bytes) {
     check_denied();
     bytes = (std::max(bytes, size_t(16)) + 255) & ~size_t(255);
-    reserve(bytes);
-    void *p = chunks_.back().p + used_;
-    used_ += bytes;
+    Chunk &c = chunk_for(bytes);
+    void *p = c.p + c.used;
+    c.used += bytes;
     return p;
 }
 
@@ -119,7 +122,7 @@ void Arena::release_all() {
     chunks_.clear();
     for (void *p : own_) (void)hipFree(p);
     own_.clear();
-    used_ = total_ = 0;
+    total_ = 0;
 }
 
 }  // namespace ldu

@@ -45,6 +45,36 @@ static bool refused(Arena &a, size_t n) {
 """
 
 PROGRAMS = {
+    # a request that opens a new chunk leaves the rest of the others usable
+    "rest": r"""
+int main() {
+    room = 1000 * MiB;
+    Arena a;
+    a.alloc(80 * MiB);
+    a.alloc(30 * MiB);                       // a chunk of 40 MiB (half of what is held)
+    const size_t left = room;
+    a.alloc(45 * MiB);                       // one of 60 MiB
+    CHECK(room < left);
+    const size_t after = room;
+    char *p = static_cast<char *>(a.alloc(9 * MiB));   // in the second chunk
+    char *q = static_cast<char *>(a.alloc(14 * MiB));  // in the third
+    char *s = static_cast<char *>(a.alloc(1));
+    CHECK(room == after && p && q && s);
+    a.reserve(300);
+    CHECK(room == after);
+    char *last = nullptr;                    // arrays of every chunk stay apart
+    for (int k = 0; k < 64; ++k) {
+        char *t = static_cast<char *>(a.alloc(300));
+        CHECK(reinterpret_cast<size_t>(t) % 16 == 0 && t != last);
+        for (int i = 0; i < 300; ++i) t[i] = 1;
+        last = t;
+    }
+    p[9 * MiB - 1] = q[14 * MiB - 1] = 1;
+    a.release_all();
+    CHECK(room == 1000 * MiB && live.empty());
+    return 0;
+}
+""",
     # free chunks of the pool go back before a request is refused
     "pool-first": r"""
 int main() {
