@@ -212,6 +212,7 @@ int ldu_create(int32_t nCells, int64_t nFaces, const int32_t *owner, const int32
         build_level_sell(h, h->arena, L, true, st);
         HIP_CHECK(hipStreamSynchronize(st));
         h->pool.trim();
+        h->arena.settle();  // the vectors of a solver's first call
         return LDU_OK;
     });
     if (rc != LDU_OK) {

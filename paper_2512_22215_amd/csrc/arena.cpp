@@ -29,8 +29,9 @@ static void *device_alloc(size_t bytes, ChunkPool *pool) {
 // much again, at least 64 KiB (small matrices keep to what the runtime hands
 // out of its own pages) and at most 512 MiB, or just the request when that
 // much is not there
-static Chunk new_chunk(size_t bytes, size_t total, ChunkPool *pool) {
+static Chunk new_chunk(size_t bytes, size_t total, ChunkPool *pool, bool grows = true) {
     Chunk c;
+    if (!grows) total = 0;
     c.bytes = std::max(bytes, std::min(std::max(total / 2, size_t(64) << 10), size_t(512) << 20));
     void *p = c.bytes > bytes ? try_alloc(c.bytes) : nullptr;
     if (!p) {
@@ -79,7 +80,7 @@ Chunk &Arena::chunk_for(size_t bytes) {
             best = &c;
     if (best) return *best;
     chunks_.reserve(chunks_.size() + 1);
-    chunks_.push_back(temporary_ ? pool_->take(bytes) : new_chunk(bytes, total_, pool_));
+    chunks_.push_back(temporary_ ? pool_->take(bytes) : new_chunk(bytes, total_, pool_, grows_));
     total_ += chunks_.back().bytes;
     return chunks_.back();
 }

@@ -61,6 +61,9 @@ public:
     T *get(size_t count) { return static_cast<T *>(alloc(count * sizeof(T))); }
     // room for `bytes` more in one chunk
     void reserve(size_t bytes) { (void)chunk_for(bytes); }
+    // chunks of the requests' own size from now on: what is still to come are
+    // single sets of arrays, not the hundreds of a set-up
+    void settle() { grows_ = false; }
     void release(void *p);  // frees one alloc_own allocation of this arena
     void release_all();
 
@@ -71,7 +74,7 @@ private:
     std::vector<void *> own_;
     size_t total_ = 0;  // bytes of all chunks
     ChunkPool *pool_ = nullptr;
-    bool temporary_ = false;
+    bool temporary_ = false, grows_ = true;
 };
 
 }  // namespace ldu

@@ -567,6 +567,7 @@ static void fill_stats_common(ldu_stats *stats) {
 // a call that runs out of memory part way leaves the set as not there.
 static void ensure_direction(ldu_t *h) {
     if (h->z) return;
+    h->arena.reserve(2 * (sizeof(double) * (size_t)h->L0.n + 256));
     double *z = h->arena.get<double>(h->L0.n);
     h->p2 = h->arena.get<double>(h->L0.n);
     h->z = z;
@@ -916,6 +917,7 @@ int pbicg_fp64(ldu_t *h, const double *b, double *x, const ldu_pcg_opts &o, bool
     const int G = stream_grid_slices(S);
     const int precond = o.precond ? 1 : 0;
     if (!h->rt) {  // shadow vectors, allocated on the handle's first PBiCG solve
+        h->arena.reserve(3 * (sizeof(double) * (size_t)n + 256));
         double *rt = h->arena.get<double>(n), *pt = h->arena.get<double>(n);
         h->qt = h->arena.get<double>(n);
         h->pt = pt;
@@ -924,6 +926,7 @@ int pbicg_fp64(ldu_t *h, const double *b, double *x, const ldu_pcg_opts &o, bool
     const bool fused = n <= kFusedBicgCells;
     if (fused) ensure_direction(h);
     if (fused && !h->zt) {
+        h->arena.reserve(2 * (sizeof(double) * (size_t)n + 256));
         h->pt2 = h->arena.get<double>(n);
         h->zt = h->arena.get<double>(n);
     }

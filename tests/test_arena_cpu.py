@@ -45,6 +45,22 @@ static bool refused(Arena &a, size_t n) {
 """
 
 PROGRAMS = {
+    # a settled arena asks for no more than its requests need
+    "settled": r"""
+int main() {
+    room = 1000 * MiB;
+    Arena a;
+    a.alloc(200 * MiB);
+    a.settle();
+    size_t left = room;
+    a.reserve(24 * MiB);
+    a.alloc(8 * MiB); a.alloc(8 * MiB); a.alloc(8 * MiB);
+    CHECK(room == left - 24 * MiB);
+    a.alloc(1 * MiB);
+    CHECK(room == left - 25 * MiB);
+    return 0;
+}
+""",
     # a request that opens a new chunk leaves the rest of the others usable
     "rest": r"""
 int main() {
