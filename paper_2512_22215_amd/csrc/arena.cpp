@@ -43,6 +43,7 @@ static Chunk new_chunk(size_t bytes, size_t total, ChunkPool *pool, bool grows =
 }
 
 Chunk ChunkPool::take(size_t bytes) {
+    free_.reserve(free_.size() + out_ + 1);
     size_t best = free_.size();
     for (size_t k = 0; k < free_.size(); ++k)
         if (free_[k].bytes >= bytes && (best == free_.size() || free_[k].bytes < free_[best].bytes))
@@ -52,10 +53,12 @@ Chunk ChunkPool::take(size_t bytes) {
         c.used = 0;
         free_[best] = free_.back();
         free_.pop_back();
+        ++out_;
         return c;
     }
     const Chunk c = new_chunk(bytes, total_, this);
     total_ += c.bytes;
+    ++out_;
     return c;
 }
 

@@ -33,7 +33,11 @@ class ChunkPool {
 public:
     ~ChunkPool() { trim(); }
     Chunk take(size_t bytes);
-    void put(Chunk c) { free_.push_back(c); }
+    // called from destructors: take() has made the room it needs
+    void put(Chunk c) noexcept {
+        free_.push_back(c);
+        --out_;
+    }
     bool trim();
     // whether the array asked for now is refused (ldu_deny_memory)
     bool denied() { return ++asked && deny > 0 && --deny == 0; }
@@ -41,7 +45,7 @@ public:
 
 private:
     std::vector<Chunk> free_;
-    size_t total_ = 0;
+    size_t total_ = 0, out_ = 0;  // bytes of all chunks; chunks with an arena
 };
 
 class Arena {  // owns device memory: a handle's, a hierarchy's, or one step's

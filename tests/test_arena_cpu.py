@@ -45,6 +45,32 @@ static bool refused(Arena &a, size_t n) {
 """
 
 PROGRAMS = {
+    # a temporary arena gives its chunks back without asking for host memory
+    "put": r"""
+#include <new>
+static bool no_host = false;
+void *operator new(size_t n) {
+    void *p = no_host ? nullptr : std::malloc(n);
+    if (!p) throw std::bad_alloc();
+    return p;
+}
+void operator delete(void *p) noexcept { std::free(p); }
+void operator delete(void *p, size_t) noexcept { std::free(p); }
+int main() {
+    room = 1000 * MiB;
+    ChunkPool pool;
+    {
+        Arena a(&pool), b(&pool);
+        for (int k = 1; k < 9; ++k) (k % 2 ? a : b).alloc(k * MiB);
+        no_host = true;
+    }
+    no_host = false;
+    CHECK(room < 1000 * MiB);
+    pool.trim();
+    CHECK(room == 1000 * MiB);
+    return 0;
+}
+""",
     # a settled arena asks for no more than its requests need
     "settled": r"""
 int main() {
