@@ -118,6 +118,22 @@ void Arena::release(void *p) {
         }
 }
 
+Arena::Step::Step(Arena &a) : a_(&a) {
+    for (const Chunk &c : a.chunks_) used_.push_back(c.used);
+}
+
+Arena::Step::~Step() {
+    if (!a_) return;
+    (void)hipDeviceSynchronize();  // the step's kernels may still write there
+    for (; a_->chunks_.size() > used_.size(); a_->chunks_.pop_back()) {
+        const Chunk &c = a_->chunks_.back();
+        a_->total_ -= c.bytes;
+        if (a_->temporary_) a_->pool_->put(c);
+        else (void)hipFree(c.p);
+    }
+    for (size_t k = 0; k < used_.size(); ++k) a_->chunks_[k].used = used_[k];
+}
+
 void Arena::release_all() {
     for (const Chunk &c : chunks_) {
         if (temporary_) pool_->put(c);

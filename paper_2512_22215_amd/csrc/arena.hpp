@@ -71,6 +71,21 @@ public:
     void release(void *p);  // frees one alloc_own allocation of this arena
     void release_all();
 
+    // what is cut from an arena after this, given back when the step that asked
+    // for it does not come to done()
+    class Step {
+    public:
+        explicit Step(Arena &a);
+        ~Step();
+        Step(const Step &) = delete;
+        Step &operator=(const Step &) = delete;
+        void done() { a_ = nullptr; }
+
+    private:
+        Arena *a_;
+        std::vector<size_t> used_;
+    };
+
 private:
     Chunk &chunk_for(size_t bytes);
     void check_denied();

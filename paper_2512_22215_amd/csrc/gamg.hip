@@ -504,11 +504,13 @@ static void ensure_f32_levels(ldu_t *h, hipStream_t st) {
 static void ensure_work(ldu_t *h) {
     for (Level &L : h->levels) {
         if (L.r) continue;
+        Arena::Step step(h->gamg_arena);
         double *r = h->gamg_arena.get<double>(L.n);
         L.e = h->gamg_arena.get<double>(L.n);
         L.e2 = h->gamg_arena.get<double>(L.n);
         L.t = h->gamg_arena.get<double>(L.n);
         L.r = r;  // last: the four exist
+        step.done();
     }
 }
 
@@ -2923,11 +2925,13 @@ static void ensure_work32(ldu_t *h, hipStream_t st) {
     ensure_f32_levels(h, st);
     for (auto &L : h->levels) {
         if (!L.r32) {
+            Arena::Step step(h->gamg_arena);
             float *r = h->gamg_arena.get<float>(L.n);
             L.e32 = h->gamg_arena.get<float>(L.n);
             L.e232 = h->gamg_arena.get<float>(L.n);
             L.t32 = h->gamg_arena.get<float>(L.n);
             L.r32 = r;  // last: the four exist
+            step.done();
         }
     }
 }
@@ -2967,6 +2971,7 @@ static void up_structure(ldu_t *h, Level &L, hipStream_t st) {
 // level: the pointers that say that it exists appear with everything that
 // belongs to them, or, when memory runs out part way, not at all.
 static void rop_structure(ldu_t *h, size_t l, hipStream_t st) {
+    Arena::Step step(h->gamg_arena);
     Level L = h->levels[l];
     const Level &C = h->levels[l + 1];
     if (!L.A.pdeg && C.n > kCsrMaxRows) {  // a large plain-slice level: Ah over its own slices
@@ -2977,6 +2982,7 @@ static void rop_structure(ldu_t *h, size_t l, hipStream_t st) {
         HIP_CHECK(hipStreamSynchronize(st));  // tmp is released after this point
         L.r_ready = false;
         h->levels[l] = L;
+        step.done();
         return;
     }
     Arena tmp(&h->pool);
@@ -3022,6 +3028,7 @@ static void rop_structure(ldu_t *h, size_t l, hipStream_t st) {
     HIP_CHECK(hipStreamSynchronize(st));  // tmp is released after this point
     L.r_ready = false;
     h->levels[l] = L;
+    step.done();
 }
 
 // R's values (and their FP32 copies, when present) for the given omega
@@ -3063,9 +3070,11 @@ static void rop_values(Level &L, double omega, hipStream_t st) {
 
 // FP32 copies of an operator's values: both, or none when memory runs out
 static void make_f32(ldu_t *h, int64_t nnz, float *&v, float *&vT) {
+    Arena::Step step(h->gamg_arena);
     float *a = h->gamg_arena.get<float>(nnz);
     vT = h->gamg_arena.get<float>(nnz);
     v = a;
+    step.done();
 }
 
 // R for every level but the coarsest, for the cycles whose down leg it
@@ -3105,6 +3114,7 @@ static void ensure_rop(ldu_t *h, const ldu_gamg_opts &o, hipStream_t st) {
 // hierarchy, values again after new coefficients or another omega, FP32 copies
 // once the FP32 path is in use
 static void gen_structure(ldu_t *h, size_t l, hipStream_t st) {
+    Arena::Step step(h->gamg_arena);
     Level L = h->levels[l];  // a copy, as in rop_structure
     const Level &C = h->levels[l + 1];
     Arena &ar = h->gamg_arena;
@@ -3145,6 +3155,7 @@ static void gen_structure(ldu_t *h, size_t l, hipStream_t st) {
     HIP_CHECK(hipStreamSynchronize(st));  // tmp is released after this point
     L.g_ready = false;
     h->levels[l] = L;
+    step.done();
 }
 
 static void ensure_gen(ldu_t *h, const ldu_gamg_opts &o, hipStream_t st) {

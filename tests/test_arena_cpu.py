@@ -35,6 +35,7 @@ extern "C" hipError_t hipFree(void *p) {
     std::free(p);
     return hipSuccess;
 }
+extern "C" hipError_t hipDeviceSynchronize(void) { return hipSuccess; }
 extern "C" hipError_t hipGetLastError(void) { return hipSuccess; }
 #define CHECK(x) do { if (!(x)) { std::printf("line %d: %s\n", __LINE__, #x); return 1; } } while (0)
 constexpr size_t MiB = size_t(1) << 20;
@@ -45,6 +46,36 @@ static bool refused(Arena &a, size_t n) {
 """
 
 PROGRAMS = {
+    # a step that fails part way leaves the arena as it was
+    "step": r"""
+int main() {
+    room = 100 * MiB;
+    Arena a;
+    a.alloc(10 * MiB);
+    a.alloc(2 * MiB);                        // 2 of 5
+    void *first = nullptr;
+    const size_t left = room;
+    for (int k = 0; k < 50; ++k) {
+        try {
+            Arena::Step step(a);
+            void *p = a.alloc(1 * MiB);      // in the rest of a chunk
+            if (!first) first = p;
+            CHECK(p == first);
+            a.alloc(40 * MiB);               // a chunk of its own
+            a.alloc(80 * MiB);
+            step.done();
+        } catch (const Error &) {
+        }
+        CHECK(room == left);
+    }
+    Arena::Step step(a);
+    CHECK(a.alloc(1 * MiB) == first);
+    a.alloc(40 * MiB);
+    step.done();
+    CHECK(room < left - 39 * MiB);
+    return 0;
+}
+""",
     # a temporary arena gives its chunks back without asking for host memory
     "put": r"""
 #include <new>

@@ -82,6 +82,15 @@ def test_operators_of_a_large_plain_level():
     # the two value arrays, the mapped columns, their bases and the flag, then a
     # CSR level's first arrays
     assert _again(None, lambda h: h.vcycle(b, **ONE_SWEEP), fresh, range(1, 9)) == 8
+    # calls that fail after the large arrays are made do not keep them
+    from paper_2512_22215_amd.ldu import LduError
+    fresh()
+    free = torch.cuda.mem_get_info()[0]
+    for _ in range(20):
+        _deny(m, 5)
+        with pytest.raises(LduError):
+            m.vcycle(b, **ONE_SWEEP)
+    assert torch.cuda.mem_get_info()[0] >= free - 8 * c.n_cells
     m.close()
 
 
