@@ -858,8 +858,16 @@ void gamg_build(ldu_t *h, const ldu_gamg_opts &o, hipStream_t st) {
         throw Error(LDU_ERR_LIMIT, "coarsest GAMG level has more than 8192 cells; raise max_levels");
     }
     detect_singular(h, h->levels.back(), st);
-    if (o.smoother == LDU_SMOOTH_JACOBI && h->levels.size() > 1 && scattered_numbering(h, st))
-        renumber_levels(h, st);
+    if (o.smoother == LDU_SMOOTH_JACOBI && h->levels.size() > 1 && scattered_numbering(h, st)) {
+        Arena::Step step(ar);
+        try {
+            renumber_levels(h, st);
+            step.done();
+        } catch (const Error &e) {  // without memory for the copies: the levels as they are
+            if (e.code != LDU_ERR_NOMEM) throw;
+            h->inner.clear();
+        }
+    }
     NumberingScope scope(h, o.smoother);  // work vectors and R of the levels that solve
     ensure_work(h);
     h->coarse_work = ar.get<double>(5 * (size_t)h->levels.back().n);

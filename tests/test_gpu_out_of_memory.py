@@ -9,7 +9,7 @@ of the Jacobi cycles, so that the cycles make theirs themselves.
 import numpy as np
 import pytest
 
-from meshgen import box_case
+from meshgen import box_case, random_order, relabel
 
 pytestmark = pytest.mark.gpu
 
@@ -116,4 +116,27 @@ def test_setup_and_renewed_setup():
         return h.vcycle(b, **ONE_SWEEP)
     call(m)
     assert _again(m, call) > 100
+    m.close()
+
+
+def test_scattered_mesh_without_memory_for_renumbered_levels():
+    """The copies of the levels are a gain in speed: without memory for them the solves run
+    on the levels as they are."""
+    from paper_2512_22215_amd import LduMatrix
+    c = box_case(80, 80, 80, coeff="lognormal", dirichlet_x0=1.0, seed=9)
+    c = relabel(c, random_order(c.n_cells, np.random.default_rng(10)))
+    m = LduMatrix.from_case(c)
+    b = _t(c.rhs[0])
+    _deny(m, 0)
+    m.gamg_setup(smoother="gs2")
+    levels = _deny(m, 0) - 4 * m.n_levels() - 2  # without the work vectors
+    plain = m.vcycle(b, **GENERAL)
+    m.gamg_setup(**GENERAL)
+    assert not torch.equal(m.vcycle(b, **GENERAL), plain)  # another order of sums
+    for k in (2, 7, 40, 90):  # 1: the test of the numbering
+        _deny(m, levels + k)
+        m.gamg_setup(**GENERAL)
+        assert torch.equal(m.vcycle(b, **GENERAL), plain), k
+    m.gamg_setup(**GENERAL)
+    assert not torch.equal(m.vcycle(b, **GENERAL), plain)
     m.close()
