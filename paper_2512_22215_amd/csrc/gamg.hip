@@ -1196,10 +1196,11 @@ k_rop_gather(int32_t nc, const int32_t *__restrict__ start, const int32_t *__res
              Sell A, const int64_t *__restrict__ tstart, int32_t *tcol, int64_t *tsrc,
              int32_t *rdeg) {
     __shared__ int32_t sc[kWavesPerBlock][kGatherPairs];
-    __shared__ int32_t ss[kWavesPerBlock][kGatherPairs];  // positions fit 31 bits
+    __shared__ int64_t ss[kWavesPerBlock][kGatherPairs];
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const uint64_t below = (uint64_t(1) << lane) - 1;
-    int32_t *pc = sc[wv], *psrc = ss[wv];
+    int32_t *pc = sc[wv];
+    int64_t *psrc = ss[wv];
     const GridRange gr = grid_range(nc, kWavesPerBlock);
     for (int64_t c = gr.begin + wv; c < gr.end; c += gr.step) {
         const int64_t o = tstart[c];
@@ -1235,7 +1236,7 @@ k_rop_gather(int32_t nc, const int32_t *__restrict__ start, const int32_t *__res
                     if (j != i) {
                         if (lds) {
                             pc[at] = j;
-                            psrc[at] = (int32_t)e;
+                            psrc[at] = e;
                         } else {
                             tcol[o + at] = j;
                             tsrc[o + at] = e;

@@ -760,6 +760,7 @@ k_face_span(int64_t nf, const int32_t *__restrict__ own, const int32_t *__restri
 bool scattered_numbering(ldu_t *h, hipStream_t st) {
     const Level &L = h->L0;
     if (L.n < kRenumberCells || L.nf == 0) return false;
+    if (L.A.nnz > INT32_MAX) return false;  // Level::src holds positions in 32 bits
     Arena tmp(&h->pool);
     unsigned long long *sum = tmp.get<unsigned long long>(1), host = 0;
     k_fill_i32<<<1, kBlock, 0, st>>>(reinterpret_cast<int32_t *>(sum), 2, 0);
