@@ -63,7 +63,8 @@ __device__ __forceinline__ GridRange grid_range(int64_t n, int per) {
 
 // true once the solve has stopped (done) or the current inner solve of a
 // mixed-precision solve has (inner_done, always 0 in FP64 solves): the
-// kernels of an iteration then return at once.  Both flags are read unconditionally (bitwise or), so
+// kernels of an iteration then return at once, those of small levels without
+// storing (they ask after their loads are on the way).  Both flags are read unconditionally (bitwise or), so
 // their two scalar loads share one round trip at kernel start instead of
 // running in sequence.
 __device__ __forceinline__ bool vc_skip(const DevScalars *ds) {

@@ -3253,6 +3253,14 @@ static int finish_status(const DevScalars &hs) {
 // standalone cycles launched before the host looks at the residual again, at
 // most: each look costs an idle gap of 20-30 us
 constexpr int kCycleBatch = 8;
+// Cycles, and iterations of the CG forms, before the first look.  A full batch
+// here made short solves pay for iterations that did nothing: gamg_solve with
+// max_cycles 1 on 32^3, 64^3 and 128^3 1245, 1872 and 2833 us against 298, 418
+// and 1015 with a look after the first cycle (each cycle looked at, before the
+// small levels ran through V and W: 415, 633 and 1320); CG + V-cycle to a
+// residual of 0.5, one iteration, 1054, 1987 and 2629 us against 443, 628 and
+// 1123.  Long solves pay one more look.
+constexpr int kFirstCycles = 1, kFirstIterations = 4;
 
 static int gamg_fp64_run(ldu_t *h, const double *b, double *x, const ldu_gamg_opts &o, bool tr,
               ldu_stats *stats, hipStream_t st) {
@@ -3282,7 +3290,9 @@ static int gamg_fp64_run(ldu_t *h, const double *b, double *x, const ldu_gamg_op
     }
     const double res0 = hs.res;
     while (hs.done == kRunning) {
-        const int batch = next_batch(res0, hs.res, hs.iters - 1, o.rel_tol, kCycleBatch);
+        const int cycles = hs.iters - 1;  // done so far
+        const int batch = next_batch(res0, hs.res, cycles, o.rel_tol, kFirstCycles,
+                                     std::min(kCycleBatch, o.max_cycles - cycles));
         for (int k = 0; k < batch; ++k) {
             const double *e = vcycle<double>(c, 0, h->r);
             k_add<<<G, kBlock, 0, st>>>(L.n, S, e, x, h->dev);
@@ -3440,7 +3450,9 @@ static int pcg_gamg_fp64_run(ldu_t *h, const double *b, double *x, const ldu_pcg
         const double res0 = res;
         const int iters0 = hs.iters;
         for (;;) {
-            const int batch = next_batch(res0, hs.res, hs.iters - iters0, o.rel_tol, every);
+            const int batch = next_batch(res0, hs.res, hs.iters - iters0, o.rel_tol,
+                                         std::min(kFirstIterations, every),
+                                         std::min(every, o.max_iter - hs.iters));
             for (int k = 0; k < batch; ++k) {
                 launch_product_dot(h, A, h->p, h->q, Gq, h->dev + 1, st);
                 if (nt)
@@ -3610,7 +3622,7 @@ static int pcg_gamg_mixed_run(ldu_t *h, const double *b, double *x, const ldu_pc
         launch_finalize<1>(h->partials, G, h->dev, EpiMxRho{}, st);
         k_mxg_p<<<1, kBlock, 0, st>>>(n, S, z, h->p32, h->partials, G, kStepFirst, h->dev,
                                       h->dev + 1);  // passes the scalars on
-        int batch = every;
+        int batch = std::min({kFirstIterations, every, o.inner_max_iter});
         for (;;) {
             for (int k = 0; k < batch; ++k) {
                 launch_mx_q(h, A32, G, st);
@@ -3624,7 +3636,8 @@ static int pcg_gamg_mixed_run(ldu_t *h, const double *b, double *x, const ldu_pc
             HIP_CHECK(hipGetLastError());
             read_scalars(h, st);
             if (hs.inner_done) break;
-            batch = next_batch(hs.r0, std::sqrt(hs.rr), hs.inner_iters, hs.inner_now * hs.r0, every);
+            batch = next_batch(hs.r0, std::sqrt(hs.rr), hs.inner_iters, hs.inner_now * hs.r0,
+                               every, std::min(every, o.inner_max_iter - hs.inner_iters));
         }
         inner_total += hs.inner_iters;
         launch_mx_refine(h, x, n, S, G, st);
@@ -3671,7 +3684,9 @@ static int gamg_mixed_run(ldu_t *h, const double *b, double *x, const ldu_gamg_o
     }
     const double res0 = hs.res;
     while (hs.done == kRunning) {
-        const int batch = next_batch(res0, hs.res, hs.iters - 1, o.rel_tol, kCycleBatch);
+        const int cycles = hs.iters - 1;  // done so far
+        const int batch = next_batch(res0, hs.res, cycles, o.rel_tol, kFirstCycles,
+                                     std::min(kCycleBatch, o.max_refine - cycles));
         for (int k = 0; k < batch; ++k) {
             k_cast_scaled<<<G, kBlock, 0, st>>>(L.n, S, h->r, L.r32, h->dev);
             const float *d = vcycle<float>(c, 0, L.r32);

@@ -390,7 +390,7 @@ void check_finite(ldu_t *h, const double *a, int64_t n, hipStream_t st);
 void launch_amul(const SellView<double> &A, const double *x, double *y, hipStream_t st);
 void launch_amul32(const SellView<float> &A, const float *x, float *y, hipStream_t st);
 void read_scalars(ldu_t *h, hipStream_t st);
-int next_batch(double res0, double res, int steps, double tol, int most);
+int next_batch(double res0, double res, int steps, double tol, int first, int most);
 void set_scalars_for_solve(ldu_t *h, double tol, int max_iter, hipStream_t st);
 double residual_norm(ldu_t *h, const Level &L, bool tr, const double *b,
                      const double *x, double *r_out, hipStream_t st);
