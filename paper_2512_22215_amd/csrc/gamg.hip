@@ -1161,9 +1161,11 @@ k_vc_restrict(int32_t nc, const int32_t *__restrict__ start, const int32_t *__re
 // times as many cache lines per entry as the level's own rows do.
 
 // entries a coarse row gathers before merging: its members' row entries and
-// their diagonals
+// their diagonals; *wide (when given) for a row of more than kGatherPairs
+constexpr int kGatherPairs = 512;
+
 __global__ void k_rop_count(int32_t nc, const int32_t *__restrict__ start,
-                            const int32_t *__restrict__ cells, Sell A, int64_t *cnt) {
+                            const int32_t *__restrict__ cells, Sell A, int64_t *cnt, int *wide) {
     GRID_STRIDE(c, nc) {
         int64_t m = 0;
         for (int32_t k = start[c]; k < start[c + 1]; ++k) {
@@ -1176,6 +1178,7 @@ __global__ void k_rop_count(int32_t nc, const int32_t *__restrict__ start,
                 for (int q = 0; q < w; ++q) m += A.col[entry_at(A, ps, q)] != i;
         }
         cnt[c] = m;
+        if (wide && m > kGatherPairs) *wide = 1;
     }
 }
 
@@ -1189,7 +1192,6 @@ __global__ void k_rop_count(int32_t nc, const int32_t *__restrict__ start,
 // time, a broadcast).  A thread per row with an insertion sort in global
 // memory took 21 ms on the 1.8M-cell merged hierarchy; this takes 0.9 ms.
 // Rows of more pairs than the LDS holds are sorted by one lane in place.
-constexpr int kGatherPairs = 512;
 
 __global__ void __launch_bounds__(kBlock)
 k_rop_gather(int32_t nc, const int32_t *__restrict__ start, const int32_t *__restrict__ cells,
@@ -1571,88 +1573,73 @@ k_vc_up_csr(CsrView<T> U, const T *__restrict__ r, const T *__restrict__ ec, T *
     if constexpr (DOT) block_partials<1>(acc, partials);
 }
 
-// row i's entries in column order with the diagonal in place: f(column,
-// position in A's slices, or -1 for the diagonal); padding is skipped
-template <class F>
-__device__ __forceinline__ void for_row_entries(const Sell &A, int32_t i, F &&f) {
-    const int64_t ps = A.iperm ? (int64_t)A.iperm[i] : (int64_t)i;
-    const int w = row_len(A, ps);
-    bool diag = false;
-    for (int k = 0; k < w; ++k) {
-        const int64_t e = entry_at(A, ps, k);
-        const int32_t j = A.col[e];
-        if (j == i) continue;
-        if (!diag && j > i) {
-            f(i, (int64_t)-1);
-            diag = true;
-        }
-        f(j, e);
+// 16 lanes share a row of U or V: kUpHeld aggregates held by a lane bound the
+// aggregates of a row (64), and a level with a row of more runs its up leg step
+// by step, as does one for the general cycles whose coarse rows gather more pairs
+// than k_rop_gather's LDS holds.  Such rows (a cell with hundreds of neighbours)
+// went to one lane, which looks through what it has found for every entry: on a
+// chain of 3000 cells with a cell of 120 more neighbours set-up 5.4 -> 20.9 ms
+// and a cycle after new coefficients 0.5 -> 3.7 ms, growing with the square.
+constexpr int kUpLanes = kRowLanes;
+constexpr int kUpHeld = 4;
+
+// the aggregates that a group of kUpLanes lanes has found in its row: the k-th
+// is lane k % kUpLanes's.  add() is called by the whole group, for one entry
+struct HeldAggregates {
+    int32_t c[kUpHeld];
+    int found = 0;
+    __device__ HeldAggregates() {
+#pragma unroll
+        for (int h = 0; h < kUpHeld; ++h) c[h] = -1;
     }
-    if (!diag) f(i, (int64_t)-1);
-}
-
-// U's row lengths: the S entries and the distinct aggregates they lie in (the
-// first few found are held in registers, the rest are looked up in the row)
-constexpr int kUpSeen = 8;
-
-__global__ void k_up_count(Sell A, const int32_t *__restrict__ agg, int64_t *cnt) {
-    GRID_STRIDE(i, A.n) {
-        int64_t m = 0;
-        int32_t seen[kUpSeen];
+    // old(h): this lane's h-th aggregate is cu; made(h): it is cu now
+    template <class Old, class New>
+    __device__ __forceinline__ void add(int32_t cu, uint64_t mine, int l, Old &&old, New &&made) {
+        bool hit = false;
 #pragma unroll
-        for (int k = 0; k < kUpSeen; ++k) seen[k] = -1;
-        int nseen = 0;
-        for_row_entries(A, (int32_t)i, [&](int32_t j, int64_t) {
-            const int32_t c = agg[j];
-            bool old = false;
-#pragma unroll
-            for (int k = 0; k < kUpSeen; ++k) old = old || seen[k] == c;
-            if (!old && nseen >= kUpSeen)
-                for_row_entries(A, (int32_t)i, [&](int32_t q, int64_t) {
-                    old = old || (q < j && agg[q] == c);
-                });
-            if (!old) {
-#pragma unroll
-                for (int k = 0; k < kUpSeen; ++k)
-                    if (k == nseen) seen[k] = c;
-                ++nseen;
+        for (int h = 0; h < kUpHeld; ++h)
+            if (c[h] == cu) {
+                old(h);
+                hit = true;
             }
-            m += old ? 1 : 2;
-        });
-        cnt[i] = m;
+        if (__ballot(hit) & mine) return;
+#pragma unroll
+        for (int h = 0; h < kUpHeld; ++h)
+            if (found == h * kUpLanes + l) {
+                c[h] = cu;
+                made(h);
+            }
+        ++found;
     }
-}
+};
 
-// row i of U by one lane
-__device__ void up_row(const Sell &A, const Csr &U, const int32_t *agg, double omega, int32_t i) {
-    const int64_t e0 = U.rptr[i], e1 = U.rptr[i + 1];
-    const double w = omega / A.diag[i];
-    int64_t s = e0, q0 = e0;
-    for_row_entries(A, i, [&](int32_t, int64_t) { ++q0; });
-    int64_t q = q0;  // end of the aggregates found so far
-    for_row_entries(A, i, [&](int32_t j, int64_t e) {
-        const double dj = A.diag[j];
-        const double a = e < 0 ? dj : A.val[e], at = e < 0 ? dj : A.valT[e];
-        U.col[s] = j;
-        U.val[s] = e < 0 ? w * (2.0 - omega) : w * ((-omega * a) / dj);
-        U.valT[s] = e < 0 ? w * (2.0 - omega) : w * ((-omega * at) / dj);
-        ++s;
-        const int32_t c = A.n + agg[j];
-        int64_t k = q0;
-        while (k < q && U.col[k] != c) ++k;
-        if (k == q) {
-            U.col[k] = c;
-            U.val[k] = U.valT[k] = 0.0;
-            ++q;
+// row lengths of U and V: the row's entries (with the diagonal) and the
+// distinct aggregates they lie in; *wide for a row of too many
+__global__ void __launch_bounds__(kBlock)
+k_up_count(Sell A, const int32_t *__restrict__ agg, int64_t *cnt, int *wide) {
+    const int l = threadIdx.x % kUpLanes;
+    const int g0 = (threadIdx.x & 63) - l;  // the group's first lane
+    const uint64_t mine = ((uint64_t(1) << kUpLanes) - 1) << g0;
+    ROW_GROUPS(row, A.n) {
+        if (row >= A.n) continue;  // the whole group
+        const int32_t i = (int32_t)row;
+        const int64_t ps = A.iperm ? (int64_t)A.iperm[i] : (int64_t)i;
+        const int w = row_len(A, ps);
+        const int32_t own = agg[i];
+        HeldAggregates held;
+        held.add(own, mine, l, [](int) {}, [](int) {});
+        int m = 1;
+        for (int k0 = 0; k0 < w && held.found <= kUpHeld * kUpLanes; k0 += kUpLanes) {
+            const int32_t j = k0 + l < w ? A.col[entry_at(A, ps, k0 + l)] : i;
+            const int32_t cj = j != i ? agg[j] : own;  // padding points at the row
+            m += __popcll(__ballot(j != i) & mine);
+            for (int u = 0; u < kUpLanes && k0 + u < w; ++u)
+                held.add(__shfl(cj, g0 + u), mine, l, [](int) {}, [](int) {});
         }
-        U.val[k] = U.val[k] + a;
-        U.valT[k] = U.valT[k] + at;
-    });
-    const int32_t own = A.n + agg[i];
-    for (int64_t k = q0; k < e1; ++k) {
-        const double p = U.col[k] == own ? 1.0 : 0.0;
-        U.val[k] = p - w * U.val[k];
-        U.valT[k] = p - w * U.valT[k];
+        if (l == 0) {
+            cnt[i] = m + held.found;
+            if (held.found > kUpHeld * kUpLanes) *wide = 1;
+        }
     }
 }
 
@@ -1663,9 +1650,6 @@ __device__ void up_row(const Sell &A, const Csr &U, const int32_t *agg, double o
 // chain of loads and stores.  Levels of 16,000, 1,700 and 190 rows of a merged
 // hierarchy: 150 + 171 + 92 -> 20 + 15 + 12 us (with the other refresh kernels a
 // 151^3 time step 13.2 -> 12.6 ms, a 100^3 solve and its gradient 43.8 -> 42.1).
-constexpr int kUpLanes = kRowLanes;
-constexpr int kUpHeld = 4;  // aggregates held by a lane: longer rows are formed by one
-
 __global__ void __launch_bounds__(kBlock)
 k_up_fill(Sell A, Csr U, const int32_t *__restrict__ agg, double omega) {
     const int l = threadIdx.x % kUpLanes;
@@ -1684,16 +1668,9 @@ k_up_fill(Sell A, Csr U, const int32_t *__restrict__ agg, double omega) {
             m += __popcll(__ballot(j != i) & mine);  // padding points at the row
         }
         const int64_t q0 = e0 + m;
-        if (e1 - q0 > kUpHeld * kUpLanes) {
-            if (l == 0) up_row(A, U, agg, omega, i);
-            continue;
-        }
         const double wi = omega / A.diag[i];
-        int32_t c[kUpHeld];
+        HeldAggregates held;
         double v[kUpHeld], vT[kUpHeld];
-#pragma unroll
-        for (int h = 0; h < kUpHeld; ++h) c[h] = -1;
-        int found = 0;
         for (int t0 = 0; t0 < m; t0 += kUpLanes) {
             const int t = t0 + l;
             int32_t cj = -1;
@@ -1710,26 +1687,17 @@ k_up_fill(Sell A, Csr U, const int32_t *__restrict__ agg, double omega) {
                 U.valT[e0 + t] = e < 0 ? wi * (2.0 - omega) : wi * ((-omega * at) / dj);
             }
             for (int u = 0; u < kUpLanes && t0 + u < m; ++u) {
-                const int32_t cu = __shfl(cj, g0 + u);
                 const double au = __shfl(a, g0 + u), atu = __shfl(at, g0 + u);
-                bool hit = false;
-#pragma unroll
-                for (int h = 0; h < kUpHeld; ++h)
-                    if (c[h] == cu) {
+                held.add(
+                    __shfl(cj, g0 + u), mine, l,
+                    [&](int h) {
                         v[h] = v[h] + au;
                         vT[h] = vT[h] + atu;
-                        hit = true;
-                    }
-                if (!(__ballot(hit) & mine)) {
-#pragma unroll
-                    for (int h = 0; h < kUpHeld; ++h)
-                        if (found == h * kUpLanes + l) {
-                            c[h] = cu;
-                            v[h] = 0.0 + au;
-                            vT[h] = 0.0 + atu;
-                        }
-                    ++found;
-                }
+                    },
+                    [&](int h) {
+                        v[h] = 0.0 + au;
+                        vT[h] = 0.0 + atu;
+                    });
             }
         }
         const int32_t own = A.n + agg[i];
@@ -1737,8 +1705,8 @@ k_up_fill(Sell A, Csr U, const int32_t *__restrict__ agg, double omega) {
         for (int h = 0; h < kUpHeld; ++h) {
             const int64_t k = q0 + h * kUpLanes + l;
             if (k < e1) {
-                const double p = c[h] == own ? 1.0 : 0.0;
-                U.col[k] = c[h];
+                const double p = held.c[h] == own ? 1.0 : 0.0;
+                U.col[k] = held.c[h];
                 U.val[k] = p - wi * v[h];
                 U.valT[k] = p - wi * vT[h];
             }
@@ -1995,6 +1963,26 @@ k_gen_energy(CsrView<T> V, const int64_t *__restrict__ qptr, const T *__restrict
     });
     if (skip) return;
     block_partials<2>(acc, partials);
+}
+
+// row i's entries in column order with the diagonal in place: f(column,
+// position in A's slices, or -1 for the diagonal); padding is skipped
+template <class F>
+__device__ __forceinline__ void for_row_entries(const Sell &A, int32_t i, F &&f) {
+    const int64_t ps = A.iperm ? (int64_t)A.iperm[i] : (int64_t)i;
+    const int w = row_len(A, ps);
+    bool diag = false;
+    for (int k = 0; k < w; ++k) {
+        const int64_t e = entry_at(A, ps, k);
+        const int32_t j = A.col[e];
+        if (j == i) continue;
+        if (!diag && j > i) {
+            f(i, (int64_t)-1);
+            diag = true;
+        }
+        f(j, e);
+    }
+    if (!diag) f(i, (int64_t)-1);
 }
 
 // V's columns and values: U's structure, with A's own entries in place of S's
@@ -2957,22 +2945,29 @@ static int csr_group(int64_t nnz, int32_t n) {
     return g;
 }
 
-// U's row bounds and arrays for a level (columns and values: k_up_fill)
+// U's row bounds and arrays for a level (columns and values: k_up_fill), unless
+// a row has too many aggregates
 static void up_structure(ldu_t *h, Level &L, hipStream_t st) {
+    Arena::Step step(h->gamg_arena);
     Arena tmp(&h->pool);
-    Csr &U = L.Uc;
-    U = Csr{};
+    Csr U;
     U.n = L.n;
     U.rptr = h->gamg_arena.get<int64_t>((size_t)L.n + 1);
     int64_t *cnt = tmp.get<int64_t>(L.n);
-    k_up_count<<<grid_n(L.n), kBlock, 0, st>>>(L.A, L.agg, cnt);
+    int *wide = tmp.get<int>(1), hwide = 0;
+    k_set_int<<<1, 1, 0, st>>>(wide, 0);
+    k_up_count<<<grid_n((int64_t)L.n * kUpLanes), kBlock, 0, st>>>(L.A, L.agg, cnt, wide);
     exclusive_scan_i64(cnt, U.rptr, L.n, tmp, st);
     HIP_CHECK(hipMemcpyAsync(&U.nnz, U.rptr + L.n, sizeof(int64_t), hipMemcpyDeviceToHost, st));
+    HIP_CHECK(hipMemcpyAsync(&hwide, wide, sizeof(int), hipMemcpyDeviceToHost, st));
     HIP_CHECK(hipStreamSynchronize(st));
+    if (hwide) return;
     U.col = h->gamg_arena.get<int32_t>(U.nnz);
     U.val = h->gamg_arena.get<double>(U.nnz);
     U.valT = h->gamg_arena.get<double>(U.nnz);
     U.group = csr_group(U.nnz, U.n);
+    L.Uc = U;
+    step.done();
 }
 
 // R's structure for level l (once per hierarchy): its slices and, per
@@ -2997,7 +2992,7 @@ static void rop_structure(ldu_t *h, size_t l, hipStream_t st) {
     Arena tmp(&h->pool);
     int64_t *cnt = tmp.get<int64_t>(C.n);
     int64_t *tstart = tmp.get<int64_t>(C.n + 1);
-    k_rop_count<<<grid_n(C.n), kBlock, 0, st>>>(C.n, L.aggStart, L.aggCells, L.A, cnt);
+    k_rop_count<<<grid_n(C.n), kBlock, 0, st>>>(C.n, L.aggStart, L.aggCells, L.A, cnt, nullptr);
     exclusive_scan_i64(cnt, tstart, C.n, tmp, st);
     int64_t total = 0;
     HIP_CHECK(hipMemcpyAsync(&total, tstart + C.n, sizeof(int64_t), hipMemcpyDeviceToHost, st));
@@ -3128,34 +3123,45 @@ static void gen_structure(ldu_t *h, size_t l, hipStream_t st) {
     const Level &C = h->levels[l + 1];
     Arena &ar = h->gamg_arena;
     Arena tmp(&h->pool);
-    auto alloc = [&](Csr &M, int32_t n, const int64_t *cnt) {
+    auto bounds = [&](Csr &M, int32_t n, const int64_t *cnt) {
         M = Csr{};
         M.n = n;
         M.rptr = ar.get<int64_t>((size_t)n + 1);
         exclusive_scan_i64(cnt, M.rptr, n, tmp, st);
         HIP_CHECK(hipMemcpyAsync(&M.nnz, M.rptr + n, sizeof(int64_t), hipMemcpyDeviceToHost, st));
-        HIP_CHECK(hipStreamSynchronize(st));
+    };
+    auto arrays = [&](Csr &M) {
         M.col = ar.get<int32_t>(M.nnz);
         M.val = ar.get<double>(M.nnz);
         M.valT = ar.get<double>(M.nnz);
-        M.group = csr_group(M.nnz, n);
+        M.group = csr_group(M.nnz, M.n);
     };
-    int64_t *cnt = tmp.get<int64_t>(L.n);
-    k_up_count<<<grid_n(L.n), kBlock, 0, st>>>(L.A, L.agg, cnt);
-    alloc(L.V, L.n, cnt);
-    L.qptr = ar.get<int64_t>(L.n);
+    int64_t *cnt = tmp.get<int64_t>(L.n), *tcnt = tmp.get<int64_t>(C.n);
     int64_t *tstart = tmp.get<int64_t>((size_t)C.n + 1);
-    k_rop_count<<<grid_n(C.n), kBlock, 0, st>>>(C.n, L.aggStart, L.aggCells, L.A, cnt);
-    exclusive_scan_i64(cnt, tstart, C.n, tmp, st);
+    int *wide = tmp.get<int>(1), hwide = 0;
     int64_t total = 0;
+    k_set_int<<<1, 1, 0, st>>>(wide, 0);
+    k_up_count<<<grid_n((int64_t)L.n * kUpLanes), kBlock, 0, st>>>(L.A, L.agg, cnt, wide);
+    k_rop_count<<<grid_n(C.n), kBlock, 0, st>>>(C.n, L.aggStart, L.aggCells, L.A, tcnt, wide);
+    bounds(L.V, L.n, cnt);
+    exclusive_scan_i64(tcnt, tstart, C.n, tmp, st);
     HIP_CHECK(hipMemcpyAsync(&total, tstart + C.n, sizeof(int64_t), hipMemcpyDeviceToHost, st));
+    HIP_CHECK(hipMemcpyAsync(&hwide, wide, sizeof(int), hipMemcpyDeviceToHost, st));
     HIP_CHECK(hipStreamSynchronize(st));
+    if (hwide) {
+        h->levels[l].g_wide = true;
+        return;
+    }
+    arrays(L.V);
+    L.qptr = ar.get<int64_t>(L.n);
     int32_t *tcol = tmp.get<int32_t>(total), *rdeg = tmp.get<int32_t>(C.n);
     L.w_src = ar.get<int64_t>(total);
     k_rop_gather<<<grid_n((int64_t)C.n * kWave), kBlock, 0, st>>>(C.n, L.aggStart, L.aggCells, L.A,
                                                                  tstart, tcol, L.w_src, rdeg);
-    k_w_count<<<grid_n(C.n), kBlock, 0, st>>>(C.n, L.aggStart, rdeg, cnt);
-    alloc(L.W, C.n, cnt);
+    k_w_count<<<grid_n(C.n), kBlock, 0, st>>>(C.n, L.aggStart, rdeg, tcnt);
+    bounds(L.W, C.n, tcnt);
+    HIP_CHECK(hipStreamSynchronize(st));
+    arrays(L.W);
     L.w_src0 = ar.get<int64_t>(L.W.nnz);
     L.w_srcn = ar.get<int32_t>(L.W.nnz);
     k_w_link<<<grid_n(C.n), kBlock, 0, st>>>(C.n, L.n, L.W, L.aggStart, L.aggCells, tstart, tcol,
@@ -3172,8 +3178,9 @@ static void ensure_gen(ldu_t *h, const ldu_gamg_opts &o, hipStream_t st) {
     const bool f32 = h->L0.A.val32 != nullptr;
     for (size_t l = 0; l + 1 < h->levels.size(); ++l) {
         Level &L = h->levels[l];
-        if (L.n > kUpRows) continue;
+        if (L.n > kUpRows || L.g_wide) continue;
         if (!L.V.rptr) gen_structure(h, l, st);
+        if (L.g_wide) continue;  // found now
         const bool fresh = L.g_ready && L.g_omega == o.omega;
         if (!fresh) {
             k_gen_fill<<<grid_n(L.n), kBlock, 0, st>>>(L.A, L.V, L.qptr, L.agg, o.omega);

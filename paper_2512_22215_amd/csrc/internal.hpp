@@ -288,6 +288,7 @@ struct Level {
     int32_t *w_srcn = nullptr;                    // (count 0: a member, value 1)
     double g_omega = 0.0;
     bool g_ready = false;                 // V's and W's values match the coefficients
+    bool g_wide = false;                  // a row is too wide for V or W
     int64_t *r_src = nullptr;             // sources of R's entries, by entry in runs:
     int64_t *r_src0 = nullptr;            //   first source of each entry of R
     int32_t *r_srcn = nullptr;            //   and their count (source -1: a diagonal)
