@@ -1650,8 +1650,14 @@ k_up_count(Sell A, const int32_t *__restrict__ agg, int64_t *cnt, int *wide) {
 // chain of loads and stores.  Levels of 16,000, 1,700 and 190 rows of a merged
 // hierarchy: 150 + 171 + 92 -> 20 + 15 + 12 us (with the other refresh kernels a
 // 151^3 time step 13.2 -> 12.6 ms, a 100^3 solve and its gradient 43.8 -> 42.1).
+// V (GEN) has A's own entries in place of S's and its Q entries start at qptr.
+// Formed by a thread a row, V made new coefficients and one default GAMG cycle
+// dearer than they had been without it (32^3, 64^3 and 128^3: 0.69, 0.98 and
+// 2.46 ms): 1.51, 2.30 and 3.72 ms, now 0.83, 1.13 and 2.41; with four cycles
+// 2.17, 3.32 and 6.44 -> 1.48, 2.15 and 5.13 (without V 1.88, 2.80 and 6.17).
+template <bool GEN>
 __global__ void __launch_bounds__(kBlock)
-k_up_fill(Sell A, Csr U, const int32_t *__restrict__ agg, double omega) {
+k_up_fill(Sell A, Csr U, int64_t *qptr, const int32_t *__restrict__ agg, double omega) {
     const int l = threadIdx.x % kUpLanes;
     const int g0 = (threadIdx.x & 63) - l;  // the group's first lane
     const uint64_t mine = ((uint64_t(1) << kUpLanes) - 1) << g0;
@@ -1668,6 +1674,7 @@ k_up_fill(Sell A, Csr U, const int32_t *__restrict__ agg, double omega) {
             m += __popcll(__ballot(j != i) & mine);  // padding points at the row
         }
         const int64_t q0 = e0 + m;
+        if (GEN && l == 0) qptr[i] = q0;
         const double wi = omega / A.diag[i];
         HeldAggregates held;
         double v[kUpHeld], vT[kUpHeld];
@@ -1683,8 +1690,8 @@ k_up_fill(Sell A, Csr U, const int32_t *__restrict__ agg, double omega) {
                 at = e < 0 ? dj : A.valT[e];
                 cj = A.n + agg[j];
                 U.col[e0 + t] = j;
-                U.val[e0 + t] = e < 0 ? wi * (2.0 - omega) : wi * ((-omega * a) / dj);
-                U.valT[e0 + t] = e < 0 ? wi * (2.0 - omega) : wi * ((-omega * at) / dj);
+                U.val[e0 + t] = GEN ? a : e < 0 ? wi * (2.0 - omega) : wi * ((-omega * a) / dj);
+                U.valT[e0 + t] = GEN ? at : e < 0 ? wi * (2.0 - omega) : wi * ((-omega * at) / dj);
             }
             for (int u = 0; u < kUpLanes && t0 + u < m; ++u) {
                 const double au = __shfl(a, g0 + u), atu = __shfl(at, g0 + u);
@@ -1963,62 +1970,6 @@ k_gen_energy(CsrView<T> V, const int64_t *__restrict__ qptr, const T *__restrict
     });
     if (skip) return;
     block_partials<2>(acc, partials);
-}
-
-// row i's entries in column order with the diagonal in place: f(column,
-// position in A's slices, or -1 for the diagonal); padding is skipped
-template <class F>
-__device__ __forceinline__ void for_row_entries(const Sell &A, int32_t i, F &&f) {
-    const int64_t ps = A.iperm ? (int64_t)A.iperm[i] : (int64_t)i;
-    const int w = row_len(A, ps);
-    bool diag = false;
-    for (int k = 0; k < w; ++k) {
-        const int64_t e = entry_at(A, ps, k);
-        const int32_t j = A.col[e];
-        if (j == i) continue;
-        if (!diag && j > i) {
-            f(i, (int64_t)-1);
-            diag = true;
-        }
-        f(j, e);
-    }
-    if (!diag) f(i, (int64_t)-1);
-}
-
-// V's columns and values: U's structure, with A's own entries in place of S's
-__global__ void k_gen_fill(Sell A, Csr V, int64_t *qptr, const int32_t *__restrict__ agg,
-                           double omega) {
-    GRID_STRIDE(i, A.n) {
-        const int64_t e0 = V.rptr[i], e1 = V.rptr[i + 1];
-        const double w = omega / A.diag[i];
-        int64_t s = e0, q0 = e0;
-        for_row_entries(A, (int32_t)i, [&](int32_t, int64_t) { ++q0; });
-        qptr[i] = q0;
-        int64_t q = q0;  // end of the aggregates found so far
-        for_row_entries(A, (int32_t)i, [&](int32_t j, int64_t e) {
-            const double a = e < 0 ? A.diag[j] : A.val[e], at = e < 0 ? A.diag[j] : A.valT[e];
-            V.col[s] = j;
-            V.val[s] = a;
-            V.valT[s] = at;
-            ++s;
-            const int32_t c = A.n + agg[j];
-            int64_t k = q0;
-            while (k < q && V.col[k] != c) ++k;
-            if (k == q) {
-                V.col[k] = c;
-                V.val[k] = V.valT[k] = 0.0;
-                ++q;
-            }
-            V.val[k] = V.val[k] + a;
-            V.valT[k] = V.valT[k] + at;
-        });
-        const int32_t own = A.n + agg[i];
-        for (int64_t k = q0; k < e1; ++k) {
-            const double p = V.col[k] == own ? 1.0 : 0.0;
-            V.val[k] = p - w * V.val[k];
-            V.valT[k] = p - w * V.valT[k];
-        }
-    }
 }
 
 // W: the members of row c (value 1, columns j), then its P^T A entries
@@ -3061,7 +3012,8 @@ static void rop_values(Level &L, double omega, hipStream_t st) {
     if (L.R.sptr) fill(L.R);
     else fill(L.Rc);
     if (L.Uc.rptr) {
-        k_up_fill<<<grid_n((int64_t)L.n * kUpLanes), kBlock, 0, st>>>(L.A, L.Uc, L.agg, omega);
+        k_up_fill<false><<<grid_n((int64_t)L.n * kUpLanes), kBlock, 0, st>>>(L.A, L.Uc, nullptr,
+                                                                           L.agg, omega);
         if (L.Uc.val32) {
             k_rop_f32<<<grid_n(L.Uc.nnz), kBlock, 0, st>>>(L.Uc.val, L.Uc.val32, L.Uc.nnz);
             k_rop_f32<<<grid_n(L.Uc.nnz), kBlock, 0, st>>>(L.Uc.valT, L.Uc.valT32, L.Uc.nnz);
@@ -3183,7 +3135,8 @@ static void ensure_gen(ldu_t *h, const ldu_gamg_opts &o, hipStream_t st) {
         if (L.g_wide) continue;  // found now
         const bool fresh = L.g_ready && L.g_omega == o.omega;
         if (!fresh) {
-            k_gen_fill<<<grid_n(L.n), kBlock, 0, st>>>(L.A, L.V, L.qptr, L.agg, o.omega);
+            k_up_fill<true><<<grid_n((int64_t)L.n * kUpLanes), kBlock, 0, st>>>(
+                L.A, L.V, L.qptr, L.agg, o.omega);
             k_w_values<<<grid_n(L.W.nnz), kBlock, 0, st>>>(L.W.nnz, L.n, L.W, L.w_src0, L.w_srcn,
                                                           L.w_src, L.A.val, L.A.valT, L.A.diag);
             L.g_omega = o.omega;
