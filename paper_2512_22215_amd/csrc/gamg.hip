@@ -1165,7 +1165,8 @@ k_vc_restrict(int32_t nc, const int32_t *__restrict__ start, const int32_t *__re
 constexpr int kGatherPairs = 512;
 
 __global__ void k_rop_count(int32_t nc, const int32_t *__restrict__ start,
-                            const int32_t *__restrict__ cells, Sell A, int64_t *cnt, int *wide) {
+                            const int32_t *__restrict__ cells, Sell A, int64_t *cnt,
+                            int64_t *wide) {
     GRID_STRIDE(c, nc) {
         int64_t m = 0;
         for (int32_t k = start[c]; k < start[c + 1]; ++k) {
@@ -1616,7 +1617,7 @@ struct HeldAggregates {
 // row lengths of U and V: the row's entries (with the diagonal) and the
 // distinct aggregates they lie in; *wide for a row of too many
 __global__ void __launch_bounds__(kBlock)
-k_up_count(Sell A, const int32_t *__restrict__ agg, int64_t *cnt, int *wide) {
+k_up_count(Sell A, const int32_t *__restrict__ agg, int64_t *cnt, int64_t *wide) {
     const int l = threadIdx.x % kUpLanes;
     const int g0 = (threadIdx.x & 63) - l;  // the group's first lane
     const uint64_t mine = ((uint64_t(1) << kUpLanes) - 1) << g0;
@@ -2905,12 +2906,12 @@ static void up_structure(ldu_t *h, Level &L, hipStream_t st) {
     U.n = L.n;
     U.rptr = h->gamg_arena.get<int64_t>((size_t)L.n + 1);
     int64_t *cnt = tmp.get<int64_t>(L.n);
-    int *wide = tmp.get<int>(1), hwide = 0;
-    k_set_int<<<1, 1, 0, st>>>(wide, 0);
+    int64_t *wide = tmp.get<int64_t>(1), hwide = 0;
+    HIP_CHECK(hipMemsetAsync(wide, 0, sizeof(int64_t), st));
     k_up_count<<<grid_n((int64_t)L.n * kUpLanes), kBlock, 0, st>>>(L.A, L.agg, cnt, wide);
     exclusive_scan_i64(cnt, U.rptr, L.n, tmp, st);
     HIP_CHECK(hipMemcpyAsync(&U.nnz, U.rptr + L.n, sizeof(int64_t), hipMemcpyDeviceToHost, st));
-    HIP_CHECK(hipMemcpyAsync(&hwide, wide, sizeof(int), hipMemcpyDeviceToHost, st));
+    HIP_CHECK(hipMemcpyAsync(&hwide, wide, sizeof(int64_t), hipMemcpyDeviceToHost, st));
     HIP_CHECK(hipStreamSynchronize(st));
     if (hwide) return;
     U.col = h->gamg_arena.get<int32_t>(U.nnz);
@@ -3066,73 +3067,127 @@ static void ensure_rop(ldu_t *h, const ldu_gamg_opts &o, hipStream_t st) {
     }
 }
 
-// V and W for the small levels of the other Jacobi cycles: structure once per
-// hierarchy, values again after new coefficients or another omega, FP32 copies
-// once the FP32 path is in use
-static void gen_structure(ldu_t *h, size_t l, hipStream_t st) {
-    Arena::Step step(h->gamg_arena);
-    Level L = h->levels[l];  // a copy, as in rop_structure
-    const Level &C = h->levels[l + 1];
+// the values at up to 3 kMaxLevels addresses, for one look of the host
+struct Sizes {
+    const int64_t *at[3 * kMaxLevels];
+    int n = 0;
+};
+__global__ void k_sizes(Sizes s, int64_t *out) {
+    for (int k = threadIdx.x; k < s.n; k += blockDim.x) out[k] = *s.at[k];
+}
+static std::vector<int64_t> read_sizes(const Sizes &s, Arena &tmp, hipStream_t st) {
+    std::vector<int64_t> v(s.n);
+    int64_t *out = tmp.get<int64_t>(s.n);
+    k_sizes<<<1, kWave, 0, st>>>(s, out);
+    HIP_CHECK(hipMemcpyAsync(v.data(), out, sizeof(int64_t) * s.n, hipMemcpyDeviceToHost, st));
+    HIP_CHECK(hipStreamSynchronize(st));
+    return v;
+}
+
+// V's and W's structure for the small levels that have none yet, all levels in
+// step: the host looks at their sizes twice in all.  With three looks a level
+// the default set-up took 9.2 ms on a 300 x 200 x 1 mesh and 12.6 on 40 x 37 x
+// 31, now 8.1 and 11.2 (before there were V and W 8.3 and 10.7)
+static void gen_structures(ldu_t *h, hipStream_t st) {
+    struct Build {
+        size_t l;
+        Level L;  // a copy, as in rop_structure
+        int64_t *cnt, *tcnt, *tstart, *wide, total;
+        int32_t *tcol, *rdeg;
+    };
+    std::vector<Build> todo;
+    for (size_t l = 0; l + 1 < h->levels.size(); ++l) {
+        const Level &L = h->levels[l];
+        if (L.n <= kUpRows && !L.g_wide && !L.V.rptr) todo.push_back({l, L});
+    }
+    if (todo.empty()) return;
     Arena &ar = h->gamg_arena;
+    Arena::Step step(ar);
     Arena tmp(&h->pool);
     auto bounds = [&](Csr &M, int32_t n, const int64_t *cnt) {
         M = Csr{};
         M.n = n;
         M.rptr = ar.get<int64_t>((size_t)n + 1);
         exclusive_scan_i64(cnt, M.rptr, n, tmp, st);
-        HIP_CHECK(hipMemcpyAsync(&M.nnz, M.rptr + n, sizeof(int64_t), hipMemcpyDeviceToHost, st));
+        return M.rptr + n;
     };
-    auto arrays = [&](Csr &M) {
-        M.col = ar.get<int32_t>(M.nnz);
-        M.val = ar.get<double>(M.nnz);
-        M.valT = ar.get<double>(M.nnz);
-        M.group = csr_group(M.nnz, M.n);
+    auto arrays = [&](Csr &M, int64_t nnz) {
+        M.nnz = nnz;
+        M.col = ar.get<int32_t>(nnz);
+        M.val = ar.get<double>(nnz);
+        M.valT = ar.get<double>(nnz);
+        M.group = csr_group(nnz, M.n);
     };
-    int64_t *cnt = tmp.get<int64_t>(L.n), *tcnt = tmp.get<int64_t>(C.n);
-    int64_t *tstart = tmp.get<int64_t>((size_t)C.n + 1);
-    int *wide = tmp.get<int>(1), hwide = 0;
-    int64_t total = 0;
-    k_set_int<<<1, 1, 0, st>>>(wide, 0);
-    k_up_count<<<grid_n((int64_t)L.n * kUpLanes), kBlock, 0, st>>>(L.A, L.agg, cnt, wide);
-    k_rop_count<<<grid_n(C.n), kBlock, 0, st>>>(C.n, L.aggStart, L.aggCells, L.A, tcnt, wide);
-    bounds(L.V, L.n, cnt);
-    exclusive_scan_i64(tcnt, tstart, C.n, tmp, st);
-    HIP_CHECK(hipMemcpyAsync(&total, tstart + C.n, sizeof(int64_t), hipMemcpyDeviceToHost, st));
-    HIP_CHECK(hipMemcpyAsync(&hwide, wide, sizeof(int), hipMemcpyDeviceToHost, st));
-    HIP_CHECK(hipStreamSynchronize(st));
-    if (hwide) {
-        h->levels[l].g_wide = true;
-        return;
+    int64_t *wide = tmp.get<int64_t>(todo.size());
+    HIP_CHECK(hipMemsetAsync(wide, 0, sizeof(int64_t) * todo.size(), st));
+    Sizes first;
+    for (Build &b : todo) {
+        Level &L = b.L;
+        const Level &C = h->levels[b.l + 1];
+        b.wide = wide++;
+        b.cnt = tmp.get<int64_t>(L.n);
+        b.tcnt = tmp.get<int64_t>(C.n);
+        b.tstart = tmp.get<int64_t>((size_t)C.n + 1);
+        k_up_count<<<grid_n((int64_t)L.n * kUpLanes), kBlock, 0, st>>>(L.A, L.agg, b.cnt, b.wide);
+        k_rop_count<<<grid_n(C.n), kBlock, 0, st>>>(C.n, L.aggStart, L.aggCells, L.A, b.tcnt,
+                                                    b.wide);
+        first.at[first.n++] = bounds(L.V, L.n, b.cnt);
+        exclusive_scan_i64(b.tcnt, b.tstart, C.n, tmp, st);
+        first.at[first.n++] = b.tstart + C.n;
+        first.at[first.n++] = b.wide;
     }
-    arrays(L.V);
-    L.qptr = ar.get<int64_t>(L.n);
-    int32_t *tcol = tmp.get<int32_t>(total), *rdeg = tmp.get<int32_t>(C.n);
-    L.w_src = ar.get<int64_t>(total);
-    k_rop_gather<<<grid_n((int64_t)C.n * kWave), kBlock, 0, st>>>(C.n, L.aggStart, L.aggCells, L.A,
-                                                                 tstart, tcol, L.w_src, rdeg);
-    k_w_count<<<grid_n(C.n), kBlock, 0, st>>>(C.n, L.aggStart, rdeg, tcnt);
-    bounds(L.W, C.n, tcnt);
-    HIP_CHECK(hipStreamSynchronize(st));
-    arrays(L.W);
-    L.w_src0 = ar.get<int64_t>(L.W.nnz);
-    L.w_srcn = ar.get<int32_t>(L.W.nnz);
-    k_w_link<<<grid_n(C.n), kBlock, 0, st>>>(C.n, L.n, L.W, L.aggStart, L.aggCells, tstart, tcol,
-                                            L.w_src0, L.w_srcn);
+    const std::vector<int64_t> v = read_sizes(first, tmp, st);
+    Sizes second;
+    for (size_t k = 0; k < todo.size(); ++k) {
+        Build &b = todo[k];
+        Level &L = b.L;
+        const Level &C = h->levels[b.l + 1];
+        if (v[3 * k + 2]) {
+            L = h->levels[b.l];
+            L.g_wide = true;
+            continue;
+        }
+        arrays(L.V, v[3 * k]);
+        b.total = v[3 * k + 1];
+        L.qptr = ar.get<int64_t>(L.n);
+        b.tcol = tmp.get<int32_t>(b.total);
+        b.rdeg = tmp.get<int32_t>(C.n);
+        L.w_src = ar.get<int64_t>(b.total);
+        k_rop_gather<<<grid_n((int64_t)C.n * kWave), kBlock, 0, st>>>(
+            C.n, L.aggStart, L.aggCells, L.A, b.tstart, b.tcol, L.w_src, b.rdeg);
+        k_w_count<<<grid_n(C.n), kBlock, 0, st>>>(C.n, L.aggStart, b.rdeg, b.tcnt);
+        second.at[second.n++] = bounds(L.W, C.n, b.tcnt);
+    }
+    if (second.n) {
+        const std::vector<int64_t> w = read_sizes(second, tmp, st);
+        size_t q = 0;
+        for (Build &b : todo) {
+            Level &L = b.L;
+            const Level &C = h->levels[b.l + 1];
+            if (L.g_wide) continue;
+            arrays(L.W, w[q++]);
+            L.w_src0 = ar.get<int64_t>(L.W.nnz);
+            L.w_srcn = ar.get<int32_t>(L.W.nnz);
+            k_w_link<<<grid_n(C.n), kBlock, 0, st>>>(C.n, L.n, L.W, L.aggStart, L.aggCells,
+                                                    b.tstart, b.tcol, L.w_src0, L.w_srcn);
+            L.g_ready = false;
+        }
+    }
     HIP_CHECK(hipGetLastError());
-    HIP_CHECK(hipStreamSynchronize(st));  // tmp is released after this point
-    L.g_ready = false;
-    h->levels[l] = L;
-    step.done();
+    for (const Build &b : todo) h->levels[b.l] = b.L;
+    step.done();  // tmp's chunks are used again in this stream's order
 }
 
+// V and W for the small levels of the other Jacobi cycles: structure once per
+// hierarchy, values again after new coefficients or another omega, FP32 copies
+// once the FP32 path is in use
 static void ensure_gen(ldu_t *h, const ldu_gamg_opts &o, hipStream_t st) {
     if (!gen_cycle(o)) return;
+    gen_structures(h, st);
     const bool f32 = h->L0.A.val32 != nullptr;
     for (size_t l = 0; l + 1 < h->levels.size(); ++l) {
         Level &L = h->levels[l];
         if (L.n > kUpRows || L.g_wide) continue;
-        if (!L.V.rptr) gen_structure(h, l, st);
-        if (L.g_wide) continue;  // found now
         const bool fresh = L.g_ready && L.g_omega == o.omega;
         if (!fresh) {
             k_up_fill<true><<<grid_n((int64_t)L.n * kUpLanes), kBlock, 0, st>>>(
