@@ -816,20 +816,28 @@ static void renumber_levels(ldu_t *h, hipStream_t st) {
     HIP_CHECK(hipStreamSynchronize(st));  // tmp is released after this point
 }
 
-// new values of the original levels into the inner ones
-static void refresh_inner(ldu_t *h, hipStream_t st) {
+// new values of the original levels into the inner ones, by the first solve
+// that runs on those: callers that go on with products, diagonal CG or
+// Gauss-Seidel cycles have no use for them (set_coeffs on a shuffled
+// 100 x 90 x 80 mesh 685 us, with the copies 1000)
+static void refresh_inner(ldu_t *h, int smoother, hipStream_t st) {
+    if (!h->inner_stale || smoother != LDU_SMOOTH_JACOBI) return;
     for (size_t l = 0; l < h->inner.size(); ++l) {
         Level &N = h->inner[l];
         if (N.src) renumbered_values(h->levels[l].A, N, st);
         refresh_f32(N, st);
         N.singular = h->levels[l].singular;
     }
+    NumberingScope scope(h, smoother);
+    refresh_rop(h, st);
+    h->inner_stale = false;
 }
 
 void gamg_build(ldu_t *h, const ldu_gamg_opts &o, hipStream_t st) {
     h->gamg_ready = false;
     h->levels.clear();
     h->inner.clear();
+    h->inner_stale = false;
     h->gamg_arena.release_all();
     Arena &ar = h->gamg_arena;
     h->levels.push_back(h->L0);
@@ -902,10 +910,8 @@ void gamg_refresh_values(ldu_t *h, hipStream_t st) {
     }
     detect_singular(h, h->levels.back(), st);
     h->dic_ready = false;
-    refresh_inner(h, st);
+    h->inner_stale = !h->inner.empty();
     refresh_rop(h, st);
-    NumberingScope scope(h, LDU_SMOOTH_JACOBI);
-    if (scope.active()) refresh_rop(h, st);
 }
 
 // DIC pivots of the coarsest level (diagonal incomplete Cholesky; the paper's
@@ -3249,6 +3255,7 @@ static void fill_level_stats(ldu_t *h, ldu_stats *stats) {
 
 void gamg_vcycle64(ldu_t *h, const double *r, double *e, const ldu_gamg_opts &o, bool tr,
                    hipStream_t st) {
+    refresh_inner(h, o.smoother, st);
     NumberingScope scope(h, o.smoother);
     const InnerVectors v = inner_vectors(h, scope.active(), r, e, false, st);
     set_scalars_for_solve(h, 0.0, 0, st);
@@ -3726,6 +3733,7 @@ static int gamg_mixed_run(ldu_t *h, const double *b, double *x, const ldu_gamg_o
 template <class Run>
 static int in_numbering(ldu_t *h, int smoother, const double *b, double *x, hipStream_t st,
                         Run &&run) {
+    refresh_inner(h, smoother, st);
     NumberingScope scope(h, smoother);
     const InnerVectors v = inner_vectors(h, scope.active(), b, x, true, st);
     const int rc = run(v.in, v.out);

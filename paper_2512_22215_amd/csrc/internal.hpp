@@ -323,6 +323,7 @@ struct ldu_t {
     std::vector<ldu::Level> inner;
     int32_t *inner_order = nullptr;          // cell of each inner position, level 0
     double *inner_b = nullptr, *inner_x = nullptr;
+    bool inner_stale = false;        // the renumbered levels wait for the last coefficients
     bool gamg_ready = false;
     ldu_gamg_opts gamg_opts{};
     bool f32_ready = false;          // FP32 copies of level values exist
