@@ -631,18 +631,30 @@ __global__ void k_rn_degree(Sell A, const int32_t *order, int32_t *deg) {
 }
 
 // columns and sources: an entry's place in its row is the number of entries
-// with a smaller new column.  Rows of at most kRnRegs stored entries are held
-// in registers (all loads of a row together), longer ones are read again for
-// every entry.
+// with a smaller new column.  A lane holds a row of at most kRnRegs stored
+// entries in registers (all loads of a row together).  A longer one is shared
+// by the wave, 64 entries held and compared with 64 at a time.  A lane that
+// read the row again for every entry added 9 ms to the set-up for one row of 200
+// entries and 40 ms for one of 400 (506,000 cells: 20 ms without renumbering);
+// now 0.9 and 8 ms, the most of it the members of the long row's aggregate being
+// sorted once more.
 constexpr int kRnRegs = 24;
 
 __global__ void __launch_bounds__(kBlock)
 k_rn_fill(Sell A, const int32_t *order, const int32_t *place, Slots slot, int32_t *col,
           int32_t *src) {
-    GRID_STRIDE(p, A.n) {
-        const int32_t i = order[p];
-        const int64_t ps = A.iperm ? (int64_t)A.iperm[i] : (int64_t)i;
-        const int w = row_len(A, ps);
+    const int lane = threadIdx.x & 63;
+    const GridRange gr = grid_range(A.n, kBlock);
+    for (int64_t p0 = gr.begin + (threadIdx.x - lane); p0 < gr.end; p0 += gr.step) {
+        const int64_t p = p0 + lane;
+        int32_t i = 0;
+        int64_t ps = 0;
+        int w = 0;
+        if (p < gr.end) {
+            i = order[p];
+            ps = A.iperm ? (int64_t)A.iperm[i] : (int64_t)i;
+            w = row_len(A, ps);
+        }
         if (w <= kRnRegs) {
             int32_t e[kRnRegs], c[kRnRegs];
 #pragma unroll
@@ -661,21 +673,33 @@ k_rn_fill(Sell A, const int32_t *order, const int32_t *place, Slots slot, int32_
                 col[to] = c[k];
                 src[to] = e[k];
             }
-            continue;
         }
-        for (int k = 0; k < w; ++k) {
-            const int64_t e = entry_at(A, ps, k);
-            const int32_t j = A.col[e];
-            if (j == i) continue;
-            const int32_t c = place[j];
-            int rank = 0;
-            for (int q = 0; q < w; ++q) {
-                const int32_t o = A.col[entry_at(A, ps, q)];
-                rank += o != i && place[o] < c;
+        for (uint64_t left = __ballot(w > kRnRegs); left; left &= left - 1) {
+            const int from = __ffsll((unsigned long long)left) - 1;
+            const int32_t ri = __shfl(i, from);
+            const int64_t rps = __shfl(ps, from);
+            const int rw = __shfl(w, from);
+            // entry k of the row and its new column (INT32_MAX: padding or none)
+            auto load = [&](int k, int32_t &e) {
+                if (k >= rw) return (int32_t)INT32_MAX;
+                e = (int32_t)entry_at(A, rps, k);
+                const int32_t j = A.col[e];
+                return j != ri ? place[j] : (int32_t)INT32_MAX;
+            };
+            for (int k0 = 0; k0 < rw; k0 += kWave) {
+                int32_t e = 0, other = 0;
+                const int32_t c = load(k0 + lane, e);
+                int rank = 0;
+                for (int q0 = 0; q0 < rw; q0 += kWave) {
+                    const int32_t cq = q0 == k0 ? c : load(q0 + lane, other);
+                    for (int u = 0; u < kWave; ++u) rank += __shfl(cq, u) < c;
+                }
+                if (c != INT32_MAX) {
+                    const int64_t to = slot(p0 + from, rank);
+                    col[to] = c;
+                    src[to] = e;
+                }
             }
-            const int64_t to = slot(p, rank);
-            col[to] = c;
-            src[to] = (int32_t)e;
         }
     }
 }
