@@ -240,7 +240,9 @@ int gamg_level_export(ldu_handle h, int level, int32_t *agg, int32_t *owner,
  * smallest column of their slot (the k-th entries of a slice's rows) for the
  * slots that span at most 65535 columns, the others reading 32-bit columns;
  * 0 when every slot reads 32-bit columns.  Either way the products are the
- * same bit for bit. */
+ * same bit for bit.  On a mesh of scattered numbering, whose GAMG cycles run on
+ * renumbered copies of the large levels, this and ldu_level_downleg report those
+ * copies (level 0's layout: the matrix as created). */
 int ldu_level_layout(ldu_handle h, int level, int *compressed, int *col16);
 /* The form of level l's one-pass down leg, r_c = P^T (I - omega A D^-1) r,
  * which cycles with one Jacobi pre-sweep from zero and no correction scaling

@@ -975,8 +975,6 @@ k_vc_zero(int32_t n, int64_t S, T *__restrict__ e, const DevScalars *ds) {
     });
 }
 
-// e_out = e + omega (r - A e) / D; DOT also accumulates the block partials of
-// rdot . e_out (the preconditioned CG's r . z, saving a pass over both)
 // The finer level's unscaled correction e_f += P e_c, applied by the kernel
 // that produces e_c: row a adds its value to the members of aggregate a.
 constexpr int kCorrBatch = 8;  // aggregate members a fused correction handles at once
@@ -2891,9 +2889,6 @@ static void ensure_work32(ldu_t *h, hipStream_t st) {
     }
 }
 
-// buffers and factors a cycle needs beyond the hierarchy: the second
-// ping-pong vector of the two-stage smoother (three or more inner steps) and
-// the DIC pivots of the coarsest level
 // lanes per row of a CSR operator: the power of two nearest mean row length /
 // entries per lane
 static int csr_group(int64_t nnz, int32_t n) {
@@ -3224,6 +3219,10 @@ static void refresh_rop(ldu_t *h, hipStream_t st) {
             rop_values(h->levels[l], h->levels[l].r_omega, st);
 }
 
+// work vectors, operators and factors that a cycle needs beyond the hierarchy,
+// made by the first cycle that asks for them: among them the second ping-pong
+// vector of the two-stage smoother (three or more inner steps) and the DIC pivots
+// of the coarsest level
 static VCtx make_ctx(ldu_t *h, const ldu_gamg_opts &o, bool tr, hipStream_t st) {
     ensure_work(h);
     ensure_rop(h, o, st);

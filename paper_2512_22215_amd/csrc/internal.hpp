@@ -82,8 +82,16 @@ constexpr int64_t kFusedBicgCells = 1 << 16;
 #define LDU_CG_BLOCKS 1024
 #endif
 constexpr int kCgBlocks = LDU_CG_BLOCKS;
-// meshes of at least this many cells are checked for a scattered numbering
-// when a hierarchy is built; levels above kRenumberRows are renumbered
+// Meshes of at least this many cells are checked for a scattered numbering
+// when a hierarchy is built; levels above kRenumberRows are renumbered.
+// Shuffled boxes, levels as they are and renumbered, default GAMG to 1e-8: 48^3
+// 9.9 and 10.7 ms, 64^3 17.0 and 13.3, 80^3 20.2 and 14.9, 100^3 45.1 and 26.3;
+// CG + V-cycle, merged: 4.1 and 4.1, 7.3 and 5.8, 11.5 and 7.8, 26.2 and 13.2;
+// set-up 17.2 and 19.1, 21.2 and 22.7, 24.8 and 26.1, 31.0 and 34.4.  From
+// 500,000 cells one solve pays for the copies; below, the break-even lies near
+// 64^3 and a caller of one loose solve would lose.  Renumbering levels of more
+// than 4000, 20,000 and 100,000 rows: set-up and GAMG at 128^3 46.2 + 34.3, 45.4
+// + 34.4 and 44.4 + 34.8 ms, CG + V-cycle at 100^3 13.3, 13.4 and 13.9 ms.
 #ifndef LDU_RENUMBER_CELLS
 #define LDU_RENUMBER_CELLS 500000
 #endif

@@ -636,7 +636,7 @@ __global__ void k_rn_degree(Sell A, const int32_t *order, int32_t *deg) {
 // by the wave, 64 entries held and compared with 64 at a time.  A lane that
 // read the row again for every entry added 9 ms to the set-up for one row of 200
 // entries and 40 ms for one of 400 (506,000 cells: 20 ms without renumbering);
-// now 0.9 and 8 ms, the most of it the members of the long row's aggregate being
+// now 1 and 9 ms, the most of it the members of the long row's aggregate being
 // sorted once more.
 constexpr int kRnRegs = 24;
 
