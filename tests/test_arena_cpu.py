@@ -129,8 +129,8 @@ int main() {
     a.alloc(45 * MiB);                       // one of 60 MiB
     CHECK(room < left);
     const size_t after = room;
-    char *p = static_cast<char *>(a.alloc(9 * MiB));   // in the second chunk
-    char *q = static_cast<char *>(a.alloc(14 * MiB));  // in the third
+    char *q = static_cast<char *>(a.alloc(14 * MiB));  // in the third chunk
+    char *p = static_cast<char *>(a.alloc(9 * MiB));   // in the second
     char *s = static_cast<char *>(a.alloc(1));
     CHECK(room == after && p && q && s);
     a.reserve(300);
