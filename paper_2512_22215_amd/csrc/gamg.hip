@@ -3611,7 +3611,7 @@ static int pcg_gamg_mixed_run(ldu_t *h, const double *b, double *x, const ldu_pc
     const int n = L.n;
     const int64_t S = L.A.nslices;
     const int G = stream_grid_slices(S);
-    const int Gr = std::min(G, kCgBlocks);
+    const int Gr = cg_blocks(n, G);
     ensure_hist(h, (int64_t)o.max_refine + 2);
     fill_level_stats(h, stats);
     if (stats) stats->history_count = 0;

@@ -82,6 +82,13 @@ constexpr int64_t kFusedBicgCells = 1 << 16;
 #define LDU_CG_BLOCKS 1024
 #endif
 constexpr int kCgBlocks = LDU_CG_BLOCKS;
+// above this many cells they run on kMaxGrid blocks: with four waves a SIMD the
+// streams of one kernel leave HBM bandwidth unused, and reading twice the partials
+// costs less.  1024 and 2048 blocks, us an iteration of diagonal CG in FP64 and
+// mixed: 128^3 61.9 and 62.0, 41.5 and 42.9; 160^3 119.2 and 120.2, 72.2 and
+// 72.8; 200^3 240.0 and 236.3, 130.8 and 131.0; 256^3 502 and 492, 293 and 278
+// (with reductions of their own: 496, 283)
+constexpr int64_t kCgWideCells = 6000000;
 // Meshes of at least this many cells are checked for a scattered numbering
 // when a hierarchy is built; levels above kRenumberRows are renumbered.
 // Shuffled boxes, levels as they are and renumbered, default GAMG to 1e-8: 48^3
@@ -363,6 +370,11 @@ inline int stream_grid_slices(int64_t nslices) {
     if (g >= 64) g &= ~int64_t(7);
     if (g < 1) g = 1;
     return (int)g;
+}
+// blocks of a CG form's vector updates over n cells, at most G
+inline int cg_blocks(int64_t n, int G) {
+    const int most = n > kCgWideCells ? kMaxGrid : kCgBlocks;
+    return G < most ? G : most;
 }
 inline int64_t slices_of(int64_t n) { return (n + kWave - 1) / kWave; }
 

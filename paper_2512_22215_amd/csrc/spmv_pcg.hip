@@ -596,7 +596,7 @@ int pcg_fp64(ldu_t *h, const double *b, double *x, const ldu_pcg_opts &o, bool t
     // products on plain slices: blocks past the cap would only add zeros; the
     // residual update: see kCgBlocks
     const int Gq = A.pdeg ? G : std::min(G, kPlainF64ProductBlocks);
-    const int Gr = std::min(G, kCgBlocks);
+    const int Gr = cg_blocks(n, G);
     double *const p0 = fused ? h->z : h->p;  // where a (re)start's direction goes
     double *const pbuf[2] = {fused ? h->p2 : h->p, h->p};  // direction after j iterations: j & 1
     if (own_hist) ensure_hist(h, (int64_t)o.max_iter + 2);
@@ -936,7 +936,7 @@ int pbicg_fp64(ldu_t *h, const double *b, double *x, const ldu_pcg_opts &o, bool
         h->zt = h->arena.get<double>(n);
     }
     const int Gq = A.pdeg ? G : std::min(G, kPlainF64ProductBlocks);
-    const int Gr = std::min(G, kCgBlocks);
+    const int Gr = cg_blocks(n, G);
     double *const p0 = fused ? h->z : h->p, *const pt0 = fused ? h->zt : h->pt;
     double *const pbuf[2] = {fused ? h->p2 : h->p, h->p};
     double *const ptbuf[2] = {fused ? h->pt2 : h->pt, h->pt};
@@ -1191,7 +1191,7 @@ int pcg_mixed(ldu_t *h, const double *b, double *x, const ldu_pcg_opts &o, bool 
     const int n = L.n;
     const int64_t S = L.A.nslices;
     const int G = stream_grid_slices(S);
-    const int Gr = std::min(G, kCgBlocks);
+    const int Gr = cg_blocks(n, G);
     ensure_hist(h, (int64_t)o.max_refine + 2);
     fill_stats_common(stats);
     set_scalars_for_solve(h, o.rel_tol, o.max_refine, st);
