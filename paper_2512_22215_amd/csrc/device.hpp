@@ -57,6 +57,12 @@ __device__ __forceinline__ GridRange grid_range(int64_t n, int per) {
     const int64_t lo = (blockIdx.x % nx) * R, hi = lo + R < n ? lo + R : n;
     return {lo + (int64_t)(blockIdx.x / nx) * per, hi, (int64_t)(G / nx) * per, true};
 }
+// Kernels that read each array once in order have nothing to share and keep the
+// whole grid side by side (STREAM_STRIDE): the check of 2M values in eighths 9.2
+// us, side by side 6.3.
+#define STREAM_STRIDE(i, n)                                                             \
+    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < (n);           \
+         i += (int64_t)gridDim.x * blockDim.x)
 #define GRID_STRIDE(i, n)                                                            \
     for (GridRange gr_ = grid_range(n, blockDim.x); gr_.once; gr_.once = false)      \
         for (int64_t i = gr_.begin + threadIdx.x; i < gr_.end; i += gr_.step)

@@ -1391,7 +1391,7 @@ __global__ void k_rop_values(int64_t nnz, M R, const int64_t *__restrict__ rs0,
 }
 
 __global__ void k_rop_f32(const double *a, float *b, int64_t n) {
-    GRID_STRIDE(i, n)
+    STREAM_STRIDE(i, n)
         b[i] = (float)a[i];
 }
 

@@ -122,7 +122,7 @@ __global__ void k_validate(int32_t n, int64_t nf, const int32_t *own, const int3
 }
 
 __global__ void k_check_finite(const double *a, int64_t n, int *flag) {
-    GRID_STRIDE(i, n)
+    STREAM_STRIDE(i, n)
         if (!isfinite(a[i])) atomicOr(flag, 2);
 }
 
@@ -477,7 +477,7 @@ void aggregate_columns(Level &L, Arena &ar, Arena &tmp, hipStream_t st) {
 }
 
 __global__ void k_to_f32(const double *a, float *b, int64_t n) {
-    GRID_STRIDE(i, n)
+    STREAM_STRIDE(i, n)
         b[i] = (float)a[i];
 }
 
