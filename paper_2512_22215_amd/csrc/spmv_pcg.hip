@@ -746,6 +746,47 @@ __device__ __forceinline__ void plain_pair(const SellView<double> &A, const doub
     }
 }
 
+// the same over compressed slices, with the cache policy of A.stream as there
+// (800,000 cells of a band graph, 96 MB of matrix: streamed 94 us an iteration,
+// kept 79; 1,500,000 cells stream)
+template <bool NT, class X, class XT>
+__device__ __forceinline__ void cmp_pair(const SellView<double> &A, const double *valT, int64_t s,
+                                         int lane, const X &x, const XT &xt, double &q,
+                                         double &qt) {
+    constexpr int B = 12;
+    const int64_t b0 = A.sptr[s];
+    const int w = A.pdeg[s * kWave + lane];
+    const int32_t *cp = A.col + b0 + lane;
+    const double *vp = A.val + b0 + lane, *tp = valT + b0 + lane;
+    SliceOffsets so;
+    for (int k = 0; k < w; k += B) {
+        int32_t c[B];
+        double v[B], vt[B], xv[B], xtv[B];
+#pragma unroll
+        for (int u = 0; u < B; ++u) {
+            const bool has = k + u < w;
+            const int64_t o = so.next(has);
+            if (has) {
+                c[u] = vld<NT>(cp + o);
+                v[u] = vld<NT>(vp + o);
+                vt[u] = vld<NT>(tp + o);
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < B; ++u)
+            if (k + u < w) {
+                xv[u] = x(c[u]);
+                xtv[u] = xt(c[u]);
+            }
+#pragma unroll
+        for (int u = 0; u < B; ++u)
+            if (k + u < w) {
+                q = q + v[u] * xv[u];
+                qt = qt + vt[u] * xtv[u];
+            }
+    }
+}
+
 template <bool CMP, class X, class XT>
 __device__ __forceinline__ void pair_entries(const SellView<double> &A, const double *valT,
                                              int64_t s, int lane, const X &x, const XT &xt,
@@ -759,38 +800,8 @@ __device__ __forceinline__ void pair_entries(const SellView<double> &A, const do
             else plain_pair<false, false>(A, valT, s, lane, x, xt, q, qt);
         }
     } else {
-        constexpr int B = 12;
-        const int64_t b0 = A.sptr[s];
-        const int w = A.pdeg[s * kWave + lane];
-        const int32_t *cp = A.col + b0 + lane;
-        const double *vp = A.val + b0 + lane, *tp = valT + b0 + lane;
-        SliceOffsets so;
-        for (int k = 0; k < w; k += B) {
-            int32_t c[B];
-            double v[B], vt[B], xv[B], xtv[B];
-#pragma unroll
-            for (int u = 0; u < B; ++u) {
-                const bool has = k + u < w;
-                const int64_t o = so.next(has);
-                if (has) {
-                    c[u] = __builtin_nontemporal_load(cp + o);
-                    v[u] = __builtin_nontemporal_load(vp + o);
-                    vt[u] = __builtin_nontemporal_load(tp + o);
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < B; ++u)
-                if (k + u < w) {
-                    xv[u] = x(c[u]);
-                    xtv[u] = xt(c[u]);
-                }
-#pragma unroll
-            for (int u = 0; u < B; ++u)
-                if (k + u < w) {
-                    q = q + v[u] * xv[u];
-                    qt = qt + vt[u] * xtv[u];
-                }
-        }
+        if (A.stream) cmp_pair<true>(A, valT, s, lane, x, xt, q, qt);
+        else cmp_pair<false>(A, valT, s, lane, x, xt, q, qt);
     }
 }
 
